@@ -17,16 +17,21 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "liblg.so")
-SOURCES = ["lg_attend.hip", "lg_detect.hip", "lg_prune.hip", "lg_capi.hip", "lg_copy.hip"]
+# (source, extra flags); lg_attend.hip is compiled in parts, in parallel
+ATTEND_PARTS = 7
+SOURCES = ([("lg_attend.hip", ("-DLG_ATTEND_PART=%d" % i,)) for i in range(ATTEND_PARTS)] +
+           [(s, ()) for s in ("lg_detect.hip", "lg_prune.hip", "lg_capi.hip", "lg_copy.hip")])
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", INCLUDE, "-I", CSRC]
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+def _compile(unit) -> str:
+    src, extra = unit
+    part = "".join("_" + f.rsplit("=", 1)[-1] for f in extra)
+    obj = os.path.join(BUILD, os.path.splitext(src)[0] + part + ".o")
+    cmd = [HIPCC, *FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("hipcc failed for %s:\n%s\n%s" % (src, r.stdout, r.stderr))

@@ -13,15 +13,25 @@
 //               whose cap fits one split), else by its splits exchanging their partials through
 //               memory; no workgroup waits for one that may not have started (see the exchange
 //               below).
-//   merge       (bfloat16, the automatic choice otherwise) each split writes its partial and its
-//               logits to memory and attend_combine_mfma merges them in a second launch.
-//   portable    (float32 or bfloat16, any cap) attend_valu + attend_combine.
-// The bfloat16 sweep runs both products of the GQA group on 16x16x32 bf16 MFMA: K rows load
-// straight into the A operand of q.K^T (16 B per lane); V rows are loaded coalesced, staged
-// row-major in a wave-private LDS tile and read back with gfx950's transposing LDS load
-// (ds_read_b64_tr_b16) as the B operand of alpha.V; alpha enters that product as a pair of bf16
-// terms (hi + lo, within 2^-16).
+//   merge       (the automatic choice otherwise) each split writes its partial and its logits to
+//               memory and attend_combine_mfma merges them in a second launch.
+//   portable    (caps beyond 32768; test hook) attend_valu + attend_combine.
+// The exchange between splits is for bfloat16 caches whose cap is a multiple of 32; the other two
+// MFMA forms take both types and any cap up to 32768.
+// The sweep runs both products of the GQA group on the matrix cores; K rows load straight into the
+// A operand of q.K^T (16 B per lane).
+//   bfloat16: 16x16x32 bf16 MFMA. V rows are loaded coalesced, staged row-major in a wave-private
+//             LDS tile and read back with gfx950's transposing LDS load (ds_read_b64_tr_b16) as the
+//             B operand of alpha.V; alpha enters that product as a pair of bf16 terms (hi + lo,
+//             within 2^-16).
+//   float32:  16x16x4 f32 MFMA. V rows load straight into the B operand: lane (g, c) needs rows
+//             4 g + v of 4 consecutive dims, which are whole 256-byte stretches of a row, and alpha
+//             enters as the lane's own float32 values.
 #include "lg_internal.h"
+
+#ifndef LG_ATTEND_PART
+#error "compile with -DLG_ATTEND_PART=0 .. 6 (see the launchers at the end)"
+#endif
 
 namespace lg {
 
@@ -194,16 +204,43 @@ __device__ __forceinline__ SplitPlan split_plan(int n, int max_split) {
 // c + 8, step 2p; lanes c >= 8: A-row c, step 2p + 1). Rotating each 16-lane row by 8 lanes then
 // swaps the misplaced halves between the two registers (see fix_k).
 // DV: the V dims (and output dims) the workgroup handles, D or a part of it (see attend_mfma_body).
-template <int D, int DV = D>
+//
+// A float32 row is twice as long. Everything above counts bytes (a k-step is 64 bytes of each row),
+// so head_dim 64 is cut exactly like a bfloat16 head_dim 128; at head_dim 128 a block is one tile of
+// 16 slots (A-row i = slot i), which keeps a block at 16 KB and its registers as they are.
+// The f32 MFMA (128 of them a block, 32 cycles each) take about a quarter of the time the block's
+// bytes take, so the sweep stays bound by memory. Measured against the vector-ALU sweep that these
+// caches had (one wave per 64 slots, a 64-lane reduction per slot and head): batch 8, 32 / 8 heads,
+// head_dim 128, cap 2048 float32 215 -> 30 us a layer (119 MB); batch 5, 32 / 8 heads, head_dim 64,
+// bfloat16 at cap 1500 (no multiple of 32) 134 -> 17 us; batch 1, 4 / 4 heads, head_dim 64, cap 256
+// float32 49 -> 18 us.
+template <typename T, int D, int DV = D>
+struct Geo {
+  static constexpr bool F32 = sizeof(T) == 4;
+  static constexpr int NS = D * (int)sizeof(T) / 64;  // k-steps: 64 bytes of a K row each
+  static constexpr int MT = NS > 4 ? 1 : 2;           // tiles of 16 slots
+  static constexpr int BS = 16 * MT;                  // slots of a block
+  static constexpr int NV = DV * BS * (int)sizeof(T) / 1024;  // V loads of 16 bytes per lane
+  static constexpr int PPR = D * (int)sizeof(T) / 16;         // 16-byte pieces of a row
+  static constexpr int VPR = DV * (int)sizeof(T) / 16;        // ... of the workgroup's V dims
+  // Slot (within the block) of A-row i of tile mt.
+  __host__ __device__ static constexpr int slot(int i, int mt) {
+    return MT == 2 ? 8 * (i >> 2) + 4 * mt + (i & 3) : i;
+  }
+};
+
+template <typename T, int D, int DV = D>
 struct Block {
-  uint4 k[2][D / 32];
-  uint4 v[DV / 16];  // V rows, 16 bytes per lane (see load_v)
+  using G = Geo<T, D, DV>;
+  uint4 k[G::MT][G::NS];
+  uint4 v[G::NV];  // V rows, 16 bytes per lane (see load_v)
 };
 
 struct RowCtx {
-  const uint16_t* kbase;  // lane's K address at slot 0: A-row (c mod 8) of tile 0, dims 8g or
-                          // 32 + 8g (c < 8 or not) of k-steps 0 and 1
-  const uint16_t* vbase;  // lane's V address at slot 0 (see load_v)
+  const char* kbase;  // lane's K address at slot 0: A-row (c mod 8) of tile 0, the 16 bytes at 16g
+                      // or 64 + 16g (c < 8 or not) of k-steps 0 and 1
+  const char* vbase;  // lane's V address at slot 0 (see load_v)
+  int krow, vrow;     // the slots of a block that kbase and vbase stand for
   const int32_t* posb;
   int L, app, cap, n_eff;
   int jsuf;  // first slot of the recent suffix within the split (see attend_mfma_body)
@@ -215,35 +252,74 @@ struct RowCtx {
 };
 
 // Block loads, in two halves so a pipelined wave can issue the next block's V rows as soon as the
-// current ones are in LDS, before its q.K^T. K: see "K loads" (base folded in kbase). V: 16 bytes
-// per lane, DV / 8 lanes per row, so each load instruction reads 512 / DV consecutive rows of the
-// workgroup's DV dims in lane order (1 KB): lane l of instruction i holds row
-// blk + i (512 / DV) + l / (DV / 8) at dims 8 (l % (DV / 8)) (base folded in vbase). Rows stay
-// below cap because cap is a multiple of 32 on this path.
+// current ones are in LDS, before its q.K^T. K: see "K loads" (base folded in kbase). V, 16 bytes
+// per lane (base folded in vbase):
+//   bfloat16: DV / 8 lanes per row, so each load instruction reads 512 / DV consecutive rows of the
+//             workgroup's DV dims in lane order (1 KB): lane l of instruction i holds row
+//             blk + i (512 / DV) + l / (DV / 8) at dims 8 (l % (DV / 8)).
+//   float32:  lane (g, c) of instruction (mt, v, h) holds slot(4g + v, mt) at dims 64 h + 4 c.
+// RC (ragged cap): cap need not be a multiple of the block, so the rows of a block that reaches past
+// cap are clamped to the last one (they are dead slots; without the clamp the last row's block would
+// read past the cache). The test is uniform over the wave.
 template <int DV> constexpr int vrows_per_load() { return 512 / DV; }
-template <int D, bool NT, int DV>
-__device__ __forceinline__ void load_v(Block<D, DV>& B, const RowCtx& r, int blk) {
-  const uint16_t* vp = r.vbase + (size_t)blk * D;
-#pragma unroll
-  for (int i = 0; i < DV / 16; ++i) B.v[i] = ld_stream16<NT>(vp + i * vrows_per_load<DV>() * D);
+template <typename T, int D, int DV>
+__device__ __forceinline__ constexpr int v_off_row(int i) {
+  using G = Geo<T, D, DV>;
+  if (!G::F32) return i * vrows_per_load<DV>();
+  constexpr int H = DV / 64;
+  return G::slot((i / H) & 3, (i / H) >> 2);
+}
+template <typename T, int D, int DV>
+__device__ __forceinline__ constexpr int v_off_byte(int i) {
+  return Geo<T, D, DV>::F32 ? 256 * (i % (DV / 64)) : 0;
 }
 
-template <int D, bool NT, int DV>
-__device__ __forceinline__ void load_k(Block<D, DV>& B, const RowCtx& r, int blk, int lane) {
-  constexpr int NKK = D / 32;
-  const uint16_t* kp = r.kbase + (size_t)blk * D;
+template <typename T, int D, bool NT, bool RC, int DV>
+__device__ __forceinline__ void load_v(Block<T, D, DV>& B, const RowCtx& r, int blk) {
+  using G = Geo<T, D, DV>;
+  constexpr int RB = D * (int)sizeof(T);
+  if (!RC || blk + G::BS <= r.cap) {
+    const char* vp = r.vbase + (size_t)blk * RB;
 #pragma unroll
-  for (int mt = 0; mt < 2; ++mt) {
+    for (int i = 0; i < G::NV; ++i)
+      B.v[i] = ld_stream16<NT>(vp + v_off_row<T, D, DV>(i) * RB + v_off_byte<T, D, DV>(i));
+  } else {
 #pragma unroll
-    for (int kk = 0; kk < NKK; ++kk)  // k-step pair kk / 2; kk odd: A-rows 8..15 (slots + 16)
-      B.k[mt][kk] = ld_stream16<NT>(kp + (4 * mt + 16 * (kk & 1)) * D + 64 * (kk >> 1));
+    for (int i = 0; i < G::NV; ++i) {
+      const int row = min(blk + r.vrow + v_off_row<T, D, DV>(i), r.cap - 1) - r.vrow;
+      B.v[i] = ld_stream16<NT>(r.vbase + (ptrdiff_t)row * RB + v_off_byte<T, D, DV>(i));
+    }
   }
 }
 
-template <int D, bool NT, int DV>
-__device__ __forceinline__ void load_block(Block<D, DV>& B, const RowCtx& r, int blk, int lane) {
-  load_v<D, NT, DV>(B, r, blk);
-  load_k<D, NT, DV>(B, r, blk, lane);
+template <typename T, int D, bool NT, bool RC, int DV>
+__device__ __forceinline__ void load_k(Block<T, D, DV>& B, const RowCtx& r, int blk) {
+  using G = Geo<T, D, DV>;
+  constexpr int RB = D * (int)sizeof(T);
+  if (!RC || blk + G::BS <= r.cap) {
+    const char* kp = r.kbase + (size_t)blk * RB;
+#pragma unroll
+    for (int mt = 0; mt < G::MT; ++mt) {
+#pragma unroll
+      for (int kk = 0; kk < G::NS; ++kk)  // k-step pair kk / 2; kk odd: A-rows 8..15
+        B.k[mt][kk] = ld_stream16<NT>(kp + G::slot(8 * (kk & 1), mt) * RB + 128 * (kk >> 1));
+    }
+  } else {
+#pragma unroll
+    for (int mt = 0; mt < G::MT; ++mt) {
+#pragma unroll
+      for (int kk = 0; kk < G::NS; ++kk) {
+        const int row = min(blk + r.krow + G::slot(8 * (kk & 1), mt), r.cap - 1) - r.krow;
+        B.k[mt][kk] = ld_stream16<NT>(r.kbase + (ptrdiff_t)row * RB + 128 * (kk >> 1));
+      }
+    }
+  }
+}
+
+template <typename T, int D, bool NT, bool RC, int DV>
+__device__ __forceinline__ void load_block(Block<T, D, DV>& B, const RowCtx& r, int blk) {
+  load_v<T, D, NT, RC, DV>(B, r, blk);
+  load_k<T, D, NT, RC, DV>(B, r, blk);
 }
 
 struct Online {
@@ -261,8 +337,8 @@ template <int D> constexpr int vtile_stride() { return D + 8; }
 // (row-major; afterwards the V registers are free), stage_qk takes the suffix mask and runs q.K^T
 // (afterwards the K registers are free).
 template <int D, int DV>
-__device__ __forceinline__ void stage_v(const Block<D, DV>& B, const RowCtx& r, int blk, int g,
-                                        int c, uint16_t* vt) {
+__device__ __forceinline__ void stage_v(const Block<uint16_t, D, DV>& B, const RowCtx& r, int blk,
+                                        int g, int c, uint16_t* vt) {
   constexpr int RS = vtile_stride<DV>(), LPR = DV / 8, RPL = vrows_per_load<DV>();
   const int lane = 16 * g + c;
   const int rl = lane / LPR, cl = 8 * (lane % LPR);  // the lane's row within a load, and dims
@@ -279,6 +355,21 @@ __device__ __forceinline__ void stage_v(const Block<D, DV>& B, const RowCtx& r, 
   // The appended row replaces the cache's slot (the wave's LDS writes land in order).
   if (r.lsub >= blk && r.lsub < blk + 32) {
     if (lane < DV / 8) *(uint4*)(vt + (r.lsub - blk) * RS + 8 * lane) = r.snew[D / 8 + r.vp0 + lane];
+  }
+}
+
+// float32 V rows stay in their registers: dead rows are zeroed and the appended row put in place.
+template <int D, int DV>
+__device__ __forceinline__ void patch_v(Block<float, D, DV>& B, const RowCtx& r, int blk, int g,
+                                        int c) {
+  using Gm = Geo<float, D, DV>;
+  const bool part = blk + Gm::BS > r.n_eff, sub = r.lsub >= blk && r.lsub < blk + Gm::BS;
+  if (!part && !sub) return;
+#pragma unroll
+  for (int i = 0; i < Gm::NV; ++i) {
+    const int slot = blk + Gm::slot(4 * g, 0) + v_off_row<float, D, DV>(i);
+    if (slot >= r.n_eff) B.v[i] = make_uint4(0, 0, 0, 0);
+    if (slot == r.lsub) B.v[i] = r.snew[Gm::PPR + r.vp0 + 16 * (i % (DV / 64)) + c];
   }
 }
 
@@ -299,41 +390,73 @@ __device__ __forceinline__ void fix_k(uint4& x, uint4& y) {
   }
 }
 
-template <int D, int DV>
-__device__ __forceinline__ void stage_qk(const Block<D, DV>& B, const RowCtx& r, int blk, int lane,
-                                         int thr, const bf16x8_t* qf, f32x4_t* S,
+// q as the B operand of q.K^T: lane (g, c) holds head c, the 16 bytes at 16 g of every k-step.
+template <typename T, int D>
+struct QFrag {
+  uint4 q[Geo<T, D>::NS];
+};
+
+template <typename T, int D, int DV>
+__device__ __forceinline__ void stage_qk(const Block<T, D, DV>& B, const RowCtx& r, int blk, int lane,
+                                         const QFrag<T, D>& qf, f32x4_t* S,
                                          unsigned long long& suf) {
-  constexpr int NKK = D / 32;
+  using Gm = Geo<T, D, DV>;
+  constexpr int NS = Gm::NS, BS = Gm::BS;
   const int g = lane >> 4, c = lane & 15;
   // Slots of this block in the recent suffix (bit j = slot blk + j).
-  const int ps = blk + (lane & 31);
-  suf = __ballot(lane < 32 && ps >= r.jsuf && ps < r.n_eff);
-  // q.K^T on the matrix cores: lane holds slots blk+8g+4mt+v of head c.
+  const int ps = blk + (lane & (BS - 1));
+  suf = __ballot(lane < BS && ps >= r.jsuf && ps < r.n_eff);
+  // q.K^T on the matrix cores: lane holds slots blk + slot(4g + v, mt) of head c.
 #pragma unroll
-  for (int mt = 0; mt < 2; ++mt) {
-    uint4 kr[NKK];
+  for (int mt = 0; mt < Gm::MT; ++mt) {
+    uint4 kr[NS];
 #pragma unroll
-    for (int kk = 0; kk < NKK; ++kk) kr[kk] = B.k[mt][kk];
+    for (int kk = 0; kk < NS; ++kk) kr[kk] = B.k[mt][kk];
 #pragma unroll
-    for (int p = 0; p < NKK / 2; ++p) fix_k(kr[2 * p], kr[2 * p + 1]);
-    // The appended row's K in the lanes of its A-row (slot 8(c/4) + 4mt + c%4 of the block).
-    if (r.lsub >= blk && r.lsub < blk + 32 && r.lsub - blk == 8 * (c >> 2) + 4 * mt + (c & 3)) {
+    for (int p = 0; p < NS / 2; ++p) fix_k(kr[2 * p], kr[2 * p + 1]);
+    // The appended row's K in the lanes of its A-row.
+    if (r.lsub >= blk && r.lsub < blk + BS && r.lsub - blk == Gm::slot(c, mt)) {
 #pragma unroll
-      for (int kk = 0; kk < NKK; ++kk) kr[kk] = r.snew[4 * kk + g];
+      for (int kk = 0; kk < NS; ++kk) kr[kk] = r.snew[4 * kk + g];
     }
     S[mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    if constexpr (Gm::F32) {
+      // Eight partial dot products for every four k-steps, added as a tree: as close to the exact
+      // sum as a lane-wise reduction (one chain of D terms is not), and eight independent chains.
 #pragma unroll
-    for (int kk = 0; kk < NKK; ++kk)
-      S[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kr[kk]), qf[kk], S[mt], 0, 0, 0);
+      for (int k0 = 0; k0 < NS; k0 += 4) {
+        f32x4_t P[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) P[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = k0; kk < k0 + 4; ++kk) {
+          const unsigned* kx = (const unsigned*)&kr[kk];
+          const unsigned* qx = (const unsigned*)&qf.q[kk];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            // A register of its own: while the element is part of a 16-byte load, clang 22
+            // (ROCm 7.2) put the accumulator over elements that were still to be multiplied, in
+            // the non-temporal merge-form instances (seen in the listing; wrong logits).
+            float x = __uint_as_float(kx[e]);
+            asm("" : "+v"(x));
+            f32x4_t& acc = P[4 * (kk & 1) + e];
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x, __uint_as_float(qx[e]), acc, 0, 0, 0);
+          }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const float t = ((P[0][v] + P[1][v]) + (P[2][v] + P[3][v])) +
+                          ((P[4][v] + P[5][v]) + (P[6][v] + P[7][v]));
+          S[mt][v] = k0 == 0 ? t : S[mt][v] + t;
+        }
+      }
+    } else {
+#pragma unroll
+      for (int kk = 0; kk < NS; ++kk)
+        S[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kr[kk]), as_bf16x8(qf.q[kk]),
+                                                        S[mt], 0, 0, 0);
+    }
   }
-}
-
-template <int D, int DV>
-__device__ __forceinline__ void stage_block(const Block<D, DV>& B, const RowCtx& r, int blk, int g,
-                                            int c, int lane, int thr, const bf16x8_t* qf,
-                                            uint16_t* vt, f32x4_t* S, unsigned long long& suf) {
-  stage_v<D, DV>(B, r, blk, g, c, vt);
-  stage_qk<D, DV>(B, r, blk, lane, thr, qf, S, suf);
 }
 
 // Where a wave writes its logits: the split's LDS copy of its stash rows, or the stash itself.
@@ -348,85 +471,164 @@ struct StashRow {
   bool use_lds;    // fixed per kernel instantiation
 };
 
-// Second half: online softmax, logit stash, suffix mass, and alpha.V (DV dims) from the LDS tile.
-template <int D, int DV>
+// Second half: online softmax, logit stash, suffix mass, and alpha.V (DV dims), V from the LDS tile
+// (bfloat16) or from the block's registers (float32).
+template <typename T, int D, int DV>
 __device__ __forceinline__ void finish_block(const f32x4_t* S, unsigned long long suf,
-                                             const RowCtx& r, int blk, int g, int c, int G,
-                                             float scale_log2, const StashRow& sr, uint16_t* vt,
-                                             Online& st, f32x4_t* O) {
-  constexpr int NB = DV / 16, RS = vtile_stride<DV>();
-  float s[2][4];
+                                             const Block<T, D, DV>& B, const RowCtx& r, int blk,
+                                             int g, int c, int G, float scale_log2,
+                                             const StashRow& sr, uint16_t* vt, Online& st,
+                                             f32x4_t* O) {
+  using Gm = Geo<T, D, DV>;
+  constexpr int MT = Gm::MT;
+  float s[MT][4];
   float mx = -INFINITY;
 #pragma unroll
-  for (int mt = 0; mt < 2; ++mt) {
+  for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const int slot = blk + 8 * g + 4 * mt + v;
+      const int slot = blk + Gm::slot(4 * g + v, mt);
       s[mt][v] = slot < r.n_eff ? S[mt][v] * scale_log2 : -INFINITY;
       mx = fmaxf(mx, s[mt][v]);
     }
   }
   if (c < G) {
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+    for (int mt = 0; mt < MT; ++mt)
     {
       const float4 sv = make_float4(s[mt][0], s[mt][1], s[mt][2], s[mt][3]);
       if (sr.use_lds)
-        *(lds_f32x4*)(sr.lds + (blk - sr.lo) + 8 * g + 4 * mt) = f32x4_t{sv.x, sv.y, sv.z, sv.w};
-      else *(float4*)(sr.glob + blk + 8 * g + 4 * mt) = sv;
+        *(lds_f32x4*)(sr.lds + (blk - sr.lo) + Gm::slot(4 * g, mt)) = f32x4_t{sv.x, sv.y, sv.z, sv.w};
+      else *(float4*)(sr.glob + blk + Gm::slot(4 * g, mt)) = sv;
     }
   }
   mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
   mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
   const float m_new = fmaxf(st.m, mx);
   const float alpha = exp2f(st.m - m_new);
-  float p[2][4];
+  float p[MT][4];
   float psum = 0.f, ssum = 0.f;
 #pragma unroll
-  for (int mt = 0; mt < 2; ++mt) {
+  for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       p[mt][v] = exp2f(s[mt][v] - m_new);
       psum += p[mt][v];
-      ssum += ((suf >> (8 * g + 4 * mt + v)) & 1ull) ? p[mt][v] : 0.f;
+      ssum += ((suf >> Gm::slot(4 * g + v, mt)) & 1ull) ? p[mt][v] : 0.f;
     }
   }
   st.l = st.l * alpha + psum;
   st.s = st.s * alpha + ssum;
   st.m = m_new;
-  // alpha of head c for slots 8g..8g+7, in k order, as two bf16 A operands: hi = alpha truncated
-  // to bf16, lo = the remainder truncated to bf16, so hi + lo is within 2^-16 of alpha.
-  uint32_t hb[8], lb[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const float x = p[e >> 2][e & 3];
-    const uint32_t xb = __float_as_uint(x) & 0xffff0000u;
-    hb[e] = xb >> 16;
-    lb[e] = __float_as_uint(x - __uint_as_float(xb)) >> 16;
-  }
-  uint4 ph, pl;
-  ph.x = hb[0] | (hb[1] << 16); ph.y = hb[2] | (hb[3] << 16); ph.z = hb[4] | (hb[5] << 16); ph.w = hb[6] | (hb[7] << 16);
-  pl.x = lb[0] | (lb[1] << 16); pl.y = lb[2] | (lb[3] << 16); pl.z = lb[4] | (lb[5] << 16); pl.w = lb[6] | (lb[7] << 16);
-  const bf16x8_t Ahi = as_bf16x8(ph), Alo = as_bf16x8(pl);
   float al[4];
+  if constexpr (Gm::F32) {
+    // k index g of step (mt, v) is slot(4g + v, mt): A is the lane's own alpha, B its V row.
+    // Accumulator 4h + e holds dims 64h + 4c + e. The block's terms are summed on their own and
+    // then added, so the running sum is rounded once a block and not once a slot.
 #pragma unroll
-  for (int v = 0; v < 4; ++v) al[v] = __shfl(alpha, 4 * g + v, 64);
-  // alpha.V: B[k][j] = V[slot 8g + k'][16nb + j] read from LDS with the transposing load: source
-  // lane c of the 16-lane group reads 4 dims 16nb + 4(c%4).. of row 8g + 4hf + c/4, and lane c
-  // receives dim 16nb + c of rows 8g + 4hf + 0..3.
-  const int trow = 8 * g + (c >> 2);
-  const int tcol = 4 * (c & 3);
+    for (int v = 0; v < 4; ++v) al[v] = __shfl(alpha, 4 * g + v, 64);
+    constexpr int H = DV / 64;
 #pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    const short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)(vt + trow * RS + 16 * nb + tcol));
-    const short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)(vt + (trow + 4) * RS + 16 * nb + tcol));
-    bf16x8_t Bv;
-    __builtin_memcpy(&Bv, &lo, 8);
-    __builtin_memcpy((char*)&Bv + 8, &hi, 8);
+    for (int h = 0; h < H; ++h) {
+      f32x4_t P[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) O[nb][v] *= al[v];
-    O[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ahi, Bv, O[nb], 0, 0, 0);
-    O[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Alo, Bv, O[nb], 0, 0, 0);
+      for (int e = 0; e < 4; ++e) P[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < 4 * MT; ++i) {
+        const unsigned* vx = (const unsigned*)&B.v[i * H + h];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          P[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[i >> 2][i & 3], __uint_as_float(vx[e]), P[e],
+                                                      0, 0, 0);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) O[4 * h + e][v] = fmaf(O[4 * h + e][v], al[v], P[e][v]);
+      }
+    }
+  } else {
+    constexpr int NB = DV / 16, RS = vtile_stride<DV>();
+    // alpha of head c for slots 8g..8g+7, in k order, as two bf16 A operands: hi = alpha truncated
+    // to bf16, lo = the remainder truncated to bf16, so hi + lo is within 2^-16 of alpha.
+    uint32_t hb[8], lb[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float x = p[e >> 2][e & 3];
+      const uint32_t xb = __float_as_uint(x) & 0xffff0000u;
+      hb[e] = xb >> 16;
+      lb[e] = __float_as_uint(x - __uint_as_float(xb)) >> 16;
+    }
+    uint4 ph, pl;
+    ph.x = hb[0] | (hb[1] << 16); ph.y = hb[2] | (hb[3] << 16); ph.z = hb[4] | (hb[5] << 16); ph.w = hb[6] | (hb[7] << 16);
+    pl.x = lb[0] | (lb[1] << 16); pl.y = lb[2] | (lb[3] << 16); pl.z = lb[4] | (lb[5] << 16); pl.w = lb[6] | (lb[7] << 16);
+    const bf16x8_t Ahi = as_bf16x8(ph), Alo = as_bf16x8(pl);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) al[v] = __shfl(alpha, 4 * g + v, 64);
+    // alpha.V: B[k][j] = V[slot 8g + k'][16nb + j] read from LDS with the transposing load: source
+    // lane c of the 16-lane group reads 4 dims 16nb + 4(c%4).. of row 8g + 4hf + c/4, and lane c
+    // receives dim 16nb + c of rows 8g + 4hf + 0..3.
+    const int trow = 8 * g + (c >> 2);
+    const int tcol = 4 * (c & 3);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const short4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)(vt + trow * RS + 16 * nb + tcol));
+      const short4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_short4*)(vt + (trow + 4) * RS + 16 * nb + tcol));
+      bf16x8_t Bv;
+      __builtin_memcpy(&Bv, &lo, 8);
+      __builtin_memcpy((char*)&Bv + 8, &hi, 8);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) O[nb][v] *= al[v];
+      O[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ahi, Bv, O[nb], 0, 0, 0);
+      O[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Alo, Bv, O[nb], 0, 0, 0);
+    }
+  }
+}
+
+// Bytes of a wave's LDS region: its V tile (bfloat16), and after the sweep its output numerators
+// ([16 heads][DV] float32).
+template <typename T, int DV>
+constexpr int wave_lds_bytes() {
+  return sizeof(T) == 2 && 32 * vtile_stride<DV>() * 2 > 16 * DV * 4 ? 32 * vtile_stride<DV>() * 2
+                                                                     : 16 * DV * 4;
+}
+// The wave's numerators into its LDS region (its last alpha.V has read the V tile).
+template <typename T, int DV>
+__device__ __forceinline__ void put_numerators(const f32x4_t* O, char* mine, int g, int c) {
+  float* my_o = (float*)mine;
+#pragma unroll
+  for (int t = 0; t < DV / 16; ++t) {
+    const int d = sizeof(T) == 4 ? 64 * (t >> 2) + 4 * c + (t & 3) : 16 * t + c;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) my_o[(4 * g + v) * DV + d] = O[t][v];
+  }
+}
+
+// Four consecutive acc values from slot j of a row whose values past `end` are not this workgroup's
+// to touch. Without RC a quad never straddles the row (cap is a multiple of 4) and is 16-byte
+// aligned; the values past `end` are rewritten as they were.
+typedef float f32x4u_t __attribute__((ext_vector_type(4), aligned(4)));
+template <bool RC>
+__device__ __forceinline__ float4 load_quad(const float* row, int j, int end) {
+  if (!RC) return *(const float4*)(row + j);
+  if (j + 4 <= end) {
+    const f32x4u_t x = *(const f32x4u_t*)(row + j);
+    return make_float4(x.x, x.y, x.z, x.w);
+  }
+  return make_float4(row[j], row[min(j + 1, end - 1)], row[min(j + 2, end - 1)],
+                     row[min(j + 3, end - 1)]);
+}
+template <bool RC>
+__device__ __forceinline__ void store_quad(float* row, int j, int end, const float4& x) {
+  if (!RC) {
+    *(float4*)(row + j) = x;
+  } else if (j + 4 <= end) {
+    *(f32x4u_t*)(row + j) = f32x4u_t{x.x, x.y, x.z, x.w};
+  } else {
+    const float* xp = (const float*)&x;
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+      if (j + e < end) row[j + e] = xp[e];
   }
 }
 
@@ -579,35 +781,30 @@ struct AccSlots {
   static_assert(NU >= 1 && NU * 64 * NW * 4 == MS, "four slots per thread and group");
   float4 v[NU];
 };
-template <int MS, int NW>
+template <bool RC, int MS, int NW>
 __device__ __forceinline__ void load_acc_slots(AccSlots<MS, NW>& o, const float* acc, int s_lo,
                                                int s_hi) {
 #pragma unroll
   for (int u = 0; u < AccSlots<MS, NW>::NU; ++u) {
     const int j0 = s_lo + 4 * (int)threadIdx.x + 256 * NW * u;
-    o.v[u] = *(const float4*)(acc + (j0 < s_hi ? j0 : s_lo));
+    o.v[u] = load_quad<RC>(acc, j0 < s_hi ? j0 : s_lo, s_hi);
   }
 }
 
 // With DV < D the workgroup owns output dims [r.dh DV, (r.dh + 1) DV) of the row; the statistics,
 // conf and acc (identical in every part) are written by part 0 only.
-template <int D, int SG, int MS, int NW, int DV>
+template <typename T, int D, bool RC, int SG, int MS, int NW, int DV>
 __device__ __forceinline__ void single_split_epilogue(const AttendArgs& a, const f32x4_t* O,
-                                                      uint16_t* vt, char* smem, const float* slog,
+                                                      char* mine, char* smem, const float* slog,
                                                       float (*sm_m)[16], float (*sm_l)[16],
                                                       float (*sm_s)[16], const RowInfo& r,
                                                       int g, int c, bool hdr_ok,
                                                       const AccSlots<MS, NW>& old) {
-  constexpr int VE = DV / 16, RS = vtile_stride<DV>();
+  constexpr int WB = wave_lds_bytes<T, DV>();
   constexpr int NU = AccSlots<MS, NW>::NU;
   const int tid = threadIdx.x, G = a.G, GDV = G * DV;
   float* acc = a.acc + r.bk * a.cap;
-  float* my_o = (float*)vt;  // the wave's numerators go to its own V tile (its last alpha.V read it)
-#pragma unroll
-  for (int t = 0; t < VE; ++t) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) my_o[(4 * g + v) * DV + 16 * t + c] = O[t][v];
-  }
+  put_numerators<T, DV>(O, mine, g, c);
   __shared__ float sM1[kMaxGroup], srZ1[kMaxGroup], sf1[kMaxGroup][NW];
   __shared__ int s_ok1;
   if (tid == 0) s_ok1 = hdr_ok ? 1 : 0;
@@ -635,13 +832,13 @@ __device__ __forceinline__ void single_split_epilogue(const AttendArgs& a, const
     if (r.dh == 0) write_row_stats(a, r.b, r.hkv, h, M, 1.f / lsum, ssum);
   }
   lds_barrier();
-  uint16_t* out = (uint16_t*)a.out + ((size_t)r.b * a.Hq + r.hkv * G) * D + r.dh * DV;
+  T* out = (T*)a.out + ((size_t)r.b * a.Hq + r.hkv * G) * D + r.dh * DV;
   for (int i = tid; i < GDV; i += 64 * NW) {
     const int h = i / DV;
     float o = 0.f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) o += sf1[h][w] * ((const float*)((const uint16_t*)smem + w * 32 * RS))[i];
-    out[h * D + (i - h * DV)] = f32_to_bf16(o * srZ1[h]);
+    for (int w = 0; w < NW; ++w) o += sf1[h][w] * ((const float*)(smem + w * WB))[i];
+    out[h * D + (i - h * DV)] = from_f32<T>(o * srZ1[h]);
   }
   if (r.dh != 0) return;
   // H2O increment of the split's slots: alpha = exp2(s - M) / Z; slots past the split keep their
@@ -668,7 +865,7 @@ __device__ __forceinline__ void single_split_epilogue(const AttendArgs& a, const
         const float nx = (r.app && j == r.L) ? sum[e] : ov[e] + sum[e];
         nvp[e] = j < r.s_hi ? nx : ov[e];
       }
-      *(float4*)(acc + j0) = nv;
+      store_quad<RC>(acc, j0, r.s_hi, nv);
     }
   }
 }
@@ -679,25 +876,19 @@ __device__ __forceinline__ void single_split_epilogue(const AttendArgs& a, const
 // slice of the row's output from every split's partial.
 template <int D, int SG, int NSB>
 __device__ __forceinline__ void exchange_epilogue(const AttendArgs& a, const f32x4_t* O,
-                                                  uint16_t* vt, char* smem, float* slog,
+                                                  char* mine, char* smem, float* slog,
                                                   float (*sm_m)[16], float (*sm_l)[16],
                                                   float (*sm_s)[16], const RowInfo& r, int g,
                                                   int c, bool hdr_ok, unsigned long long rw_old,
                                                   unsigned long long rw_chk) {
-  constexpr int NW = kWaves, VE = D / 16, RS = vtile_stride<D>();
+  constexpr int NW = kWaves, WB = wave_lds_bytes<uint16_t, D>();
   constexpr int kStIter = (NSB * SG * 3 + 255) / 256;           // statistics words of a row
   constexpr int kPoIter = (SG * D + kMaxMfmaSplits + 255) / 256; // numerator words of a slice
-  static_assert((size_t)kPoIter * 256 * 4 <= (size_t)NW * 32 * RS * 2,
+  static_assert((size_t)kPoIter * 256 * 4 <= (size_t)NW * WB,
                 "the polled numerators are staged in the V tiles");
   const int tid = threadIdx.x, G = a.G, GD = G * D, ns = r.ns;
   const size_t bk = r.bk;
-  // The wave's numerators go to its own V tile (its last alpha.V has read it).
-  float* my_o = (float*)vt;
-#pragma unroll
-  for (int t = 0; t < VE; ++t) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) my_o[(4 * g + v) * D + 16 * t + c] = O[t][v];
-  }
+  put_numerators<uint16_t, D>(O, mine, g, c);
   __shared__ int s_role, s_ok, s_mode[kMaxMfmaSplits];
   __shared__ unsigned s_tag, s_gen, s_prev;
   if (tid == 0) {
@@ -764,8 +955,7 @@ __device__ __forceinline__ void exchange_epilogue(const AttendArgs& a, const f32
     const int h = i / D;
     float o = 0.f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w)
-      o += sm_f[h][w] * ((const float*)((const uint16_t*)smem + w * 32 * RS))[i];
+    for (int w = 0; w < NW; ++w) o += sm_f[h][w] * ((const float*)(smem + w * WB))[i];
     st_word(nm_row + (size_t)r.split * GD + i, enc_word(o));
   }
   // This thread's four slots of the split; their split-relative probabilities exp2(s - M_split)
@@ -1052,30 +1242,26 @@ __device__ __forceinline__ void exchange_epilogue(const AttendArgs& a, const f32
 
 // Merge form: the waves of the workgroup are merged in LDS into one partial for this split
 // (part_ml, part_s, part_o); attend_combine_mfma finishes the row in a second launch.
-template <int D, int SG>
+template <typename T, int D, int SG>
 __device__ __forceinline__ void merge_form_epilogue(const AttendArgs& a, const f32x4_t* O,
-                                                    uint16_t* vt, char* smem, const float* slog,
+                                                    char* mine, char* smem, const float* slog,
                                                     float (*sm_m)[16], float (*sm_l)[16],
                                                     float (*sm_s)[16], const RowInfo& r, int wave,
                                                     int lane, int g, int c, int nb) {
-  constexpr int NW = kWaves, VE = D / 16, RS = vtile_stride<D>();
+  constexpr int NW = kWaves, WB = wave_lds_bytes<T, D>(), BS = Geo<T, D>::BS;
   const int G = a.G;
-  // Each wave, as soon as its own loop is done, puts its output numerators into its own V tile
-  // (its last alpha.V has read it) and copies its blocks' logits from the LDS copy to the stash,
-  // 16 B per lane (head hh + lane / 8, slots 4 (lane % 8).. of the block), so the waves that
-  // finish first do this while the others still stream.
-  float* my_o = (float*)vt;  // [16][D]
-#pragma unroll
-  for (int t = 0; t < VE; ++t) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) my_o[(4 * g + v) * D + 16 * t + c] = O[t][v];
-  }
+  // Each wave, as soon as its own loop is done, puts its output numerators into its own LDS region
+  // and copies its blocks' logits from the LDS copy to the stash, 16 B per lane (head
+  // hh + lane / QB, slots 4 (lane % QB).. of the block), so the waves that finish first do this
+  // while the others still stream.
+  put_numerators<T, D>(O, mine, g, c);
   if (SG > 0) {
+    constexpr int QB = BS / 4;  // groups of four slots in a block
     for (int i = 0; i < nb; ++i) {
-      const int off = 32 * (wave + NW * i);  // the block's first slot, relative to s_lo
+      const int off = BS * (wave + NW * i);  // the block's first slot, relative to s_lo
 #pragma unroll
-      for (int hh = 0; hh < (SG > 0 ? SG : 1); hh += 8) {
-        const int h = hh + (lane >> 3), q = lane & 7;
+      for (int hh = 0; hh < (SG > 0 ? SG : 1); hh += 64 / QB) {
+        const int h = hh + lane / QB, q = lane % QB;
         if (h < G)
           *(float4*)(a.stash + (r.bk * G + h) * a.cap_s + r.s_lo + off + 4 * q) =
               *(const float4*)(slog + h * kMaxSplitSlots + off + 4 * q);
@@ -1109,16 +1295,15 @@ __device__ __forceinline__ void merge_form_epilogue(const AttendArgs& a, const f
     const int h = i / D, d = i - h * D;
     float o = 0.f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w)
-      o += sm_f[h][w] * ((const float*)((const uint16_t*)smem + w * 32 * RS))[h * D + d];
+    for (int w = 0; w < NW; ++w) o += sm_f[h][w] * ((const float*)(smem + w * WB))[h * D + d];
     a.part_o[(pbase + h) * D + d] = o;
   }
 }
 
-// MFMA sweep (bfloat16 cache): one workgroup of kWaves waves per split of a row; CO selects the
-// one-launch form (the row is finished in this launch), otherwise the merge form (split partials
-// for attend_combine_mfma).
-template <int D, bool NT, int SG, bool CO, int NSB, int MS, int NW, int DS>
+// MFMA sweep: one workgroup of NW waves per split of a row; CO selects the one-launch form (the row
+// is finished in this launch), otherwise the merge form (split partials for attend_combine_mfma).
+// RC: a cap that need not be a multiple of 32 (float32 always; no exchange between splits).
+template <typename T, int D, bool NT, bool RC, int SG, bool CO, int NSB, int MS, int NW, int DS>
 __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
   static_assert(!CO || (SG > 0 && kWaves * 64 * 4 >= kMaxSplitSlots),
                 "the one-launch form keeps every logit of its split in LDS and handles four slots "
@@ -1130,9 +1315,11 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
                 "the exchange and the merge form use kWaves waves per workgroup");
   static_assert(DS == 1 || (DS == 2 && D == 128 && CO && MS > kMaxSplitSlots),
                 "the output dims are split only in single-split rows of head_dim 128");
+  static_assert(RC || sizeof(T) == 2, "float32 caches take the ragged-cap instances");
   constexpr int DV = D / DS;    // V and output dims of this workgroup
-  constexpr int NKK = D / 32;   // k-steps of the q.K^T product
-  constexpr int VE = DV / 16;   // V dims per lane per row
+  constexpr int VE = DV / 16;   // output accumulators per lane
+  using Gm = Geo<T, D, DV>;
+  constexpr int BS = Gm::BS, ES = (int)sizeof(T);
   // Grid order. Split slowest: consecutive workgroups (which the dispatcher deals round-robin to
   // the 8 XCDs) belong to different rows, so the busy splits of a launch spread over every XCD
   // even when some split indices have no slots. Row-major (one-launch form, grids larger than the
@@ -1159,12 +1346,14 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
   const int G = a.G;
   const size_t bk = (size_t)b * a.Hkv + hkv;
   const int cap = a.cap;
-  const uint16_t* Kb = (const uint16_t*)a.k + bk * cap * D;
-  const uint16_t* Vb = (const uint16_t*)a.v + bk * cap * D;
+  const char* Kb = (const char*)a.k + bk * cap * (D * ES);
+  const char* Vb = (const char*)a.v + bk * cap * (D * ES);
   RowCtx rc;
-  rc.kbase = Kb + (size_t)(8 * ((c & 7) >> 2) + (c & 3)) * D + 8 * (c < 8 ? g : 4 + g);
-  rc.vbase = Vb + (size_t)(lane / (DV / 8)) * D + dh * DV + 8 * (lane % (DV / 8));
-  rc.vp0 = dh * (DV / 8);
+  rc.krow = Gm::slot(c & 7, 0);
+  rc.kbase = Kb + rc.krow * (D * ES) + 16 * (c < 8 ? g : 4 + g);
+  rc.vrow = Gm::F32 ? Gm::slot(4 * g, 0) : lane / Gm::VPR;
+  rc.vbase = Vb + rc.vrow * (D * ES) + dh * DV * ES + 16 * (Gm::F32 ? c : lane % Gm::VPR);
+  rc.vp0 = dh * Gm::VPR;
   rc.posb = a.pos + (size_t)b * cap;
   rc.cap = cap;
   // Split 0 starts at slot 0 whatever the plan, so its waves request their first block (block
@@ -1180,9 +1369,9 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
     for (int k = 0; k < kPosPer; ++k) pv[k] = rc.posb[min(lo + (int)threadIdx.x + 64 * NW * k, cap - 1)];
   };
   if (split == 0) load_pos(0);
-  Block<D, DV> A;
-  const bool spec = split == 0 && 32 * wave < cap;
-  if (spec) load_block<D, NT, DV>(A, rc, 32 * wave, lane);
+  Block<T, D, DV> A;
+  const bool spec = split == 0 && BS * wave < cap;
+  if (spec) load_block<T, D, NT, RC, DV>(A, rc, BS * wave);
   int L, app;
   const int n_eff = live_slots(a, b, &L, &app);
   if (n_eff == 0) {  // the merge launch writes the empty result, or split 0 of the one-launch form
@@ -1194,7 +1383,7 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
         if (threadIdx.x == 0) refuse_row(a, b, LG_ATTEND_STATUS_WORKSPACE);
         return;
       }
-      uint16_t* out = (uint16_t*)a.out + ((size_t)b * a.Hq + hkv * G) * D;
+      T* out = (T*)a.out + ((size_t)b * a.Hq + hkv * G) * D;
       for (int i = threadIdx.x; i < G * D; i += 64 * NW) out[i] = 0;
       if (threadIdx.x < G) {
         a.lse[(size_t)b * a.Hq + hkv * G + threadIdx.x] = -INFINITY;
@@ -1207,7 +1396,7 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
   const int p_ns = bp.ns, p_chunk = bp.chunk;
   const int s_lo = split * bp.chunk, s_hi = min(s_lo + bp.chunk, n_eff);
   if (split >= p_ns) return;
-  const int nblk = (s_hi - s_lo + 31) / 32;
+  const int nblk = (s_hi - s_lo + BS - 1) / BS;
   // Recent suffix of the split: positions strictly increase over the live slots and the appended
   // slot holds the newest position t, so the slots whose position exceeds thr = t - suffix_w are
   // the split's last ones, from jsuf = s_lo + (stored slots of the split at or below thr) on (none
@@ -1228,14 +1417,14 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
   // The appended row (slot L, when this split holds it): stored to the cache for later steps and
   // staged in LDS, from where the sweep takes it in place of the slot's old contents, so no wave
   // waits for the store (the barrier below waits for LDS only).
-  __shared__ uint4 s_new[2 * (D / 8)];
+  __shared__ uint4 s_new[2 * Gm::PPR];
   rc.lsub = -1;
   rc.snew = s_new;
   const bool holds_new = app && L >= s_lo && L < s_hi;
-  if (holds_new && threadIdx.x < 2 * (D / 8)) {
-    const int which = threadIdx.x / (D / 8), piece = threadIdx.x % (D / 8);
-    const uint4 x = ((const uint4*)((const uint16_t*)(which ? a.v_new : a.k_new) + bk * D))[piece];
-    if (dh == 0) ((uint4*)((uint16_t*)(which ? a.v_w : a.k_w) + (bk * cap + L) * D))[piece] = x;
+  if (holds_new && threadIdx.x < 2 * Gm::PPR) {
+    const int which = threadIdx.x / Gm::PPR, piece = threadIdx.x % Gm::PPR;
+    const uint4 x = ((const uint4*)((const T*)(which ? a.v_new : a.k_new) + bk * D))[piece];
+    if (dh == 0) ((uint4*)((T*)(which ? a.v_w : a.k_w) + (bk * cap + L) * D))[piece] = x;
     s_new[threadIdx.x] = x;
   }
   lds_barrier();
@@ -1258,20 +1447,17 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
   rc.app = app;
   rc.n_eff = n_eff;
 
-  // q as the B operand: B[k][j] = q[head j][dim], lane (g, c) holds head c, dims kk*32+8g..+8.
-  bf16x8_t qf[NKK];
+  QFrag<T, D> qf;
   {
-    const uint16_t* qrow = (const uint16_t*)a.q + ((size_t)b * a.Hq + hkv * G + (c < G ? c : 0)) * D;
+    const char* qrow = (const char*)a.q + ((size_t)b * a.Hq + hkv * G + (c < G ? c : 0)) * (D * ES);
 #pragma unroll
-    for (int kk = 0; kk < NKK; ++kk) {
-      uint4 u = c < G ? *(const uint4*)(qrow + kk * 32 + 8 * g) : make_uint4(0, 0, 0, 0);
-      qf[kk] = as_bf16x8(u);
-    }
+    for (int kk = 0; kk < Gm::NS; ++kk)
+      qf.q[kk] = c < G ? *(const uint4*)(qrow + 64 * kk + 16 * g) : make_uint4(0, 0, 0, 0);
   }
   // A split that finishes its row alone reads its acc slots now (they are needed only after the
   // sweep, whose loads then hide their latency); kept in registers in the long-split kernel.
   AccSlots<MS, NW> acc_old;
-  if constexpr (CO && MS > kMaxSplitSlots) load_acc_slots(acc_old, a.acc + bk * cap, s_lo, s_hi);
+  if constexpr (CO && MS > kMaxSplitSlots) load_acc_slots<RC>(acc_old, a.acc + bk * cap, s_lo, s_hi);
   __shared__ __attribute__((aligned(16))) float slog[SG > 0 ? SG * MS : 4];
   // With SG > 0 the logits are staged in LDS (and, in the merge form, written to the stash once at
   // the end); otherwise they are stored to the stash from the loop.
@@ -1286,11 +1472,10 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
 #pragma unroll
   for (int rr = 0; rr < VE; ++rr) O[rr] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   // LDS: per-wave V tiles during the sweep, then the wave partials or the polled words.
-  constexpr int RS = vtile_stride<DV>();
-  constexpr size_t kTileBytes = (size_t)NW * 32 * RS * 2;
-  constexpr size_t kMergeBytes = (size_t)NW * 16 * DV * 4;
-  __shared__ __attribute__((aligned(16))) char smem[kTileBytes > kMergeBytes ? kTileBytes : kMergeBytes];
-  uint16_t* vt = (uint16_t*)smem + wave * 32 * RS;
+  constexpr int WB = wave_lds_bytes<T, DV>();
+  __shared__ __attribute__((aligned(16))) char smem[NW * WB];
+  char* mine = smem + wave * WB;
+  uint16_t* vt = (uint16_t*)mine;
 
   // Wave w takes blocks w, w + NW, ... of the split. The next block's V rows are loaded as soon as
   // the current ones are in LDS and its K rows right after the current q.K^T (into the same, now
@@ -1298,7 +1483,7 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
   // last block is peeled so the loop's loads are unconditional: the wait counts at the loop head
   // then let the V rows be staged while the K rows of the same block are still in flight.
   const int nb = wave < nblk ? (nblk - wave + NW - 1) / NW : 0;
-  f32x4_t S[2];
+  f32x4_t S[Gm::MT];
   unsigned long long suf;
   // Thread 0 parks the arrival word and the header check in LDS as soon as they have returned
   // (they were requested before the first block, and vector memory reads complete in order, so
@@ -1309,7 +1494,7 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
   __shared__ int s_hdr_ok;
   unsigned long long rw_chk = 0;
   if (nb > 0) {
-    if (!spec) load_block<D, NT, DV>(A, rc, s_lo + 32 * wave, lane);
+    if (!spec) load_block<T, D, NT, RC, DV>(A, rc, s_lo + BS * wave);
     if (CO && threadIdx.x == 0) {
       s_hdr_ok = hd0.x == kWsMagic && hd0.y == kWsVersion && (int)hd0.z == a.B &&
                  (int)hd0.w == a.Hq && (int)hd1.x == a.Hkv && (int)hd1.y == D &&
@@ -1318,18 +1503,29 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
       s_rw_old = rw_old;
     }
     for (int i = 0; i + 1 < nb; ++i) {
-      const int blk = s_lo + 32 * (wave + NW * i);
-      stage_v<D, DV>(A, rc, blk, g, c, vt);
-      load_v<D, NT, DV>(A, rc, blk + 32 * NW);
-      stage_qk<D, DV>(A, rc, blk, lane, thr, qf, S, suf);
-      load_k<D, NT, DV>(A, rc, blk + 32 * NW, lane);
-      finish_block<D, DV>(S, suf, rc, blk, g, c, G, a.scale_log2, stash_row, vt, st, O);
+      const int blk = s_lo + BS * (wave + NW * i);
+      if constexpr (Gm::F32) {
+        // V is read from its registers, so the next block's V rows are requested last.
+        patch_v<D, DV>(A, rc, blk, g, c);
+        stage_qk<T, D, DV>(A, rc, blk, lane, qf, S, suf);
+        load_k<T, D, NT, RC, DV>(A, rc, blk + BS * NW);
+        finish_block<T, D, DV>(S, suf, A, rc, blk, g, c, G, a.scale_log2, stash_row, vt, st, O);
+        load_v<T, D, NT, RC, DV>(A, rc, blk + BS * NW);
+      } else {
+        stage_v<D, DV>(A, rc, blk, g, c, vt);
+        load_v<T, D, NT, RC, DV>(A, rc, blk + BS * NW);
+        stage_qk<T, D, DV>(A, rc, blk, lane, qf, S, suf);
+        load_k<T, D, NT, RC, DV>(A, rc, blk + BS * NW);
+        finish_block<T, D, DV>(S, suf, A, rc, blk, g, c, G, a.scale_log2, stash_row, vt, st, O);
+      }
     }
     if (multi && threadIdx.x == 0 && (int)(s_rw_old & 0xffffu) != p_ns - 1)
       rw_chk = row_peek(a.rows + bk);
-    const int blk = s_lo + 32 * (wave + NW * (nb - 1));
-    stage_block<D, DV>(A, rc, blk, g, c, lane, thr, qf, vt, S, suf);
-    finish_block<D, DV>(S, suf, rc, blk, g, c, G, a.scale_log2, stash_row, vt, st, O);
+    const int blk = s_lo + BS * (wave + NW * (nb - 1));
+    if constexpr (Gm::F32) patch_v<D, DV>(A, rc, blk, g, c);
+    else stage_v<D, DV>(A, rc, blk, g, c, vt);
+    stage_qk<T, D, DV>(A, rc, blk, lane, qf, S, suf);
+    finish_block<T, D, DV>(S, suf, A, rc, blk, g, c, G, a.scale_log2, stash_row, vt, st, O);
   }
 
   // The wave's partial: head c's max in every lane, sum and suffix sum reduced over the row groups.
@@ -1355,30 +1551,31 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
     const unsigned long long rw_old0 = threadIdx.x == 0 ? s_rw_old : 0ull;
     if constexpr (MS > kMaxSplitSlots) {
       // the plan gives such a launch one split per row (split >= cap)
-      single_split_epilogue<D, SG, MS, NW, DV>(a, O, vt, smem, slog, sm_m, sm_l, sm_s, ri, g, c,
+      single_split_epilogue<T, D, RC, SG, MS, NW, DV>(a, O, mine, smem, slog, sm_m, sm_l, sm_s, ri, g, c,
                                            hdr_ok, acc_old);
     } else {
       if (p_ns == 1) {
-        load_acc_slots(acc_old, a.acc + bk * cap, s_lo, s_hi);
-        single_split_epilogue<D, SG, MS, NW, DV>(a, O, vt, smem, slog, sm_m, sm_l, sm_s, ri, g, c,
+        load_acc_slots<RC>(acc_old, a.acc + bk * cap, s_lo, s_hi);
+        single_split_epilogue<T, D, RC, SG, MS, NW, DV>(a, O, mine, smem, slog, sm_m, sm_l, sm_s, ri, g, c,
                                              hdr_ok, acc_old);
       } else {
-        exchange_epilogue<D, SG, NSB>(a, O, vt, smem, slog, sm_m, sm_l, sm_s, ri, g, c, hdr_ok,
-                                      rw_old0, rw_chk);
+        if constexpr (!RC)
+          exchange_epilogue<D, SG, NSB>(a, O, mine, smem, slog, sm_m, sm_l, sm_s, ri, g, c, hdr_ok,
+                                        rw_old0, rw_chk);
       }
     }
   } else {
-    merge_form_epilogue<D, SG>(a, O, vt, smem, slog, sm_m, sm_l, sm_s, ri, wave, lane, g, c, nb);
+    merge_form_epilogue<T, D, SG>(a, O, mine, smem, slog, sm_m, sm_l, sm_s, ri, wave, lane, g, c, nb);
   }
 }
 
 // Kernel entry point: the occupancy target of two waves per SIMD is given to the register
 // allocator. NSB bounds the splits per row of a one-launch grid (it sizes the statistics poll).
-template <int D, bool NT, int SG, bool CO, int NSB = kMaxMfmaSplits, int MS = kMaxSplitSlots,
-          int NW = kWaves, int DS = 1>
+template <typename T, int D, bool NT, bool RC, int SG, bool CO, int NSB = kMaxMfmaSplits,
+          int MS = kMaxSplitSlots, int NW = kWaves, int DS = 1>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 8)))
 void attend_mfma(AttendArgs a) {
-  attend_mfma_body<D, NT, SG, CO, NSB, MS, NW, DS>(a);
+  attend_mfma_body<T, D, NT, RC, SG, CO, NSB, MS, NW, DS>(a);
 }
 
 // -------------------------------------------------------------------------------------------
@@ -1484,7 +1681,7 @@ struct CombineLoads {
 
 // Issues the loads of one combine workgroup: slots from lo (quads below lim), output slice `per`
 // entries wide of each of nsl splits, and (STATS) the split statistics.
-template <int D, int GM, bool STATS>
+template <int D, bool RC, int GM, bool STATS>
 __device__ __forceinline__ void combine_loads(CombineLoads<D, GM>& c, const AttendArgs& a,
                                               size_t bk, int split, int lo, int lim, int per,
                                               int nsl) {
@@ -1492,7 +1689,7 @@ __device__ __forceinline__ void combine_loads(CombineLoads<D, GM>& c, const Atte
   const int j0 = lo + 4 * tid;
   const int jl = j0 < lim ? j0 : lo;  // in bounds, discarded past lim
   const float* stash = a.stash + bk * G * a.cap_s;
-  c.old = *(const float4*)(a.acc + bk * a.cap + jl);
+  c.old = load_quad<RC>(a.acc + bk * a.cap, jl, lim);
 #pragma unroll
   for (int h = 0; h < GM; ++h)
     c.lgv[h] = *(const float4*)(stash + (size_t)min(h, G - 1) * a.cap_s + jl);
@@ -1521,7 +1718,7 @@ __device__ __forceinline__ void combine_loads(CombineLoads<D, GM>& c, const Atte
 }
 
 // FX: the launch's splits are fixed chunks (a.split == kFixedChunk).
-template <int D, int GM, bool FX>
+template <typename T, int D, bool RC, int GM, bool FX>
 __global__ __launch_bounds__(256) void attend_combine_mfma(AttendArgs a) {
   const int split = blockIdx.z, hkv = blockIdx.x, b = blockIdx.y;  // the sweep's grid
   const int tid = threadIdx.x;
@@ -1530,10 +1727,10 @@ __global__ __launch_bounds__(256) void attend_combine_mfma(AttendArgs a) {
   CombineLoads<D, GM> ld;
   int lo = split * a.split, per = (GD + a.ns_grid - 1) / a.ns_grid, nsl = a.ns_grid;
   if constexpr (FX)
-    combine_loads<D, GM, true>(ld, a, bk, split, lo, min(lo + a.split, a.cap), per, nsl);
+    combine_loads<D, RC, GM, true>(ld, a, bk, split, lo, min(lo + a.split, a.cap), per, nsl);
   int L, app;
   const int n_eff = live_slots(a, b, &L, &app);
-  uint16_t* out = (uint16_t*)a.out + ((size_t)b * a.Hq + hkv * G) * D;
+  T* out = (T*)a.out + ((size_t)b * a.Hq + hkv * G) * D;
   __shared__ int s_hdr;
   if (tid == 0) s_hdr = header_ok<D>(a) ? 1 : 0;
   __syncthreads();
@@ -1558,7 +1755,7 @@ __global__ __launch_bounds__(256) void attend_combine_mfma(AttendArgs a) {
     lo = split * plan.chunk;
     per = (GD + ns - 1) / ns;
     nsl = ns;
-    combine_loads<D, GM, false>(ld, a, bk, split, lo, min(lo + plan.chunk, n_eff), per, nsl);
+    combine_loads<D, RC, GM, false>(ld, a, bk, split, lo, min(lo + plan.chunk, n_eff), per, nsl);
   }
   const int hi = min(lo + plan.chunk, n_eff);
   // Slots j0..j0+3 of this thread (splits are at most 1024 slots). The sweep wrote -inf logits
@@ -1646,13 +1843,13 @@ __global__ __launch_bounds__(256) void attend_combine_mfma(AttendArgs a) {
       const int j = j0 + e;
       nvp[e] = j < hi ? ((app && j == L) ? sum : ov[e] + sum) : ov[e];
     }
-    *(float4*)(acc + j0) = nv;
+    store_quad<RC>(acc, j0, hi, nv);
   }
   for (int i = tid; i < cnt; i += 256) {
     const int h = (o_lo + i) / D;
     float o = 0.f;
     for (int k = 0; k < ns; ++k) o += sF[h * kMaxMfmaSplits + k] * spo[k * per + i];
-    out[o_lo + i] = f32_to_bf16(o * srZ[h]);
+    out[o_lo + i] = from_f32<T>(o * srZ[h]);
   }
 }
 
@@ -1660,49 +1857,41 @@ __global__ __launch_bounds__(256) void attend_combine_mfma(AttendArgs a) {
 // Host-side launchers.
 // -------------------------------------------------------------------------------------------
 
-// Portable form: vector-ALU sweep of 64-slot splits, then the portable combine.
-template <typename T, int D>
-static hipError_t launch_valu(AttendArgs a, hipStream_t st) {
-  dim3 grid(a.ns_grid, a.Hkv, a.B);
-  hipLaunchKernelGGL((attend_valu<T, D>), grid, dim3(64), 0, st, a);
-  hipLaunchKernelGGL((attend_combine<T, D>), grid, dim3(256), 0, st, a);
-  return hipGetLastError();
-}
-
 // Above this many K/V bytes per layer the sweep streams with non-temporal loads (a model's cache
 // of such layers does not stay in the 256 MB last-level cache between decode steps).
 constexpr double kStreamBytes = 16.0 * 1024 * 1024;
 static bool stream_nt(const AttendArgs& a, int D) {
-  return 4.0 * a.B * a.Hkv * (double)a.cap * D >= kStreamBytes;
+  const double e = a.dtype == LG_BF16 ? 2.0 : 4.0;
+  return 2.0 * e * a.B * a.Hkv * (double)a.cap * D >= kStreamBytes;
 }
 
-template <int D, bool FX>
+template <typename T, int D, bool RC, bool FX>
 static void launch_combine(const AttendArgs& a, dim3 grid, hipStream_t st) {
   if (a.G <= 4)
-    hipLaunchKernelGGL((attend_combine_mfma<D, 4, FX>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((attend_combine_mfma<T, D, RC, 4, FX>), grid, dim3(256), 0, st, a);
   else if (a.G <= 8)
-    hipLaunchKernelGGL((attend_combine_mfma<D, 8, FX>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((attend_combine_mfma<T, D, RC, 8, FX>), grid, dim3(256), 0, st, a);
   else
-    hipLaunchKernelGGL((attend_combine_mfma<D, 16, FX>), grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((attend_combine_mfma<T, D, RC, 16, FX>), grid, dim3(256), 0, st, a);
 }
 
 // Merge form: the MFMA sweep writes split partials and the logit stash, attend_combine_mfma
 // merges them in a second launch.
-template <int D, bool NT>
+template <typename T, int D, bool NT, bool RC>
 static hipError_t launch_merge_nt(AttendArgs a, hipStream_t st) {
   dim3 grid(a.Hkv, a.B, a.ns_grid);
   if (a.split < kLdsStashMinSplit)
-    hipLaunchKernelGGL((attend_mfma<D, NT, 0, false>), grid, dim3(64 * kWaves), 0, st, a);
+    hipLaunchKernelGGL((attend_mfma<T, D, NT, RC, 0, false>), grid, dim3(64 * kWaves), 0, st, a);
   else if (a.G <= 4)
-    hipLaunchKernelGGL((attend_mfma<D, NT, 4, false>), grid, dim3(64 * kWaves), 0, st, a);
+    hipLaunchKernelGGL((attend_mfma<T, D, NT, RC, 4, false>), grid, dim3(64 * kWaves), 0, st, a);
   else if (a.G <= 8)
-    hipLaunchKernelGGL((attend_mfma<D, NT, 8, false>), grid, dim3(64 * kWaves), 0, st, a);
+    hipLaunchKernelGGL((attend_mfma<T, D, NT, RC, 8, false>), grid, dim3(64 * kWaves), 0, st, a);
   else
-    hipLaunchKernelGGL((attend_mfma<D, NT, 16, false>), grid, dim3(64 * kWaves), 0, st, a);
+    hipLaunchKernelGGL((attend_mfma<T, D, NT, RC, 16, false>), grid, dim3(64 * kWaves), 0, st, a);
   if (a.split == kFixedChunk)
-    launch_combine<D, true>(a, grid, st);
+    launch_combine<T, D, RC, true>(a, grid, st);
   else
-    launch_combine<D, false>(a, grid, st);
+    launch_combine<T, D, RC, false>(a, grid, st);
   return hipGetLastError();
 }
 
@@ -1725,7 +1914,7 @@ static long device_cus() {
 
 // One-launch form. A grid of at most one workgroup per compute unit is ordered split slowest;
 // a larger one row-major (see attend_mfma_body). Either order is correct with any residency.
-template <int D, bool NT, int SG>
+template <typename T, int D, bool NT, bool RC, int SG>
 static hipError_t launch_one_sg(AttendArgs a, hipStream_t st) {
   const long n = (long)a.Hkv * a.B * a.ns_grid;
   a.row_major = n > device_cus() ? 1 : 0;
@@ -1735,13 +1924,13 @@ static hipError_t launch_one_sg(AttendArgs a, hipStream_t st) {
       if constexpr (D == 128) {
         if (a.dsplit == 2) {
           const unsigned n16 = (unsigned)((a.B * a.Hkv + 7) / 8) * 16;
-          hipLaunchKernelGGL((attend_mfma<D, NT, SG, true, 4, kMaxSingleSlots, kSingleWaves, 2>),
+          hipLaunchKernelGGL((attend_mfma<T, D, NT, RC, SG, true, 4, kMaxSingleSlots, kSingleWaves, 2>),
                              dim3(n16), dim3(64 * kSingleWaves), 0, st, a);
           return hipGetLastError();
         }
       }
       if (a.dsplit != 1) return hipErrorInvalidValue;  // the plan never gives this
-      hipLaunchKernelGGL((attend_mfma<D, NT, SG, true, 4, kMaxSingleSlots, kSingleWaves>), grid,
+      hipLaunchKernelGGL((attend_mfma<T, D, NT, RC, SG, true, 4, kMaxSingleSlots, kSingleWaves>), grid,
                          dim3(64 * kSingleWaves), 0, st, a);
       return hipGetLastError();
     }
@@ -1749,34 +1938,72 @@ static hipError_t launch_one_sg(AttendArgs a, hipStream_t st) {
   if (a.dsplit != 1) return hipErrorInvalidValue;
   if (a.split > kMaxSplitSlots) return hipErrorInvalidValue;  // the plan never gives this
   if (a.ns_grid <= 4)
-    hipLaunchKernelGGL((attend_mfma<D, NT, SG, true, 4>), grid, dim3(64 * kWaves), 0, st, a);
+    hipLaunchKernelGGL((attend_mfma<T, D, NT, RC, SG, true, 4>), grid, dim3(64 * kWaves), 0, st, a);
+  else if constexpr (RC)
+    return hipErrorInvalidValue;  // no exchange between splits: the plan never gives this
   else if (a.ns_grid <= 8)
-    hipLaunchKernelGGL((attend_mfma<D, NT, SG, true, 8>), grid, dim3(64 * kWaves), 0, st, a);
+    hipLaunchKernelGGL((attend_mfma<T, D, NT, RC, SG, true, 8>), grid, dim3(64 * kWaves), 0, st, a);
   else
-    hipLaunchKernelGGL((attend_mfma<D, NT, SG, true, kMaxMfmaSplits>), grid, dim3(64 * kWaves), 0, st, a);
+    hipLaunchKernelGGL((attend_mfma<T, D, NT, RC, SG, true, kMaxMfmaSplits>), grid, dim3(64 * kWaves), 0, st, a);
   return hipGetLastError();
 }
 
-template <int D, bool NT>
+template <typename T, int D, bool NT, bool RC>
 static hipError_t launch_one_nt(AttendArgs a, hipStream_t st) {
-  if (a.G <= 4) return launch_one_sg<D, NT, 4>(a, st);
-  if (a.G <= 8) return launch_one_sg<D, NT, 8>(a, st);
-  return launch_one_sg<D, NT, 16>(a, st);
+  if (RC && a.ns_grid != 1) return hipErrorInvalidValue;  // the plan never gives this
+  if (a.G <= 4) return launch_one_sg<T, D, NT, RC, 4>(a, st);
+  if (a.G <= 8) return launch_one_sg<T, D, NT, RC, 8>(a, st);
+  return launch_one_sg<T, D, NT, RC, 16>(a, st);
+}
+
+template <typename T, int D, bool RC>
+hipError_t launch_mfma_form(AttendArgs a, hipStream_t st);
+
+// The build compiles this file once per part, in parallel, each with the kernels of one cache type
+// and head_dim; part 0 holds the portable kernels and the dispatch.
+#if LG_ATTEND_PART > 0
+template <typename T, int D, bool RC>
+hipError_t launch_mfma_form(AttendArgs a, hipStream_t st) {
+  const bool nt = stream_nt(a, D);
+  if (a.form == kFormMerge)
+    return nt ? launch_merge_nt<T, D, true, RC>(a, st) : launch_merge_nt<T, D, false, RC>(a, st);
+  return nt ? launch_one_nt<T, D, true, RC>(a, st) : launch_one_nt<T, D, false, RC>(a, st);
+}
+
+#if LG_ATTEND_PART == 1
+template hipError_t launch_mfma_form<uint16_t, 128, false>(AttendArgs, hipStream_t);
+#elif LG_ATTEND_PART == 2
+template hipError_t launch_mfma_form<uint16_t, 64, false>(AttendArgs, hipStream_t);
+#elif LG_ATTEND_PART == 3
+template hipError_t launch_mfma_form<uint16_t, 128, true>(AttendArgs, hipStream_t);
+#elif LG_ATTEND_PART == 4
+template hipError_t launch_mfma_form<uint16_t, 64, true>(AttendArgs, hipStream_t);
+#elif LG_ATTEND_PART == 5
+template hipError_t launch_mfma_form<float, 128, true>(AttendArgs, hipStream_t);
+#elif LG_ATTEND_PART == 6
+template hipError_t launch_mfma_form<float, 64, true>(AttendArgs, hipStream_t);
+#endif
+#else
+// Portable form: vector-ALU sweep of 64-slot splits, then the portable combine.
+template <typename T, int D>
+static hipError_t launch_valu(AttendArgs a, hipStream_t st) {
+  dim3 grid(a.ns_grid, a.Hkv, a.B);
+  hipLaunchKernelGGL((attend_valu<T, D>), grid, dim3(64), 0, st, a);
+  hipLaunchKernelGGL((attend_combine<T, D>), grid, dim3(256), 0, st, a);
+  return hipGetLastError();
 }
 
 template <int D>
-static hipError_t launch_mfma_form(AttendArgs a, hipStream_t st) {
-  const bool nt = stream_nt(a, D);
-  if (a.form == kFormMerge) return nt ? launch_merge_nt<D, true>(a, st) : launch_merge_nt<D, false>(a, st);
-  return nt ? launch_one_nt<D, true>(a, st) : launch_one_nt<D, false>(a, st);
+static hipError_t launch_attend_d(AttendArgs a, lg_dtype dt, hipStream_t st) {
+  if (a.form == kFormPortable)
+    return dt == LG_BF16 ? launch_valu<uint16_t, D>(a, st) : launch_valu<float, D>(a, st);
+  if (dt != LG_BF16) return launch_mfma_form<float, D, true>(a, st);
+  return a.cap % 32 == 0 ? launch_mfma_form<uint16_t, D, false>(a, st)
+                         : launch_mfma_form<uint16_t, D, true>(a, st);
 }
 
 hipError_t launch_attend(AttendArgs a, lg_dtype dt, int D, hipStream_t st) {
-  if (a.form != kFormPortable)
-    return D == 128 ? launch_mfma_form<128>(a, st) : launch_mfma_form<64>(a, st);
-  if (dt == LG_BF16)
-    return D == 128 ? launch_valu<uint16_t, 128>(a, st) : launch_valu<uint16_t, 64>(a, st);
-  return D == 128 ? launch_valu<float, 128>(a, st) : launch_valu<float, 64>(a, st);
+  return D == 128 ? launch_attend_d<128>(a, dt, st) : launch_attend_d<64>(a, dt, st);
 }
 
 // Workspace initialisation: every byte zero, then the header. The fill is a kernel (not a memset)
@@ -1794,5 +2021,7 @@ hipError_t launch_ws_init(void* ws, size_t bytes, const WsHeader& h, hipStream_t
   hipLaunchKernelGGL(ws_init_kernel, dim3(blocks), dim3(256), 0, st, (uint4*)ws, n16, h);
   return hipGetLastError();
 }
+
+#endif  // LG_ATTEND_PART
 
 }  // namespace lg

@@ -27,12 +27,13 @@ __host__ __device__ inline size_t align_up(size_t x, size_t a) { return (x + a -
 // ------------------------------------------------------------------------------------------
 // Attention launch plan and workspace layout (host and device).
 // ------------------------------------------------------------------------------------------
-// Kernel forms of lg_decode_attend. The automatic choice for bfloat16 caches whose cap is a
-// multiple of 32 (<= 32768): kFormOneLaunch when every row is a single split (no exchange; see
-// attend_plan), kFormMerge otherwise (the sweep and a merging launch: at 1 to 64 rows and in the
-// ragged batch it measured faster than the one-launch form's exchange); kFormPortable for the
-// other caches. The one-launch form with several splits per row is reachable through the test
-// hook.
+// Kernel forms of lg_decode_attend. The automatic choice for caps up to 32768 (both types):
+// kFormOneLaunch when every row is a single split (no exchange; see attend_plan), kFormMerge
+// otherwise (the sweep and a merging launch: at 1 to 64 rows and in the ragged batch it measured
+// faster than the one-launch form's exchange); kFormPortable for longer caches, whose rows would
+// be more than kMaxMfmaSplits splits. The one-launch form with several splits per row (bfloat16,
+// cap a multiple of 32) is reachable through the test hook, which takes the MFMA forms for those
+// caches only.
 enum : int { kFormAuto = 0, kFormPortable = 1, kFormMerge = 2, kFormOneLaunch = 3 };
 constexpr int kWaves = 4;            // waves per workgroup of the MFMA sweep
 constexpr int kMaxMfmaSplits = 32;   // splits per row of the MFMA forms at most
@@ -47,8 +48,11 @@ constexpr long kSingleSplitRows = 128;
 // shrinks from its maximum until the launch has about this many, down to one block per wave.
 constexpr long kTargetWorkgroups = 256;
 
+constexpr int kMaxMfmaCap = kMaxMfmaSplits * kMaxSplitSlots;
+
+// Caches whose MFMA form and split length the test hook may choose.
 inline bool mfma_eligible(const lg_layer_cache& c) {
-  return c.dtype == LG_BF16 && c.cap % 32 == 0 && c.cap <= 32768;
+  return c.dtype == LG_BF16 && c.cap % 32 == 0 && c.cap <= kMaxMfmaCap;
 }
 
 struct AttendPlan {
@@ -75,7 +79,7 @@ inline bool single_split_rows(const lg_layer_cache& c) {
 inline AttendPlan attend_plan(const lg_layer_cache& c, int form, int split_req) {
   AttendPlan p;
   p.form = form != kFormAuto ? form
-           : !mfma_eligible(c) ? kFormPortable
+           : c.cap > kMaxMfmaCap ? kFormPortable
            : (split_req == 0 && single_split_rows(c)) ? kFormOneLaunch : kFormMerge;
   if (p.form == kFormPortable) {
     p.split = kSplitQuantum;
@@ -138,6 +142,16 @@ inline AttendLayout attend_layout(const lg_layer_cache& c, const AttendPlan& p) 
   const size_t G = (size_t)(c.n_q_heads / c.n_kv_heads), D = (size_t)c.head_dim;
   const size_t rows = (size_t)c.batch * c.n_kv_heads;
   L.cap_s = (int)align_up((size_t)c.cap, 256);
+  if (p.form == kFormOneLaunch && !mfma_eligible(c)) {
+    // Only single-split rows get here, and they use nothing past the header. The size is the
+    // portable pair's, which such layers needed before they had an MFMA form.
+    AttendPlan q = p;
+    q.form = kFormPortable;
+    q.split = kSplitQuantum;
+    q.ns_grid = (c.cap + kSplitQuantum - 1) / kSplitQuantum;
+    L.bytes = attend_layout(c, q).bytes;
+    return L;
+  }
   size_t o = sizeof(WsHeader) > 256 ? sizeof(WsHeader) : 256;
   if (p.form == kFormOneLaunch) {
     L.off_rows = o;  o = align_up(o + rows * 8, 256);

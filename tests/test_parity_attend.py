@@ -233,6 +233,49 @@ def test_single_split_rows(B, Hq, Hkv, D, cap, whole_dims):
              flags=lg.TEST_WHOLE_DIMS if whole_dims else 0)
 
 
+RAGGED_CAPS = [
+    # B, Hq, Hkv, D, cap, lens: caps around one block, one wave round and one split, and odd ones
+    (2, 4, 2, 128, 1, [0, 0]), (3, 3, 3, 64, 15, [0, 7, 14]), (2, 16, 1, 128, 31, [30, 16]),
+    (3, 8, 2, 64, 33, [32, 31, 3]), (2, 7, 1, 128, 127, [126, 64]), (3, 28, 4, 128, 129, [128, 127, 0]),
+    (2, 12, 2, 128, 1023, [1022, 700]), (5, 32, 8, 64, 1500, [1499, 1000, 0, 1, 1471]),
+    (9, 32, 8, 128, 2047, [2046, 2015, 2016, 1, 0, 1024, 1023, 600, 31]),
+    (16, 24, 8, 128, 1025, [1024, 0, 1] + list(range(300, 313))),
+    (43, 21, 3, 64, 777, [776, 768, 0, 1] + list(range(500, 539))),
+    (32, 28, 4, 128, 1999, [1998, 1984, 0, 1] + list(range(1200, 1228))),
+    (64, 64, 4, 128, 1001, [1000, 0] + list(range(800, 862))), (3, 8, 1, 64, 5003, [5002, 4096, 77]),
+    # splits of 512 slots and more, group bounds 8 and 16, both head_dims
+    (36, 14, 2, 128, 2047, [2046, 0] + list(range(1500, 1534))),
+    (70, 16, 1, 64, 2046, [2045, 1] + list(range(1000, 1068))),
+    (35, 32, 2, 128, 2045, [2044, 2] + list(range(700, 733))),
+    (36, 10, 2, 64, 2044, [2043, 0] + list(range(1900, 1934))),
+    # one row, long cap: splits of 512 slots and more in a cache that is not streamed past the caches
+    (1, 2, 1, 64, 16389, [16388]), (1, 7, 1, 64, 16387, [16000]), (1, 16, 1, 64, 16385, [9999]),
+]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("shape", RAGGED_CAPS)
+def test_attend_ragged_caps(shape, dtype):
+    """The automatic choice for caps that are no multiple of a block, and for float32 caches: every
+    row against the oracle (dead slots hold NaN, rows past the live ones keep their scores), and in
+    float32 against the portable pair. Both sum in float32: out is a mean of n <= 5003 unit-variance
+    values with weights p, each p off by the rounding of its logit (|s| <= ~40, 2^-24 relative, times
+    ln 2) and each sum by ~sqrt(n) 2^-24, so 2e-5 of the row's largest value bounds the difference."""
+    B, Hq, Hkv, D, cap, lens = shape
+    got = run_case(B, Hq, Hkv, D, cap, lens, dtype, 0, seed=cap + Hq)
+    if dtype == "f32":
+        ref = run_case(B, Hq, Hkv, D, cap, lens, dtype, FORMS["portable"], seed=cap + Hq)
+        for x, y in zip(got, ref):
+            x, y = np.nan_to_num(x, neginf=0.0), np.nan_to_num(y, neginf=0.0)
+            assert np.all(np.abs(x - y) <= 2e-5 * np.maximum(1, np.abs(y).max()))
+
+
+@pytest.mark.parametrize("dtype,cap", [("f32", 32768), ("bf16", 32767), ("bf16", 32800), ("f32", 33000)])
+def test_attend_longest_ragged_caps(dtype, cap):
+    """The longest caps of the MFMA forms, and caps beyond them (portable kernels)."""
+    run_case(1, 8, 2, 64, cap, [cap - 1], dtype, 0, seed=cap)
+
+
 def _random_shape(i):
     rng = np.random.default_rng(1000 + i)
     G = int(rng.choice([1, 2, 4, 7, 8, 16]))
