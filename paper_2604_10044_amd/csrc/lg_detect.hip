@@ -1,10 +1,10 @@
 // lg_detect.hip -- Stage 1 of LoopGuard: the debounced online onset rule (Sec. 5.2, Eq. (8) and
-// Eq. (9); App. B.2), one 512-lane workgroup (8 waves) per sequence, integer arithmetic only.
+// Eq. (9); App. B.2), one 1024-lane workgroup (16 waves) per sequence, integer arithmetic only.
 //
 // Window statistics come from the equality structure of the window by lag: for a lag delta,
 // E_delta[i] = (y[i] == y[i - delta]) over window positions i. A wave builds E_delta 64 positions
-// at a time with one ballot (lane = position), the eight waves taking every eighth lag. From the
-// masks, the longest earlier match starting at i (the LZ match length of the Eq. (6) reading) is
+// at a time with one ballot (lane = position), the waves taking every 16th lag. From the masks, the
+// longest earlier match starting at i (the LZ match length of the Eq. (6) reading) is
 // the longest run of ones of E_delta starting at i, maximised over delta: each lane counts the
 // trailing ones of the mask shifted to its position, chunks taken from the window end so the run
 // carries across 64-position boundaries. The other statistics follow from it:
@@ -15,6 +15,11 @@
 // the call directly follows the one the state was written for, L_P(n) = L_P(n-1) + 1 on a match at
 // the newest token and 0 otherwise (capped); any other call recomputes all L_P, one wave per
 // period, 256 comparisons per iteration.
+//
+// One workgroup has one sequence, so a launch is a chain of latencies and not of bytes or
+// operations: the state, the confidence and the keep set's inputs are requested at the start, the
+// phases are separated by four barriers (waves that a phase does not need do the next one's work),
+// and the parse runs inside one wave, whose LDS accesses are in order without barriers.
 #include "lg_keepset.h"
 
 namespace lg {
@@ -30,37 +35,10 @@ struct DetectArgs {
   lg_decision* decision;
 };
 
-constexpr int kDetThreads = 512;
+constexpr int kDetThreads = 1024;
 constexpr int kDetWaves = kDetThreads / 64;
 constexpr int kBuf = kMaxHorizon + kMaxWindow + 64;
-
-__device__ __forceinline__ int block_sum(int x, int* red) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  __syncthreads();
-  if (lane == 0) red[wave] = x;
-  __syncthreads();
-  int s = 0;
-#pragma unroll
-  for (int w = 0; w < kDetWaves; ++w) s += red[w];
-  __syncthreads();
-  return s;
-}
-
-__device__ __forceinline__ int block_max(int x, int* red) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) x = max(x, __shfl_xor(x, o, 64));
-  __syncthreads();
-  if (lane == 0) red[wave] = x;
-  __syncthreads();
-  int s = red[0];
-#pragma unroll
-  for (int w = 1; w < kDetWaves; ++w) s = max(s, red[w]);
-  __syncthreads();
-  return s;
-}
+static_assert(kMaxWindow + kMaxPeriod <= kDetThreads, "one thread per window position and period");
 
 // The scalar fields of lg_guard_state (the tail runs are handled by all lanes).
 struct StateHeader {
@@ -73,13 +51,21 @@ __device__ __forceinline__ int trailing_ones(unsigned long long x) {
   return nx == 0ull ? 64 : __builtin_ctzll(nx);
 }
 
-// kChunks = window chunks of 64 positions the kernel is compiled for (W <= 64 * kChunks).
+__device__ __forceinline__ int wave_max(int x) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) x = max(x, __shfl_xor(x, o, 64));
+  return x;
+}
+
+// kChunks = window chunks of 64 positions the kernel is compiled for (W <= 64 * kChunks). The
+// decision is left in *dec (LDS) for the keep set; valid after the caller's next barrier.
 template <int kChunks>
-__device__ void detect_block(const DetectArgs& a) {
+__device__ void detect_block(const DetectArgs& a, lg_decision* dec) {
   const lg_guard_params& p = a.p;
   const int b = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: lag loops stay scalar
+  const lg_guard_state& gst = a.state[b];
   // The newest position is clamped to [-1, 2^30 - 1] (stream lengths 0 .. 2^30) and t0 to
   // [0, n] (a monitored stream that starts after n is empty), so every index derived from them
   // below stays in int32 range and inside the staged buffers whatever the caller passes.
@@ -98,18 +84,64 @@ __device__ void detect_block(const DetectArgs& a) {
   int* y = ybuf + kMaxWindow;
   __shared__ int ellw[kDetWaves][kMaxWindow];      // per-wave LZ match length at window index
   __shared__ int ellmax[kMaxWindow];               // ... maximised over the waves
-  __shared__ int nxt[2][kMaxWindow + 1], cst[2][kMaxWindow + 1];
-  __shared__ int red[kDetWaves];
+  __shared__ int par[kMaxWindow + 1];              // LZ parse: next position << 16 | cost
+  __shared__ int Lsh[kMaxPeriod];
+  __shared__ int s_u[kDetWaves], s_nov[kDetWaves], s_key[kDetWaves];
 
+  // The stream index lo_all + i lives at ring slot (lo_all + i) % ring; ring >= nbuf.
   const int32_t* tok = a.tokens + (size_t)b * a.ring;
-  for (int i = tid; i < nbuf; i += kDetThreads) y[i] = tok[(lo_all + i) % a.ring];
-  __syncthreads();
-  const int* yw = y + (w0 - lo_all);  // window: yw[0 .. m)
-  const lg_guard_state& gst = a.state[b];
-  const int cr_valid = gst.cr_valid;
-  const bool do_cr = !cr_valid || p.cr_interval <= 1 || (n % p.cr_interval) == 0;
+  const int r0 = lo_all % a.ring;
+  for (int i = tid; i < nbuf; i += kDetThreads) {
+    int k = r0 + i;
+    k -= k >= a.ring ? a.ring : 0;
+    y[i] = tok[k];
+  }
+  // Requested now, used phases later.
+  const int run_old = tid < p.rep_pmax ? gst.tail_run[min(tid, kMaxPeriod - 1)] : 0;
+  StateHeader st;
+  st.streak = gst.streak; st.stall = gst.stall; st.rep = gst.rep; st.n_int = gst.n_int;
+  st.n_last = gst.n_last; st.level = gst.level; st.cr_valid = gst.cr_valid;
+  st.cr_cost = gst.cr_cost; st.cr_m = gst.cr_m;
+  const bool incremental = gst.tail_n == n - 1 && gst.tail_t0 == t0 && gst.tail_horizon == H &&
+                           gst.tail_pmax == p.rep_pmax;
+  const float conf = a.conf ? a.conf[b] : 0.f;
+  const bool do_cr = !st.cr_valid || p.cr_interval <= 1 || (n % p.cr_interval) == 0;
   const int g = p.nov_ngram;
   const int nch = (m + 63) >> 6;
+  __syncthreads();
+  const int* yw = y + (w0 - lo_all);  // window: yw[0 .. m)
+
+  // ---- trailing self-alignment L_P, P = 1 .. rep_pmax ----
+  // L_P = largest k <= min(H - P, n - P - t0) with y[n-1-r] == y[n-1-r-P] for all r < k.
+  if (incremental) {
+    const int P = tid + 1;
+    if (P <= p.rep_pmax) {
+      const int ylast = nbuf > 0 ? y[(n - 1) - lo_all] : 0;
+      const int kmax = min(H - P, n - P - t0);
+      const bool eq = kmax > 0 && y[(n - 1 - P) - lo_all] == ylast;
+      Lsh[tid] = eq ? min(run_old + 1, kmax) : 0;
+    }
+  } else {
+    for (int P = wave + 1; P <= p.rep_pmax; P += kDetWaves) {
+      const int kmax = max(0, min(H - P, n - P - t0));
+      int Lp = kmax;
+      for (int q0 = 0; q0 < kmax; q0 += 256) {
+        unsigned long long miss[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int r = q0 + 64 * q + lane;
+          const bool eq = r < kmax && y[(n - 1 - r) - lo_all] == y[(n - 1 - r - P) - lo_all];
+          miss[q] = __ballot(!eq);
+        }
+        int hit = -1;
+#pragma unroll
+        for (int q = 3; q >= 0; --q)
+          if (miss[q]) hit = 64 * q + __builtin_ctzll(miss[q]);
+        if (hit >= 0) { Lp = min(kmax, q0 + hit); break; }
+      }
+      if (lane == 0) Lsh[P - 1] = Lp;
+    }
+  }
 
   // ---- window statistics from the lag masks ----
   // Every window statistic follows from ell[i] = the longest earlier match starting at window
@@ -156,110 +188,86 @@ __device__ void detect_block(const DetectArgs& a) {
   for (int c = 0; c < kChunks; ++c)
     if (c < nch && 64 * c + lane < m) ellw[wave][64 * c + lane] = ell[c];
   __syncthreads();
-  // ell over all lags; slot m terminates the parse below.
-  for (int i = tid; i < m; i += kDetThreads) {
-    int e = ellw[0][i];
+
+  // ---- threads below kMaxWindow: ell over all lags, the distinct count and the parse's first
+  // links; the others: the qualifying period with the longest tail, ties to the smallest P
+  // (maximise T * 1024 + (1023 - P)), and the new tail runs ----
+  if (tid < kMaxWindow) {
+    const int i = tid;
+    int e = 0;
+    if (i < m) {
 #pragma unroll
-    for (int w = 1; w < kDetWaves; ++w) e = max(e, ellw[w][i]);
-    ellmax[i] = e;
-  }
-  __syncthreads();
-
-  // Distinct tokens and novelty.
-  int uloc = 0, nloc = 0, rloc = 0;
-  const int nov_lo = max(g - 1, m - p.nov_span);  // window index of the first examined position
-  for (int i = tid; i < m; i += kDetThreads) {
-    uloc += ellmax[i] >= 1 ? 0 : 1;
-    if (i >= nov_lo) {
-      rloc += 1;
-      nloc += ellmax[i - g + 1] >= g ? 0 : 1;
+      for (int w = 0; w < kDetWaves; ++w) e = max(e, ellw[w][i]);
+      ellmax[i] = e;
+      par[i] = e >= 3 ? (min(i + e, m) << 16) | 2 : ((i + 1) << 16) | 1;
     }
-  }
-  const int distinct = block_sum(uloc, red);
-  const int novel = block_sum(nloc, red);
-  const int nov_r = block_sum(rloc, red);
-
-  // Greedy LZ parse by pointer doubling: cost of the parse from i to the end of the window.
-  int lz_cost = gst.cr_cost, lz_m = gst.cr_m;
-  if (do_cr) {
-    for (int i = tid; i <= m; i += kDetThreads) {
-      if (i == m) { nxt[0][i] = m; cst[0][i] = 0; }
-      else {
-        const int e = ellmax[i];
-        nxt[0][i] = e >= 3 ? min(i + e, m) : i + 1;
-        cst[0][i] = e >= 3 ? 2 : 1;
-      }
-    }
-    __syncthreads();
-    int cur = 0;
-    for (int span = 1; span <= m; span <<= 1) {
-      for (int i = tid; i <= m; i += kDetThreads) {
-        const int j = nxt[cur][i];
-        cst[cur ^ 1][i] = cst[cur][i] + cst[cur][j];
-        nxt[cur ^ 1][i] = nxt[cur][j];
-      }
-      __syncthreads();
-      cur ^= 1;
-    }
-    lz_cost = cst[cur][0];
-    lz_m = m;
-  }
-
-  // ---- trailing self-alignment L_P, P = 1 .. rep_pmax ----
-  // L_P = largest k <= min(H - P, n - P - t0) with y[n-1-r] == y[n-1-r-P] for all r < k.
-  const bool incremental = gst.tail_n == n - 1 && gst.tail_t0 == t0 && gst.tail_horizon == H &&
-                           gst.tail_pmax == p.rep_pmax;
-  __shared__ int Lsh[kMaxPeriod];
-  if (incremental) {
-    const int ylast = nbuf > 0 ? y[(n - 1) - lo_all] : 0;
-    for (int P = tid + 1; P <= p.rep_pmax; P += kDetThreads) {
-      const int kmax = min(H - P, n - P - t0);
-      const bool eq = kmax > 0 && y[(n - 1 - P) - lo_all] == ylast;
-      Lsh[P - 1] = eq ? min(gst.tail_run[P - 1] + 1, kmax) : 0;
-    }
+    if (i == 0) par[m] = m << 16;
+    const int u = __popcll(__ballot(i < m && e < 1));
+    if (lane == 0) s_u[wave] = u;
   } else {
-    for (int P = wave + 1; P <= p.rep_pmax; P += kDetWaves) {
-      const int kmax = max(0, min(H - P, n - P - t0));
-      int Lp = kmax;
-      for (int r0 = 0; r0 < kmax; r0 += 256) {
-        unsigned long long miss[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int r = r0 + 64 * q + lane;
-          const bool eq = r < kmax && y[(n - 1 - r) - lo_all] == y[(n - 1 - r - P) - lo_all];
-          miss[q] = __ballot(!eq);
-        }
-        int hit = -1;
-#pragma unroll
-        for (int q = 3; q >= 0; --q)
-          if (miss[q]) hit = 64 * q + __builtin_ctzll(miss[q]);
-        if (hit >= 0) { Lp = min(kmax, r0 + hit); break; }
-      }
-      if (lane == 0) Lsh[P - 1] = Lp;
+    const int P = tid - kMaxWindow + 1;
+    int key = 0;
+    if (P <= p.rep_pmax) {
+      const int Lp = Lsh[P - 1];
+      const int TP = Lp + P;
+      if (Lp >= (p.rep_min_copies - 1) * P && TP >= p.rep_min_len) key = TP * 1024 + (1023 - P);
+      a.state[b].tail_run[P - 1] = Lp;
     }
+    key = wave_max(key);
+    if (lane == 0) s_key[wave] = key;
   }
   __syncthreads();
-  // qualifying period with the longest tail, ties to the smallest P: maximise T * 1024 + (1023 - P)
-  int key = 0;
-  for (int P = tid + 1; P <= p.rep_pmax; P += kDetThreads) {
-    const int Lp = Lsh[P - 1];
-    const int TP = Lp + P;
-    if (Lp >= (p.rep_min_copies - 1) * P && TP >= p.rep_min_len) key = max(key, TP * 1024 + (1023 - P));
+
+  // ---- wave 0: cost of the greedy parse from the window's start, by pointer doubling; the last
+  // kMaxWindow threads: novelty ----
+  const int nov_lo = max(g - 1, m - p.nov_span);  // window index of the first examined position
+  int lz_cost = st.cr_cost, lz_m = st.cr_m;
+  if (wave == 0) {
+    if (do_cr) {
+      // A wave's LDS accesses complete in order: the gathers of a round are all done before its
+      // stores, and the next round's follow them.
+      int own[kChunks];
+#pragma unroll
+      for (int c = 0; c < kChunks; ++c) own[c] = par[min(64 * c + lane, m)];
+      for (int hop = 1; hop <= m; hop <<= 1) {
+        if (__builtin_amdgcn_readfirstlane(own[0]) >> 16 >= m) break;  // position 0's parse is done
+        int far[kChunks];
+#pragma unroll
+        for (int c = 0; c < kChunks; ++c) far[c] = par[own[c] >> 16];
+#pragma unroll
+        for (int c = 0; c < kChunks; ++c) own[c] = far[c] + (own[c] & 0xffff);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int c = 0; c < kChunks; ++c)
+          if (64 * c + lane < m) par[64 * c + lane] = own[c];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      }
+      lz_cost = __builtin_amdgcn_readfirstlane(own[0]) & 0xffff;
+      lz_m = m;
+    }
+  } else if (tid >= kDetThreads - kMaxWindow) {
+    const int i = tid - (kDetThreads - kMaxWindow);
+    const int v = __popcll(__ballot(i >= nov_lo && i < m && ellmax[max(i - g + 1, 0)] < g));
+    if (lane == 0) s_nov[wave] = v;
   }
-  key = block_max(key, red);
-  for (int P = tid + 1; P <= p.rep_pmax; P += kDetThreads) a.state[b].tail_run[P - 1] = Lsh[P - 1];
+  __syncthreads();
 
   if (tid == 0) {
-    StateHeader st;
-    st.streak = gst.streak; st.stall = gst.stall; st.rep = gst.rep; st.n_int = gst.n_int;
-    st.n_last = gst.n_last; st.level = gst.level; st.cr_valid = gst.cr_valid;
-    st.cr_cost = gst.cr_cost; st.cr_m = gst.cr_m;
+    int distinct = 0, novel = 0, key = 0;
+#pragma unroll
+    for (int w = 0; w < kMaxWindow / 64; ++w) distinct += s_u[w];
+#pragma unroll
+    for (int w = kDetWaves - kMaxWindow / 64; w < kDetWaves; ++w) {
+      novel += s_nov[w];
+      key = max(key, s_key[w]);
+    }
+    const int nov_r = max(0, m - nov_lo);
     const int Ps = key > 0 ? 1023 - (key & 1023) : 0;
     const int Ts = key > 0 ? key >> 10 : 0;
     const int vote_ttr = (long long)p.ttr_den * distinct < (long long)p.ttr_num * m;
     if (do_cr) { st.cr_cost = lz_cost; st.cr_m = lz_m; st.cr_valid = 1; }
     const int vote_cr = (long long)p.cr_den * st.cr_cost < (long long)p.cr_num * st.cr_m;
-    const float c = a.conf ? a.conf[b] : 0.f;
+    const float c = conf;
     const int attend_error = c != c;  // NaN: an attention call of this step failed for b
     st.streak = (c > p.conf_threshold) ? st.streak + 1 : 0;
     const int vote_p1 = st.streak >= p.streak_min;
@@ -301,6 +309,7 @@ __device__ void detect_block(const DetectArgs& a) {
     d.attend_error = attend_error;
     d.reserved = 0;
     a.decision[b] = d;
+    *dec = d;
     // header fields only: the tail runs were written above by all lanes
     lg_guard_state* out = &a.state[b];
     out->streak = st.streak; out->stall = st.stall; out->rep = st.rep; out->n_int = st.n_int;
@@ -313,17 +322,21 @@ __device__ void detect_block(const DetectArgs& a) {
 
 template <int kChunks>
 __global__ __launch_bounds__(kDetThreads) void detect_kernel(DetectArgs a) {
-  detect_block<kChunks>(a);
+  __shared__ lg_decision dec;
+  detect_block<kChunks>(a, &dec);
 }
 
-// The detector and the keep set of one sequence in one launch (lg_detect_and_prune): the keep set
-// reads the decision that the detector has just written (visible to the workgroup after the
-// barrier) and runs with the detector's kDetThreads threads.
+// The detector and the keep set of one sequence in one launch (lg_detect_and_prune): the keep set's
+// inputs are requested before the detector runs, the decision reaches it through LDS, and it runs
+// with the detector's kDetThreads threads.
 template <int kChunks>
 __global__ __launch_bounds__(kDetThreads) void detect_keep_kernel(DetectArgs a, KeepArgs k) {
-  detect_block<kChunks>(a);
+  __shared__ lg_decision dec;
+  const KeepInputs in = load_keep_inputs(k, blockIdx.x);
+  detect_block<kChunks>(a, &dec);
   __syncthreads();
-  keep_set_block<kDetThreads>(k);
+  const bool trig = k.policy == LG_POLICY_LOOPGUARD && dec.trigger != 0;
+  keep_set_block<kDetThreads>(k, in, trig, dec.span_lo, dec.level);
 }
 
 static DetectArgs detect_args(const lg_guard_params* p, const int32_t* tokens, int ring,

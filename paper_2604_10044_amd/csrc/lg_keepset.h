@@ -7,7 +7,8 @@
 
 namespace lg {
 
-constexpr int kPruneThreads = 256;
+constexpr int kPruneThreads = 256;   // compaction
+constexpr int kKeepThreads = 512;    // keepset_kernel
 
 struct KeepArgs {
   int32_t n_anchor, recent_div, sparse_div, policy, have_scores;
@@ -66,18 +67,23 @@ __device__ __forceinline__ int block_exclusive_scan(int x, int* total, int* red)
   return before + inc - x;
 }
 
-template <int TPB>
-__device__ __forceinline__ int block_count(int x, int* red) {
-  int tot;
-  (void)block_exclusive_scan<TPB>(x, &tot, red);
-  return tot;
-}
-
-// Is rank r one of floor(k*M/S), k = 0..S-1 (M > S > 0)? The ranks are strictly increasing in k,
-// so r is hit iff k = ceil(r*S/M) maps back onto it.
-__device__ __forceinline__ bool sparse_hit(int r, int M, int S) {
-  const long long k = ((long long)r * S + M - 1) / M;
-  return k < S && (k * M) / S == r;
+// Elements of the ascending array x[0, n) below thr, found by one wave: 64 probes a round, each at
+// the end of one of 64 equal segments, so 65536 positions take three dependent loads where a scan of
+// them by the workgroup took 256 rounds. An array that is not ascending gives some value in [0, n].
+__device__ __forceinline__ int wave_lower_bound(const int32_t* x, int n, int thr) {
+  const int lane = threadIdx.x & 63;
+  int lo = 0, hi = n;
+  while (lo < hi) {
+    const int step = (hi - lo + 63) >> 6;
+    const long long first = (long long)lo + (long long)lane * step;  // the lane's segment
+    const bool below = first < hi && x[min((int)first + step - 1, hi - 1)] < thr;
+    const int cnt = __popcll(__ballot(below));
+    const int seg = (int)min((long long)lo + (long long)cnt * step, (long long)hi);
+    hi = step == 1 ? seg : (int)min((long long)seg + step, (long long)hi);
+    lo = seg;
+    if (step == 1) break;
+  }
+  return lo;
 }
 
 // Keys of the H2O order: the score as an order-preserving unsigned integer (float order, -0 below
@@ -86,6 +92,21 @@ __device__ __forceinline__ unsigned long long h2o_key(const int32_t* scores, int
   uint32_t u = have ? (uint32_t)scores[j] : 0u;
   u = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
   return ((unsigned long long)u << 32) | (uint32_t)j;
+}
+
+// What the keep set of a sequence needs from memory, requested before anything waits for it (the
+// fused launch does so before the detector's work).
+struct KeepInputs {
+  int len, budget, t_append, appended;  // len: live slots before the commit, clamped into the cache
+};
+__device__ __forceinline__ KeepInputs load_keep_inputs(const KeepArgs& a, int b) {
+  KeepInputs x;
+  x.len = a.len[b];
+  x.budget = min(a.budget[b], a.cap);  // a budget above the cache's capacity acts as the capacity
+  x.t_append = a.t_append != nullptr ? a.t_append[b] : 0;
+  x.len = x.len < 0 ? 0 : (x.len > a.cap ? a.cap : x.len);
+  x.appended = a.t_append != nullptr && x.len < a.cap;
+  return x;
 }
 
 // The need-th largest key among slots [0, n) (1 <= need <= n): 8-bit digits from the top, one
@@ -124,41 +145,35 @@ __device__ unsigned long long radix_select_desc(const int32_t* scores, bool have
 }
 
 // The keep set of sequence blockIdx.x (see the file comment of lg_prune.hip), by the TPB
-// threads of the workgroup.
+// threads of the workgroup. trig, span and level are the sequence's decision (uniform).
+//
+// Positions ascend over the slots, so the anchors, the middle and the recent window are ranges of
+// slots, and LoopGuard's and StreamingLLM's keep sets are known once the ranges' ends are: kept
+// entry r is a slot in closed form. Three waves find the ends (wave_lower_bound), and every entry is
+// then written independently. Before, the workgroup classified and scanned the slots 256 at a time:
+// 64 contexts of up to 65536 tokens 416 us, a 2048-slot cache 15.7 us (MI355X).
 template <int TPB>
-__device__ void keep_set_block(const KeepArgs& a) {
+__device__ void keep_set_block(const KeepArgs& a, const KeepInputs& in, bool trig, int span,
+                               int level) {
   const int b = blockIdx.x;
   const int tid = threadIdx.x;
-  __shared__ int sh[6];
   __shared__ int red[TPB / 64];
   int32_t* pos = a.pos + (size_t)b * a.cap;
   int32_t* kidx = a.keep_idx + (size_t)b * a.cap;
+  const int Ls = in.len, L = Ls + in.appended;  // stored slots; live slots after the commit
+  const int budget = in.budget;
+  const bool flag = trig || L >= budget;
   if (tid == 0) {
-    int L = a.len[b];
-    L = L < 0 ? 0 : (L > a.cap ? a.cap : L);
-    if (a.t_append != nullptr) {
-      if (L < a.cap) {
-        pos[L] = a.t_append[b];
-        L += 1;
-      }
-      a.len[b] = L;
+    if (in.appended) pos[Ls] = in.t_append;
+    if (!flag) {
+      if (a.t_append != nullptr) a.len[b] = L;
+      a.new_len[b] = -1;
     }
-    const int trig = a.policy == LG_POLICY_LOOPGUARD && a.decision != nullptr && a.decision[b].trigger;
-    // a budget above the cache's capacity acts as the capacity, so a full cache is pruned
-    const int flag = trig ? 1 : (L >= min(a.budget[b], a.cap) ? 2 : 0);
-    sh[0] = L;
-    sh[1] = flag;
-    sh[2] = trig ? a.decision[b].span_lo : -1;
-    sh[3] = trig ? min(max(a.decision[b].level, 0), 30) : 0;
-    sh[4] = L > 0 ? pos[L - 1] : 0;
   }
-  __syncthreads();
-  const int L = sh[0], flag = sh[1], span = sh[2], level = sh[3], t = sh[4];
-  if (flag == 0) {
-    if (tid == 0) a.new_len[b] = -1;
-    return;
-  }
-  const int budget = min(a.budget[b], a.cap);
+  if (!flag) return;
+  if (!trig) span = -1;
+  level = trig ? min(max(level, 0), 30) : 0;
+  const int t = in.appended ? in.t_append : (L > 0 ? pos[L - 1] : 0);
   const int R = budget / a.recent_div;
   const int thrR = sat_sub(sat_sub(t, R), -1);  // t - R + 1
   // The kept set leaves room for the next append: at most budget - 1 slots (LoopGuard: claimed by
@@ -166,98 +181,105 @@ __device__ void keep_set_block(const KeepArgs& a) {
   // size capped). With the paper's constants nothing is cut.
   const int cap_k = max(0, budget - 1);
   const int Ktot = min(budget / a.sparse_div + budget / a.recent_div, cap_k);  // baselines
-  int S = 0, Br = 0, A_keep = 0;
-
-  int M = 0, c_first = 0;
-  int win_lo = 0, n_anchor_slots = 0;       // StreamingLLM
-  int older = 0;                            // H2O: slots [0, older) are ranked by score
-  bool keep_all_older = true;
-  unsigned long long thr_key = 0;
-  const bool have = a.have_scores != 0;
-  if (a.policy == LG_POLICY_LOOPGUARD) {
-    // Pass 1: sizes of the anchor prefix, the middle region and the clean recent window.
-    int aloc = 0, mloc = 0, cloc = 0;
-    for (int j = tid; j < L; j += TPB) {
-      const int pj = pos[j];
-      const bool A = pj < a.n_anchor;
-      const bool Rc = !A && pj >= thrR;
-      const bool bad = Rc && span >= 0 && pj >= span;
-      aloc += A ? 1 : 0;
-      mloc += (!A && !Rc) ? 1 : 0;
-      cloc += (Rc && !bad) ? 1 : 0;
-    }
-    const int NA = block_count<TPB>(aloc, red);
-    M = block_count<TPB>(mloc, red);
-    const int C = block_count<TPB>(cloc, red);
-    A_keep = min(NA, cap_k);
-    Br = min(R >> level, cap_k - A_keep);
-    S = max(0, min(budget / a.sparse_div - a.n_anchor, cap_k - A_keep - Br));
-    c_first = C - min(Br, C);  // clean recent slots with rank >= c_first are kept
-  } else if (a.policy == LG_POLICY_STREAMING) {
-    int aloc = 0;
-    for (int j = tid; j < L; j += TPB) aloc += pos[j] < a.n_anchor ? 1 : 0;
-    n_anchor_slots = min(block_count<TPB>(aloc, red), Ktot);  // a prefix of the slots (positions ascend)
-    const int window = max(0, Ktot - n_anchor_slots);
-    win_lo = max(n_anchor_slots, L - window);
-  } else {
+  int kept;
+  if (a.policy == LG_POLICY_H2O) {
+    // Slots [0, older) are ranked by score, the later ones kept.
+    const bool have = a.have_scores != 0;
+    const int Rp = max(0, min(min(R, L), Ktot));
+    const int older = L - Rp;
+    const int heavy = max(0, Ktot - Rp);
+    const bool keep_all_older = older <= heavy;
     __shared__ unsigned int hist[256];
     __shared__ unsigned long long s_prefix;
     __shared__ int s_need;
-    const int Rp = min(min(R, L), Ktot);
-    older = L - Rp;
-    const int heavy = max(0, Ktot - Rp);
-    keep_all_older = older <= heavy;
+    unsigned long long thr_key = ~0ull;  // keeps none of the older slots
+    // Without scores the order is the slots': the latest heavy ones stay.
     if (!keep_all_older && heavy > 0)
-      thr_key = radix_select_desc<TPB>(kidx, have, older, heavy, hist, &s_prefix, &s_need, red);
-    else if (!keep_all_older)
-      thr_key = ~0ull;  // keep none of the older slots (never reached with K >= R)
-  }
-
-  // Pass 2: ranks and the kept list, 256 slots at a time.
-  int mid_base = 0, cr_base = 0, out_base = 0;
-  for (int j0 = 0; j0 < L; j0 += TPB) {
-    const int j = j0 + tid;
-    bool A = false, Mid = false, Cr = false, keep = false;
-    if (j < L) {
-      const int pj = pos[j];
-      if (a.policy == LG_POLICY_LOOPGUARD) {
-        A = pj < a.n_anchor;
-        const bool Rc = !A && pj >= thrR;
-        const bool bad = Rc && span >= 0 && pj >= span;
-        Mid = !A && !Rc;
-        Cr = Rc && !bad;
-      } else if (a.policy == LG_POLICY_STREAMING) {
-        keep = j < n_anchor_slots || j >= win_lo;
-      } else {
-        keep = j >= older || keep_all_older || h2o_key(kidx, j, have) >= thr_key;
+      thr_key = have ? radix_select_desc<TPB>(kidx, have, older, heavy, hist, &s_prefix, &s_need, red)
+                     : h2o_key(kidx, older - heavy, have);
+    kept = 0;
+    for (int j0 = 0; j0 < L; j0 += TPB) {
+      const int j = j0 + tid;
+      const bool keep = j < L && (j >= older || keep_all_older || h2o_key(kidx, j, have) >= thr_key);
+      int ktot;
+      const int slot = kept + block_exclusive_scan<TPB>(keep ? 1 : 0, &ktot, red);
+      if (keep) kidx[slot] = j;
+      kept += ktot;
+    }
+    __syncthreads();
+    // Gather pos in place (ascending chunks, read all before writing).
+    for (int r0 = 0; r0 < kept; r0 += TPB) {
+      const int r = r0 + tid;
+      int v = 0;
+      if (r < kept) {
+        const int j = kidx[r];
+        v = in.appended && j == Ls ? in.t_append : pos[j];
+      }
+      __syncthreads();
+      if (r < kept) pos[r] = v;
+    }
+  } else {
+    // Ends of the ranges among the stored slots, then with the appended one.
+    __shared__ int s_end[3];
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (wave < 3) {
+      const int thr = wave == 0 ? a.n_anchor : wave == 1 ? thrR : span;
+      const int e = wave_lower_bound(pos, Ls, thr) + (in.appended && in.t_append < thr ? 1 : 0);
+      if ((tid & 63) == 0) s_end[wave] = e;
+    }
+    __syncthreads();
+    const int NA = s_end[0];
+    // Kept: slots [0, n_a), n_s of the M slots from NA, and n_r slots from r_lo.
+    int n_a, n_s = 0, M = 0, S = 0, n_r, r_lo;
+    if (a.policy == LG_POLICY_STREAMING) {
+      n_a = min(NA, max(Ktot, 0));
+      r_lo = max(n_a, L - max(0, Ktot - n_a));
+      n_r = L - r_lo;
+    } else {
+      const int jR = max(NA, s_end[1]);                    // middle: [NA, jR)
+      const int jB = span >= 0 ? max(jR, s_end[2]) : L;    // clean recent window: [jR, jB)
+      M = jR - NA;
+      n_a = min(NA, cap_k);
+      const int Br = min(R >> level, cap_k - n_a);
+      S = max(0, min(budget / a.sparse_div - a.n_anchor, cap_k - n_a - Br));
+      n_s = min(M, S);
+      n_r = max(0, min(Br, jB - jR));
+      r_lo = jB - n_r;
+    }
+    kept = n_a + n_s + n_r;
+    // Entry r of the keep list, and pos gathered in place: entries ascend and slot(r) >= r, so a
+    // chunk's writes lie below every slot a later chunk reads; a chunk is read before it is written.
+    constexpr int U = 8;
+    for (int r0 = 0; r0 < kept; r0 += TPB * U) {
+      int j[U], v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int r = r0 + u * TPB + tid;
+        const int k = r - n_a;
+        int x = r;
+        if (k >= 0 && k < n_s && M > n_s)
+          x = NA + (((long long)k * M) >> 32 ? (int)((long long)k * M / S)
+                                             : (int)((unsigned)k * (unsigned)M / (unsigned)S));
+        else if (k >= 0 && k < n_s) x = NA + k;
+        else if (k >= n_s) x = r_lo + (k - n_s);
+        j[u] = x;
+        v[u] = 0;
+        if (r < kept) v[u] = in.appended && x == Ls ? in.t_append : pos[x];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int r = r0 + u * TPB + tid;
+        if (r < kept) {
+          kidx[r] = j[u];
+          pos[r] = v[u];
+        }
       }
     }
-    int mtot, ctot;
-    const int mrank = mid_base + block_exclusive_scan<TPB>(Mid ? 1 : 0, &mtot, red);
-    const int crank = cr_base + block_exclusive_scan<TPB>(Cr ? 1 : 0, &ctot, red);
-    if (A) keep = j < A_keep;  // the anchors are a prefix of the slots
-    if (Mid) keep = (M <= S) || sparse_hit(mrank, M, S);
-    if (Cr) keep = crank >= c_first;
-    int ktot;
-    const int slot = out_base + block_exclusive_scan<TPB>(keep ? 1 : 0, &ktot, red);
-    if (keep) kidx[slot] = j;
-    mid_base += mtot;
-    cr_base += ctot;
-    out_base += ktot;
-  }
-  __syncthreads();
-  // Gather pos in place (ascending chunks, read all before writing).
-  for (int r0 = 0; r0 < out_base; r0 += TPB) {
-    const int r = r0 + tid;
-    int v = 0;
-    if (r < out_base) v = pos[kidx[r]];
-    __syncthreads();
-    if (r < out_base) pos[r] = v;
-    __syncthreads();
   }
   if (tid == 0) {
-    a.new_len[b] = out_base;
-    a.len[b] = out_base;
+    a.new_len[b] = kept;
+    a.len[b] = kept;
   }
 }
 

@@ -3,16 +3,17 @@
 // upkeep.
 //
 // keepset_kernel (one workgroup per sequence): commit the append, decide whether the sequence is
-// pruned (trigger, or cache at its budget), mark every live slot as anchor / recent window / bad
-// tail / middle from its position, and stream-compact the kept slots with block-wide prefix sums:
+// pruned (trigger, or cache at its budget), and write the kept slots to keep_idx:
 //   kept(j) = anchor(j) or (middle(j) and rank_mid(j) is one of the S evenly spaced ranks) or
 //             (clean recent(j) and it is among the last R >> l clean recent slots)
-// The kept slot list is written to keep_idx; pos is gathered in place.
+// Positions ascend over the slots, so these regions are ranges whose ends are found by search and
+// every kept slot has a closed form; pos is gathered in place.
 //
 // With the baseline policies (H2O, StreamingLLM; Sec. 6.1) only a cache at its budget is pruned and
 // the kept set is the policy's: h2o_score_kernel first sums every slot's acc over the layers and KV
 // heads into keep_idx (float bits, used as scratch), and keepset_kernel finds the H2O threshold
-// key by an 8-bit radix select over (score, slot) keys before the same stream compaction.
+// key by an 8-bit radix select over (score, slot) keys and stream-compacts the slots at or above it
+// with block-wide prefix sums.
 //
 // compact_kernel (one workgroup per (kv head, sequence, layer)): moves K, V and acc rows
 // r <- keep_idx[r] in place. keep_idx is ascending with keep_idx[r] >= r, so walking the rows in
@@ -88,8 +89,17 @@ struct CompactArgs {
   int32_t B, Hkv, cap, row_bytes;
 };
 
-__global__ __launch_bounds__(kPruneThreads) void keepset_kernel(KeepArgs a) {
-  keep_set_block<kPruneThreads>(a);
+__global__ __launch_bounds__(kKeepThreads) void keepset_kernel(KeepArgs a) {
+  const int b = blockIdx.x;
+  const KeepInputs in = load_keep_inputs(a, b);
+  bool trig = false;
+  int span = -1, level = 0;
+  if (a.policy == LG_POLICY_LOOPGUARD && a.decision != nullptr) {
+    trig = a.decision[b].trigger != 0;
+    span = a.decision[b].span_lo;
+    level = a.decision[b].level;
+  }
+  keep_set_block<kKeepThreads>(a, in, trig, span, level);
 }
 
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
@@ -238,7 +248,7 @@ hipError_t launch_prune(const lg_guard_params* p, int batch, int cap, int n_laye
                                 keep_idx, new_len);
   hipError_t e = ka.have_scores ? launch_h2o_scores(ka, n_layers, layers, st) : hipSuccess;
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(keepset_kernel, dim3(batch), dim3(kPruneThreads), 0, st, ka);
+  hipLaunchKernelGGL(keepset_kernel, dim3(batch), dim3(kKeepThreads), 0, st, ka);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   return launch_compact(ka, n_layers, layers, st);

@@ -162,6 +162,19 @@ def test_prune_parity_random_shapes(i):
           tied_acc=policy == 1 and i % 2 == 0)
 
 
+@pytest.mark.parametrize("policy", [0, 1, 2])
+@pytest.mark.parametrize("B,cap,D,dtype", [(1, 1, 64, "bf16"), (5, 2, 64, "bf16"), (70, 65, 64, "bf16"),
+                                           (9, 64, 128, "f32"), (130, 129, 64, "f32"), (3, 255, 128, "bf16"),
+                                           (3, 257, 64, "f32"), (2, 4097, 128, "bf16"), (2, 5000, 64, "bf16")])
+def test_prune_parity_edges(B, cap, D, dtype, policy):
+    """Caches around the search's 64-way rounds and the compaction's passes (1, 64 +- 1, 256 +- 1,
+    4096 + 1 slots), every row width, and batches of more than 64 sequences of which about half are
+    pruned (the compaction's workgroups share them by rank)."""
+    p = oracle.paper_params(policy=policy)
+    _case(B, cap, D, dtype, 2, seed=900 + cap + policy, params=p, tied_acc=policy == 1,
+          budgets=[max(1, cap - i % 3) for i in range(B)])
+
+
 def test_budget_upkeep_without_decisions():
     assert _case(16, 512, 128, "bf16", 2, seed=11, with_decision=False) > 0
 
