@@ -7,7 +7,6 @@
 
 namespace lg {
 
-constexpr int kPruneThreads = 256;   // compaction
 constexpr int kKeepThreads = 512;    // keepset_kernel
 
 struct KeepArgs {

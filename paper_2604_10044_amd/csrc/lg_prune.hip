@@ -15,8 +15,8 @@
 // key by an 8-bit radix select over (score, slot) keys and stream-compacts the slots at or above it
 // with block-wide prefix sums.
 //
-// compact_kernel (one workgroup per (kv head, sequence, layer)): moves K, V and acc rows
-// r <- keep_idx[r] in place. keep_idx is ascending with keep_idx[r] >= r, so walking the rows in
+// compact_kernel (one workgroup per 128-byte column of a (layer, kv head)'s K or V rows and group of
+// sequences): moves K, V and acc rows r <- keep_idx[r] in place. keep_idx is ascending with keep_idx[r] >= r, so walking the rows in
 // chunks, reading a whole chunk before writing it, never overwrites a row a later chunk reads;
 // the next chunk's loads are issued before the current chunk's stores.
 #include "lg_keepset.h"
@@ -87,6 +87,7 @@ struct CompactArgs {
   const int32_t* keep_idx;
   const int32_t* new_len;
   int32_t B, Hkv, cap, row_bytes;
+  int32_t n_col;  // 128-byte columns of a K row and a V row together
 };
 
 __global__ __launch_bounds__(kKeepThreads) void keepset_kernel(KeepArgs a) {
@@ -103,86 +104,106 @@ __global__ __launch_bounds__(kKeepThreads) void keepset_kernel(KeepArgs a) {
 }
 
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-constexpr int kCompactUnroll = 8;  // row groups per compaction pass (rows in flight per thread)
+
+// A compaction workgroup moves one 128-byte column of one layer's K or V for one KV head: a row's
+// columns are independent, so a sequence's rows spread over row_bytes / 64 times as many workgroups
+// as there are (layer, kv head) pairs. With whole K and V rows per workgroup, one flagged sequence
+// (the usual event) of the 7B shape was 112 workgroups, each a chain of ten dependent passes:
+// 52.8 us for the 1261 rows in 28 layers on MI355X, 33 us now; all 32 sequences at once 0.89 ms (5.5
+// GB, read and written), 0.91 ms before. Threads x rows in flight per thread, for one sequence (the
+// whole call) / for all: 256 x 8 44.1 / 915 us, 512 x 8 44.8 / 861, 512 x 4 41.8 / 888, 1024 x 4
+// 48.0 / 831, 1024 x 8 (spills) 95 / 869.
+constexpr int kCompactThreads = 512;
+constexpr int kCompactUnroll = 4;                        // rows in flight per thread
+constexpr int kColBytes = 128;
+constexpr int kColLanes = kColBytes / 16;                // lanes of a row
+constexpr int kPassRows = kCompactThreads / kColLanes;   // rows of one load instruction
+constexpr int kRowsPerPass = kPassRows * kCompactUnroll;
+constexpr int kCompactWorkgroups = 4096;
+static_assert(kRowsPerPass <= kCompactThreads, "at most one score per thread and pass");
 
 // Rows of a compaction pass, held in registers between its loads and its stores.
-template <int U>
 struct MovePass {
-  uint4 k[U], v[U];
-  float acc[U];
-  int src[U];
+  u32x4_t x[kCompactUnroll];
+  int src[kCompactUnroll];
+  float acc;     // column 0 of K only: the score of row r0 + tid
+  int acc_src;
 };
 
-template <int TPR, int U>
-__device__ __forceinline__ void compact_load(MovePass<U>& m, int r0, int rsub, int piece, int nl,
-                                             const int32_t* kidx, const uint4* K, const uint4* V,
+__device__ __forceinline__ void compact_load(MovePass& m, int r0, int rsub, int nl,
+                                             const int32_t* kidx, const char* col, int row_bytes,
                                              const float* acc) {
-  constexpr int RPP = kPruneThreads / TPR;
 #pragma unroll
-  for (int u = 0; u < U; ++u) {  // all source indices first: one wait before the row loads
-    const int r = r0 + u * RPP + rsub;
+  for (int u = 0; u < kCompactUnroll; ++u) {  // all source indices first: one wait before the loads
+    const int r = r0 + u * kPassRows + rsub;
     m.src[u] = r < nl ? kidx[r] : r;
   }
+  const int ra = r0 + (int)threadIdx.x;
+  m.acc_src = acc != nullptr && (int)threadIdx.x < kRowsPerPass && ra < nl ? kidx[ra] : ra;
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int r = r0 + u * RPP + rsub;
-    if (m.src[u] != r) {  // rows are read once: non-temporal
-      const u32x4_t k4 = __builtin_nontemporal_load((const u32x4_t*)(K + (size_t)m.src[u] * TPR + piece));
-      const u32x4_t v4 = __builtin_nontemporal_load((const u32x4_t*)(V + (size_t)m.src[u] * TPR + piece));
-      m.k[u] = make_uint4(k4.x, k4.y, k4.z, k4.w);
-      m.v[u] = make_uint4(v4.x, v4.y, v4.z, v4.w);
-      m.acc[u] = acc[m.src[u]];
-    }
+  for (int u = 0; u < kCompactUnroll; ++u) {
+    const int r = r0 + u * kPassRows + rsub;
+    if (m.src[u] != r)  // rows are read once: non-temporal
+      m.x[u] = __builtin_nontemporal_load((const u32x4_t*)(col + (size_t)m.src[u] * row_bytes));
   }
+  if (m.acc_src != ra) m.acc = acc[m.acc_src];
 }
 
-template <int TPR, int U>
-__device__ __forceinline__ void compact_store(const MovePass<U>& m, int r0, int rsub, int piece,
-                                              uint4* K, uint4* V, float* acc) {
-  constexpr int RPP = kPruneThreads / TPR;
+__device__ __forceinline__ void compact_store(const MovePass& m, int r0, int rsub, char* col,
+                                              int row_bytes, float* acc) {
 #pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int r = r0 + u * RPP + rsub;
-    if (m.src[u] != r) {  // non-temporal: the rows are next read by a streaming attention sweep
-      __builtin_nontemporal_store(u32x4_t{m.k[u].x, m.k[u].y, m.k[u].z, m.k[u].w},
-                                  (u32x4_t*)(K + (size_t)r * TPR + piece));
-      __builtin_nontemporal_store(u32x4_t{m.v[u].x, m.v[u].y, m.v[u].z, m.v[u].w},
-                                  (u32x4_t*)(V + (size_t)r * TPR + piece));
-      if (piece == 0) acc[r] = m.acc[u];
-    }
+  for (int u = 0; u < kCompactUnroll; ++u) {
+    const int r = r0 + u * kPassRows + rsub;
+    if (m.src[u] != r)  // non-temporal: the rows are next read by a streaming attention sweep
+      __builtin_nontemporal_store(m.x[u], (u32x4_t*)(col + (size_t)r * row_bytes));
   }
+  const int ra = r0 + (int)threadIdx.x;
+  if (m.acc_src != ra) acc[ra] = m.acc;
 }
 
-// Passes of RPP * U rows in ascending order. Pass p writes rows [r0, r0 + RPP*U) and may read
-// them as sources, so its loads must all complete before any of its stores (one barrier per
+// Passes of kRowsPerPass rows in ascending order. Pass p writes rows [r0, r0 + kRowsPerPass) and may
+// read them as sources, so its loads must all complete before any of its stores (one barrier per
 // pass); its sources are >= its rows, and the next pass's sources are >= the next pass's rows,
 // which lie above every row pass p writes, so the next pass's loads are issued before pass p's
 // stores.
-template <int TPR, int U>
-__global__ __launch_bounds__(kPruneThreads) void compact_kernel(CompactArgs a) {
-  // Grid (layer, kv head, sequence), the layer fastest: the dispatcher deals consecutive
-  // workgroups round-robin to the 8 XCDs, so the rows of one flagged sequence (the usual event)
-  // spread over all of them.
-  const int l = blockIdx.x, hkv = blockIdx.y, b = blockIdx.z;
-  const int nl = a.new_len[b];
-  if (nl <= 0) return;
-  constexpr int RPP = kPruneThreads / TPR;  // rows per pass and unroll step
-  constexpr int ROWS = RPP * U;             // rows per pass
+__device__ __forceinline__ void compact_column(const CompactArgs& a, int l, int hkv, int col, int b,
+                                               int nl) {
   const int tid = threadIdx.x;
-  const int rsub = tid / TPR, piece = tid % TPR;
+  const int rsub = tid / kColLanes, piece = tid % kColLanes;
+  const int ncol = a.row_bytes / kColBytes;
   const size_t bk = (size_t)b * a.Hkv + hkv;
-  uint4* K = (uint4*)((char*)a.layer[l].k + bk * a.cap * (size_t)a.row_bytes);
-  uint4* V = (uint4*)((char*)a.layer[l].v + bk * a.cap * (size_t)a.row_bytes);
-  float* acc = a.layer[l].acc + bk * a.cap;
+  char* rows = (char*)(col < ncol ? a.layer[l].k : a.layer[l].v) + bk * a.cap * (size_t)a.row_bytes +
+               (col % ncol) * kColBytes + 16 * piece;
+  float* acc = col == 0 ? a.layer[l].acc + bk * a.cap : nullptr;
   const int32_t* kidx = a.keep_idx + (size_t)b * a.cap;
-  MovePass<U> cur, nxt;
-  compact_load<TPR, U>(cur, 0, rsub, piece, nl, kidx, K, V, acc);
-  for (int r0 = 0; r0 < nl; r0 += ROWS) {
+  MovePass cur, nxt;
+  compact_load(cur, 0, rsub, nl, kidx, rows, a.row_bytes, acc);
+  for (int r0 = 0; r0 < nl; r0 += kRowsPerPass) {
     __syncthreads();  // every thread holds this pass's rows
-    const bool more = r0 + ROWS < nl;
-    if (more) compact_load<TPR, U>(nxt, r0 + ROWS, rsub, piece, nl, kidx, K, V, acc);
-    compact_store<TPR, U>(cur, r0, rsub, piece, K, V, acc);
+    const bool more = r0 + kRowsPerPass < nl;
+    if (more) compact_load(nxt, r0 + kRowsPerPass, rsub, nl, kidx, rows, a.row_bytes, acc);
+    compact_store(cur, r0, rsub, rows, a.row_bytes, acc);
     if (more) cur = nxt;
+  }
+}
+
+// Grid (layer, kv head x column, group of sequences), the layer fastest: the dispatcher deals
+// consecutive workgroups round-robin to the 8 XCDs, so the rows of one flagged sequence spread over
+// all of them. Group z takes the flagged sequences of rank z, z + groups, ..., whichever they are,
+// so a launch with nothing to move stays small and a few flagged sequences do not share a group.
+__global__ __launch_bounds__(kCompactThreads) void compact_kernel(CompactArgs a) {
+  const int l = blockIdx.x, hkv = blockIdx.y / a.n_col, col = blockIdx.y % a.n_col;
+  const int lane = threadIdx.x & 63, groups = gridDim.z;
+  int rank = 0;  // flagged sequences before this chunk
+  for (int b0 = 0; b0 < a.B; b0 += 64) {
+    const int mine = b0 + lane < a.B ? a.new_len[b0 + lane] : 0;
+    unsigned long long m = __ballot(mine > 0);
+    for (; m != 0; m &= m - 1, ++rank) {
+      if (rank % groups != (int)blockIdx.z) continue;
+      const int k = __builtin_ctzll(m);
+      compact_column(a, l, hkv, col, b0 + k, __builtin_amdgcn_readlane(mine, k));
+      __syncthreads();
+    }
   }
 }
 
@@ -227,12 +248,13 @@ hipError_t launch_compact(const KeepArgs& ka, int n_layers, const lg_layer_cache
     ca.Hkv = Hkv;
     ca.cap = ka.cap;
     ca.row_bytes = row_bytes;
-    dim3 grid(nl, Hkv, ka.B);
-    switch (row_bytes / 16) {
-      case 8: hipLaunchKernelGGL((compact_kernel<8, kCompactUnroll>), grid, dim3(kPruneThreads), 0, st, ca); break;
-      case 16: hipLaunchKernelGGL((compact_kernel<16, kCompactUnroll>), grid, dim3(kPruneThreads), 0, st, ca); break;
-      default: hipLaunchKernelGGL((compact_kernel<32, kCompactUnroll>), grid, dim3(kPruneThreads), 0, st, ca); break;
-    }
+    ca.n_col = 2 * row_bytes / kColBytes;
+    // About kCompactWorkgroups workgroups: enough to fill the chip when every sequence is flagged,
+    // few enough that the launch of a step with nothing to move costs no more than its start.
+    const int per_group = nl * Hkv * ca.n_col;
+    const int groups = min(ka.B, max(1, kCompactWorkgroups / per_group));
+    dim3 grid(nl, Hkv * ca.n_col, groups);
+    hipLaunchKernelGGL(compact_kernel, grid, dim3(kCompactThreads), 0, st, ca);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
