@@ -45,11 +45,10 @@ typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 // keeps normal loads so it can stay resident in the last-level cache across steps.
 template <bool NT>
 __device__ __forceinline__ uint4 ld_stream16(const void* p) {
-  if (NT) {
-    const u32x4_t v = __builtin_nontemporal_load((const u32x4_t*)p);
-    return make_uint4(v.x, v.y, v.z, v.w);
-  }
-  return *(const uint4*)p;
+  // A vector type in both cases: a struct's load can be split into dwords when its address comes
+  // from a branch.
+  const u32x4_t v = NT ? __builtin_nontemporal_load((const u32x4_t*)p) : *(const u32x4_t*)p;
+  return make_uint4(v.x, v.y, v.z, v.w);
 }
 
 template <typename T> __device__ __forceinline__ float to_f32(T x);
@@ -326,6 +325,29 @@ struct Online {
   float m, l, s;
 };
 
+// Maximum over the four 16-lane row groups, in every lane: two register swaps between lanes (gfx950's
+// permlane swaps) where a shuffle is an LDS round trip.
+__device__ __forceinline__ float row_groups_max(float x) {
+  typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
+  const unsigned u = __float_as_uint(x);
+  const u32x2_t r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const unsigned w = __float_as_uint(fmaxf(__uint_as_float(r.x), __uint_as_float(r.y)));
+  const u32x2_t t = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return fmaxf(__uint_as_float(t.x), __uint_as_float(t.y));
+}
+// Maximum or sum over the four neighbouring lanes 4k .. 4k + 3, in each of them.
+template <bool MAX>
+__device__ __forceinline__ float quad_all(float x) {
+  const float y = __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(x), 0xB1, 0xf, 0xf, true));
+  x = MAX ? fmaxf(x, y) : x + y;
+  const float z = __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(x), 0x4E, 0xf, 0xf, true));
+  return MAX ? fmaxf(x, z) : x + z;
+}
+
+// 2^x by the hardware instruction: exp2f without its scaling of results below 2^-126, which are 0
+// here (a probability that small against one of at least 2^-11 in the same sum).
+__device__ __forceinline__ float exp2_hw(float x) { return __builtin_amdgcn_exp2f(x); }
+
 typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) short4_t lds_short4;
 
@@ -396,6 +418,56 @@ struct QFrag {
   uint4 q[Geo<T, D>::NS];
 };
 
+// Slots of a block in the recent suffix (bit j = slot blk + j).
+template <int BS>
+__device__ __forceinline__ unsigned long long suffix_bits(const RowCtx& r, int blk, int lane) {
+  const int ps = blk + (lane & (BS - 1));
+  return __ballot(lane < BS && ps >= r.jsuf && ps < r.n_eff);
+}
+
+// q.K^T of one tile of 16 slots, K rows in the A layout.
+template <typename T, int D>
+__device__ __forceinline__ f32x4_t qk_tile(const uint4* kr, const QFrag<T, D>& qf) {
+  constexpr int NS = Geo<T, D>::NS;
+  f32x4_t S = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  if constexpr (sizeof(T) == 4) {
+    // Eight partial dot products for every four k-steps, added as a tree: as close to the exact
+    // sum as a lane-wise reduction (one chain of D terms is not), and eight independent chains.
+#pragma unroll
+    for (int k0 = 0; k0 < NS; k0 += 4) {
+      f32x4_t P[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) P[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int kk = k0; kk < k0 + 4; ++kk) {
+        const unsigned* kx = (const unsigned*)&kr[kk];
+        const unsigned* qx = (const unsigned*)&qf.q[kk];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          // A register of its own: while the element is part of a 16-byte load, clang 22
+          // (ROCm 7.2) put the accumulator over elements that were still to be multiplied, in
+          // the non-temporal merge-form instances (seen in the listing; wrong logits).
+          float x = __uint_as_float(kx[e]);
+          asm("" : "+v"(x));
+          f32x4_t& acc = P[4 * (kk & 1) + e];
+          acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x, __uint_as_float(qx[e]), acc, 0, 0, 0);
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const float t = ((P[0][v] + P[1][v]) + (P[2][v] + P[3][v])) +
+                        ((P[4][v] + P[5][v]) + (P[6][v] + P[7][v]));
+        S[v] = k0 == 0 ? t : S[v] + t;
+      }
+    }
+  } else {
+#pragma unroll
+    for (int kk = 0; kk < NS; ++kk)
+      S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kr[kk]), as_bf16x8(qf.q[kk]), S, 0, 0, 0);
+  }
+  return S;
+}
+
 template <typename T, int D, int DV>
 __device__ __forceinline__ void stage_qk(const Block<T, D, DV>& B, const RowCtx& r, int blk, int lane,
                                          const QFrag<T, D>& qf, f32x4_t* S,
@@ -403,9 +475,7 @@ __device__ __forceinline__ void stage_qk(const Block<T, D, DV>& B, const RowCtx&
   using Gm = Geo<T, D, DV>;
   constexpr int NS = Gm::NS, BS = Gm::BS;
   const int g = lane >> 4, c = lane & 15;
-  // Slots of this block in the recent suffix (bit j = slot blk + j).
-  const int ps = blk + (lane & (BS - 1));
-  suf = __ballot(lane < BS && ps >= r.jsuf && ps < r.n_eff);
+  suf = suffix_bits<BS>(r, blk, lane);
   // q.K^T on the matrix cores: lane holds slots blk + slot(4g + v, mt) of head c.
 #pragma unroll
   for (int mt = 0; mt < Gm::MT; ++mt) {
@@ -419,43 +489,7 @@ __device__ __forceinline__ void stage_qk(const Block<T, D, DV>& B, const RowCtx&
 #pragma unroll
       for (int kk = 0; kk < NS; ++kk) kr[kk] = r.snew[4 * kk + g];
     }
-    S[mt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    if constexpr (Gm::F32) {
-      // Eight partial dot products for every four k-steps, added as a tree: as close to the exact
-      // sum as a lane-wise reduction (one chain of D terms is not), and eight independent chains.
-#pragma unroll
-      for (int k0 = 0; k0 < NS; k0 += 4) {
-        f32x4_t P[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) P[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int kk = k0; kk < k0 + 4; ++kk) {
-          const unsigned* kx = (const unsigned*)&kr[kk];
-          const unsigned* qx = (const unsigned*)&qf.q[kk];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            // A register of its own: while the element is part of a 16-byte load, clang 22
-            // (ROCm 7.2) put the accumulator over elements that were still to be multiplied, in
-            // the non-temporal merge-form instances (seen in the listing; wrong logits).
-            float x = __uint_as_float(kx[e]);
-            asm("" : "+v"(x));
-            f32x4_t& acc = P[4 * (kk & 1) + e];
-            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x, __uint_as_float(qx[e]), acc, 0, 0, 0);
-          }
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const float t = ((P[0][v] + P[1][v]) + (P[2][v] + P[3][v])) +
-                          ((P[4][v] + P[5][v]) + (P[6][v] + P[7][v]));
-          S[mt][v] = k0 == 0 ? t : S[mt][v] + t;
-        }
-      }
-    } else {
-#pragma unroll
-      for (int kk = 0; kk < NS; ++kk)
-        S[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kr[kk]), as_bf16x8(qf.q[kk]),
-                                                        S[mt], 0, 0, 0);
-    }
+    S[mt] = qk_tile<T, D>(kr, qf);
   }
 }
 
@@ -502,17 +536,16 @@ __device__ __forceinline__ void finish_block(const f32x4_t* S, unsigned long lon
       else *(float4*)(sr.glob + blk + Gm::slot(4 * g, mt)) = sv;
     }
   }
-  mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+  mx = row_groups_max(mx);
   const float m_new = fmaxf(st.m, mx);
-  const float alpha = exp2f(st.m - m_new);
+  const float alpha = exp2_hw(st.m - m_new);
   float p[MT][4];
   float psum = 0.f, ssum = 0.f;
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      p[mt][v] = exp2f(s[mt][v] - m_new);
+      p[mt][v] = exp2_hw(s[mt][v] - m_new);
       psum += p[mt][v];
       ssum += ((suf >> Gm::slot(4 * g + v, mt)) & 1ull) ? p[mt][v] : 0.f;
     }
@@ -822,7 +855,7 @@ __device__ __forceinline__ void single_split_epilogue(const AttendArgs& a, const
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
       const float mw = sm_m[w][h];
-      const float f = mw == -INFINITY ? 0.f : exp2f(mw - M);
+      const float f = mw == -INFINITY ? 0.f : exp2_hw(mw - M);
       sf1[h][w] = f;
       lsum += f * sm_l[w][h];
       ssum += f * sm_s[w][h];
@@ -857,7 +890,7 @@ __device__ __forceinline__ void single_split_epilogue(const AttendArgs& a, const
         const f32x4_t lg = *(const f32x4_t*)(slog + hc * MS + 4 * tid + 256 * NW * u);
         const float M = sM1[hc], rz = srZ1[hc];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sum[e] += h < G ? exp2f(lg[e] - M) * rz : 0.f;
+        for (int e = 0; e < 4; ++e) sum[e] += h < G ? exp2_hw(lg[e] - M) * rz : 0.f;
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -936,7 +969,7 @@ __device__ __forceinline__ void exchange_epilogue(const AttendArgs& a, const f32
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
       const float mw = sm_m[w][h];
-      const float f = mw == -INFINITY ? 0.f : exp2f(mw - M);
+      const float f = mw == -INFINITY ? 0.f : exp2_hw(mw - M);
       sm_f[h][w] = f;
       lsum += f * sm_l[w][h];
       ssum += f * sm_s[w][h];
@@ -968,7 +1001,7 @@ __device__ __forceinline__ void exchange_epilogue(const AttendArgs& a, const f32
         f32x4_t* lp = (f32x4_t*)(slog + h * kMaxSplitSlots + 4 * tid);
         const f32x4_t lg = *lp;
         const float ms = sMs[h];
-        *lp = f32x4_t{exp2f(lg[0] - ms), exp2f(lg[1] - ms), exp2f(lg[2] - ms), exp2f(lg[3] - ms)};
+        *lp = f32x4_t{exp2_hw(lg[0] - ms), exp2_hw(lg[1] - ms), exp2_hw(lg[2] - ms), exp2_hw(lg[3] - ms)};
       }
     }
   };
@@ -1081,7 +1114,7 @@ __device__ __forceinline__ void exchange_epilogue(const AttendArgs& a, const f32
     for (int k = 0; k < ns; ++k) M = fmaxf(M, sst[(k * G + h) * 3]);
     float Z = 0.f, S = 0.f;
     for (int k = 0; k < ns; ++k) {
-      const float f = exp2f(sst[(k * G + h) * 3] - M);
+      const float f = exp2_hw(sst[(k * G + h) * 3] - M);
       sF[h][k] = f;
       Z += sst[(k * G + h) * 3 + 1] * f;
       S += sst[(k * G + h) * 3 + 2] * f;
@@ -1282,7 +1315,7 @@ __device__ __forceinline__ void merge_form_epilogue(const AttendArgs& a, const f
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
       const float mw = sm_m[w][h];
-      const float f = mw == -INFINITY ? 0.f : exp2f(mw - M);
+      const float f = mw == -INFINITY ? 0.f : exp2_hw(mw - M);
       sm_f[h][w] = f;
       lsum += f * sm_l[w][h];
       ssum += f * sm_s[w][h];
@@ -1579,6 +1612,271 @@ void attend_mfma(AttendArgs a) {
 }
 
 // -------------------------------------------------------------------------------------------
+// Few rows: a launch whose rows are too few to fill the device is a chain of latencies, so it is one
+// launch in which every row is finished by its own workgroups, without an exchange: DS workgroups of
+// NW waves, each reading the whole K row (from its XCD's L2 after the first) and computing the
+// softmax, and forming D / DS of the output dims.
+//
+// What bounds it is how fast one CU takes loads. In the A layout neighbouring lanes hold different
+// rows, and the CU's address unit then takes about one cycle a lane (55 cycles a load instruction,
+// measured), where lanes in memory order take 16 a KB: so K, which is contiguous over a block, is
+// loaded in lane order and turned through a wave-private LDS tile, 16 slots at a time. Nothing a
+// wave needs waits for something else: scores, queries, new rows, the header and then its first
+// block with its positions are requested before the row's length is known, and no barrier
+// precedes the sweep.
+// -------------------------------------------------------------------------------------------
+// A block's K rows in memory order: lane l of load j holds the 16 bytes at 1024 j + 16 l.
+template <typename T, int D>
+struct KRaw {
+  static constexpr int RB = D * (int)sizeof(T), NK = Geo<T, D>::BS * RB / 1024;
+  uint4 x[NK];
+};
+// last: byte offset of the row's last 16 bytes (dead slots past cap are clamped to it).
+template <typename T, int D>
+__device__ __forceinline__ void load_kraw(KRaw<T, D>& K, const char* row, int blk, int lane, unsigned last) {
+  const unsigned off = (unsigned)blk * KRaw<T, D>::RB + 16 * lane;
+#pragma unroll
+  for (int j = 0; j < KRaw<T, D>::NK; ++j) K.x[j] = ld_stream16<false>(row + min(off + 1024 * j, last));
+}
+// LDS tile of 16 K rows, row i = A-row i, padded so that 16 rows' pieces fall into different banks.
+template <typename T, int D> constexpr int ktile_stride() { return D * (int)sizeof(T) + 16; }
+// Tile mt of the block into LDS (row-major) and out again in the A layout. A load of four slots or
+// fewer lies in one tile: MT == 2 deals the slots to the tiles four at a time.
+template <typename T, int D>
+__device__ __forceinline__ void turn_k(const KRaw<T, D>& K, const RowCtx& r, int blk, int lane, int mt,
+                                       char* kt, uint4* kr) {
+  using Gm = Geo<T, D>;
+  constexpr int RB = KRaw<T, D>::RB, KS = ktile_stride<T, D>(), LPR = RB / 16;
+  const int g = lane >> 4, c = lane & 15;
+#pragma unroll
+  for (int j = 0; j < KRaw<T, D>::NK; ++j) {
+    const int s = (64 * j + lane) / LPR;  // slot of the block
+    if (Gm::MT == 1 || RB >= 256) {
+      if (Gm::MT == 2 && ((64 * j / LPR) >> 2 & 1) != mt) continue;
+      const int i = Gm::MT == 2 ? 4 * (s >> 3) + (s & 3) : s;
+      *(uint4*)(kt + i * KS + 16 * (lane % LPR)) = K.x[j];
+    } else if (((s >> 2) & 1) == mt) {  // a load holds eight slots, four of each tile
+      *(uint4*)(kt + (4 * (s >> 3) + (s & 3)) * KS + 16 * (lane % LPR)) = K.x[j];
+    }
+  }
+  // The appended row replaces the cache's slot (the wave's LDS writes land in order).
+  const int sub = r.lsub - blk;
+  if (sub >= 0 && sub < Gm::BS && (Gm::MT == 1 || ((sub >> 2) & 1) == mt) && lane < Gm::PPR)
+    *(uint4*)(kt + (Gm::MT == 2 ? 4 * (sub >> 3) + (sub & 3) : sub) * KS + 16 * lane) = r.snew[lane];
+#pragma unroll
+  for (int kk = 0; kk < Gm::NS; ++kk) kr[kk] = *(const uint4*)(kt + c * KS + 64 * kk + 16 * g);
+}
+
+template <typename T, int D, int SG, int MS, int NW, int DS>
+__global__ __launch_bounds__(64 * NW) void attend_few(AttendArgs a) {
+  constexpr int DV = D / DS, VE = DV / 16;
+  using Gm = Geo<T, D, DV>;
+  constexpr int BS = Gm::BS, ES = (int)sizeof(T), WB = wave_lds_bytes<T, DV>();
+  constexpr int NJ = MS / (64 * NW);  // slots per thread: tid + 64 NW k
+  static_assert(NJ >= 1 && NW <= 16 && 64 % DS == 0, "slots in whole waves");
+  // The DS parts of row r are workgroups 8 DS (r / 8) + r % 8 + 8 dh: on one XCD.
+  const int j0 = blockIdx.x % (8 * DS);
+  const int row = 8 * (blockIdx.x / (8 * DS)) + (j0 & 7);
+  if (row >= a.B * a.Hkv) return;
+  const int dh = j0 >> 3;
+  const int b = row / a.Hkv, hkv = row - b * a.Hkv;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int g = lane >> 4, c = lane & 15;
+  const int G = a.G, cap = a.cap;
+  const size_t bk = (size_t)row;
+  RowCtx rc;
+  const char* krow = (const char*)a.k + bk * cap * (D * ES);
+  const unsigned klast = (unsigned)cap * (D * ES) - 16;
+  rc.vrow = Gm::F32 ? Gm::slot(4 * g, 0) : lane / Gm::VPR;
+  rc.vbase = (const char*)a.v + (bk * cap + rc.vrow) * (D * ES) + dh * DV * ES +
+             16 * (Gm::F32 ? c : lane % Gm::VPR);
+  rc.vp0 = dh * Gm::VPR;
+  rc.posb = a.pos + (size_t)b * cap;
+  rc.cap = cap;
+  float old[NJ];
+  float* acc = a.acc + bk * cap;
+#pragma unroll
+  for (int k = 0; k < NJ; ++k) {
+    old[k] = acc[min(tid + 64 * NW * k, cap - 1)];
+  }
+  QFrag<T, D> qf;
+  {
+    const char* qrow = (const char*)a.q + ((size_t)b * a.Hq + hkv * G + (c < G ? c : 0)) * (D * ES);
+#pragma unroll
+    for (int kk = 0; kk < Gm::NS; ++kk)
+      qf.q[kk] = c < G ? *(const uint4*)(qrow + 64 * kk + 16 * g) : make_uint4(0, 0, 0, 0);
+  }
+  // The new rows, for every wave on its own (no barrier before the sweep).
+  __shared__ uint4 s_new[NW][2 * Gm::PPR];
+  rc.snew = s_new[wave];
+  constexpr int XN = (2 * Gm::PPR + 63) / 64;
+  uint4 xnew[XN];
+  // (Without an append the cache's first row stands in: a load in a branch would blur what is
+  // outstanding when a wave waits.)
+  const T* new_k = (const T*)(a.k_new != nullptr ? a.k_new : a.k) + bk * D;
+  const T* new_v = (const T*)(a.v_new != nullptr ? a.v_new : a.v) + bk * D;
+#pragma unroll
+  for (int k = 0; k < XN; ++k) {
+    const int i = (lane + 64 * k) % (2 * Gm::PPR);
+    xnew[k] = ((const uint4*)(i < Gm::PPR ? new_k : new_v))[i % Gm::PPR];
+  }
+  const bool hdr_ok = header_ok<D>(a);
+  KRaw<T, D> K;
+  Block<T, D, DV> A;  // V
+  int ps = 0;         // positions of the block's slots
+  if (BS * wave < cap) {
+    ps = rc.posb[min(BS * wave + (lane & (BS - 1)), cap - 1)];
+    load_kraw<T, D>(K, krow, BS * wave, lane, klast);
+    load_v<T, D, false, true, DV>(A, rc, BS * wave);
+  }
+  const int thr = sat_sub(a.t[b], a.suffix_w[b]);
+  int L, app;
+  const int n = live_slots(a, b, &L, &app);
+  if (n == 0) {
+    if (dh != 0) return;
+    if (!hdr_ok) {
+      if (tid == 0) refuse_row(a, b, LG_ATTEND_STATUS_WORKSPACE);
+      return;
+    }
+    T* out = (T*)a.out + ((size_t)b * a.Hq + hkv * G) * D;
+    for (int i = tid; i < G * D; i += 64 * NW) out[i] = 0;
+    if (tid < G) {
+      a.lse[(size_t)b * a.Hq + hkv * G + tid] = -INFINITY;
+      a.suffix_mass[(size_t)b * a.Hq + hkv * G + tid] = 0.f;
+    }
+    return;
+  }
+  if (app) {
+#pragma unroll
+    for (int k = 0; k < XN; ++k) {
+      const int i = lane + 64 * k;
+      if (i < 2 * Gm::PPR) {
+        s_new[wave][i] = xnew[k];
+        if (dh == 0 && wave == 0)
+          ((uint4*)((T*)(i < Gm::PPR ? a.k_w : a.v_w) + (bk * cap + L) * D))[i % Gm::PPR] = xnew[k];
+      }
+    }
+  }
+  const bool t_in = a.t[b] > thr;  // the appended slot is in the recent suffix
+  rc.L = L;
+  rc.app = app;
+  rc.n_eff = n;
+  rc.lsub = app ? L : -1;
+  __shared__ __attribute__((aligned(16))) float slog[SG * MS];
+  __shared__ __attribute__((aligned(16))) char smem[NW * WB];
+  char* mine = smem + wave * WB;
+  uint16_t* vt = (uint16_t*)mine;
+  __shared__ __attribute__((aligned(16))) char ktile[NW * 16 * ktile_stride<T, D>()];
+  char* kt = ktile + wave * 16 * ktile_stride<T, D>();
+  StashRow sr;
+  sr.use_lds = true;
+  sr.lds = (lds_float*)slog + (c < G ? c : 0) * MS;
+  sr.glob = nullptr;
+  sr.lo = 0;
+  Online st{-INFINITY, 0.f, 0.f};
+  f32x4_t O[VE];
+#pragma unroll
+  for (int i = 0; i < VE; ++i) O[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  for (int blk = BS * wave; blk < n; blk += BS * NW) {
+    const int next = blk + BS * NW;
+    f32x4_t S[Gm::MT];
+#pragma unroll
+    for (int mt = 0; mt < Gm::MT; ++mt) {
+      uint4 kr[Gm::NS];
+      turn_k<T, D>(K, rc, blk, lane, mt, kt, kr);
+      S[mt] = qk_tile<T, D>(kr, qf);
+    }
+    const int slot = blk + (lane & (BS - 1));
+    const unsigned long long suf =
+        __ballot(lane < BS && slot < n && (slot == rc.lsub ? t_in : ps > thr));
+    if (next < n) {
+      ps = rc.posb[min(next + (lane & (BS - 1)), cap - 1)];
+      load_kraw<T, D>(K, krow, next, lane, klast);
+    }
+    if constexpr (Gm::F32) patch_v<D, DV>(A, rc, blk, g, c);
+    else {
+      stage_v<D, DV>(A, rc, blk, g, c, vt);
+      if (next < n) load_v<T, D, false, true, DV>(A, rc, next);
+    }
+    finish_block<T, D, DV>(S, suf, A, rc, blk, g, c, G, a.scale_log2, sr, vt, st, O);
+    if (Gm::F32 && next < n) load_v<T, D, false, true, DV>(A, rc, next);
+  }
+  // The wave's partial; then the waves are merged by wave 0 (lane: head c, waves g, g + 4, ...).
+  float l_run = st.l, s_run = st.s;
+  l_run += __shfl_xor(l_run, 16, 64);
+  l_run += __shfl_xor(l_run, 32, 64);
+  s_run += __shfl_xor(s_run, 16, 64);
+  s_run += __shfl_xor(s_run, 32, 64);
+  __shared__ float sm_m[NW][16], sm_l[NW][16], sm_s[NW][16], sf[16][NW], sM[16], srZ[16], sS[16];
+  if (g == 0) {
+    sm_m[wave][c] = st.m;
+    sm_l[wave][c] = l_run;
+    sm_s[wave][c] = s_run;
+  }
+  put_numerators<T, DV>(O, mine, g, c);
+  // The old scores are here by now: taken before the row's stores, whose completion a later wait
+  // for them would include.
+#pragma unroll
+  for (int k = 0; k < NJ; ++k) asm volatile("" : "+v"(old[k]));
+  lds_barrier();
+  if (!hdr_ok) {
+    if (tid == 0) refuse_row(a, b, LG_ATTEND_STATUS_WORKSPACE);
+    return;
+  }
+  if (wave == 0) {  // four neighbouring lanes per head, each a quarter of the waves
+    const int h = lane >> 2, q4 = lane & 3;
+    constexpr int Q = NW / 4;
+    float mw[Q], M = -INFINITY;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      mw[q] = sm_m[4 * q + q4][h];
+      M = fmaxf(M, mw[q]);
+    }
+    M = quad_all<true>(M);
+    float lsum = 0.f, ssum = 0.f;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const float f = mw[q] == -INFINITY ? 0.f : exp2_hw(mw[q] - M);
+      sf[h][4 * q + q4] = f;
+      lsum += f * sm_l[4 * q + q4][h];
+      ssum += f * sm_s[4 * q + q4][h];
+    }
+    lsum = quad_all<false>(lsum);
+    ssum = quad_all<false>(ssum);
+    if (q4 == 0) {
+      sM[h] = M;
+      srZ[h] = 1.f / lsum;
+      sS[h] = ssum;
+    }
+  }
+  lds_barrier();
+  if (dh == 0 && tid >= 64 * (NW - 1) && lane < G)
+    write_row_stats(a, b, hkv, lane, sM[lane], srZ[lane], sS[lane]);
+  T* out = (T*)a.out + ((size_t)b * a.Hq + hkv * G) * D + dh * DV;
+  for (int i = tid; i < G * DV; i += 64 * NW) {
+    const int h = i / DV;
+    float o = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) o += sf[h][w] * ((const float*)(smem + w * WB))[i];
+    out[h * D + (i - h * DV)] = from_f32<T>(o * srZ[h]);
+  }
+  // H2O increment, one slot per thread: the parts of the row take the groups of 64 in turn.
+#pragma unroll
+  for (int k = 0; k < NJ; ++k) {
+    const int j = tid + 64 * NW * k;
+    if (((j >> 6) & (DS - 1)) == dh && j < n) {
+      float sum = 0.f;
+#pragma unroll
+      for (int h = 0; h < SG; ++h) {
+        const int hc = min(h, G - 1);
+        sum += h < G ? exp2_hw(slog[hc * MS + j] - sM[hc]) * srZ[hc] : 0.f;
+      }
+      acc[j] = app && j == L ? sum : old[k] + sum;
+    }
+  }
+}
+
+// -------------------------------------------------------------------------------------------
 // Combine: exact softmax over the splits, outputs, and the H2O increment from the stash.
 // Same grid as the sweep (one workgroup per split) so a split's stash is read on the XCD that
 // wrote it.
@@ -1795,7 +2093,7 @@ __global__ __launch_bounds__(256) void attend_combine_mfma(AttendArgs a) {
     for (int k = 0; k < ns; ++k) M = fmaxf(M, sml[k * G + tid].x);
     float Z = 0.f, S = 0.f;
     for (int k = 0; k < ns; ++k) {
-      const float f = exp2f(sml[k * G + tid].x - M);
+      const float f = exp2_hw(sml[k * G + tid].x - M);
       sF[tid * kMaxMfmaSplits + k] = f;
       Z += sml[k * G + tid].y * f;
       S += sps[k * G + tid] * f;
@@ -1837,7 +2135,7 @@ __global__ __launch_bounds__(256) void attend_combine_mfma(AttendArgs a) {
       float sum = 0.f;
 #pragma unroll
       for (int h = 0; h < GM; ++h) {
-        const float pr = exp2f(((const float*)&ld.lgv[h])[e] - mh[h]) * rzh[h];
+        const float pr = exp2_hw(((const float*)&ld.lgv[h])[e] - mh[h]) * rzh[h];
         sum += h < G ? pr : 0.f;
       }
       const int j = j0 + e;
@@ -1962,8 +2260,36 @@ hipError_t launch_mfma_form(AttendArgs a, hipStream_t st);
 // The build compiles this file once per part, in parallel, each with the kernels of one cache type
 // and head_dim; part 0 holds the portable kernels and the dispatch.
 #if LG_ATTEND_PART > 0
+// Few rows (the plan has cap <= few_max_slots, and <= 1024 in float32). 16 waves where the logits leave the LDS for it (bfloat16: the step of a 1.5B-shaped batch
+// of one 261 us with 16 waves, 271 with 8); a second block in flight per wave is slower (its loads
+// only queue in the CU's address unit, and delay the first block's: 8 waves 295 -> 308 us).
+template <typename T, int D, int SG, int MS>
+static hipError_t launch_few_ms(const AttendArgs& a, hipStream_t st) {
+  constexpr int DS = few_dsplit(sizeof(T) == 4, D);
+  constexpr int NW = SG * MS <= 8192 && sizeof(T) == 2 ? 16 : 8;
+  const unsigned grid = (unsigned)((a.B * a.Hkv + 7) / 8) * 8 * DS;
+  hipLaunchKernelGGL((attend_few<T, D, SG, MS, NW, DS>), dim3(grid), dim3(64 * NW), 0, st, a);
+  return hipGetLastError();
+}
+template <typename T, int D, int SG>
+static hipError_t launch_few(const AttendArgs& a, hipStream_t st) {
+  constexpr int most = few_max_slots(sizeof(T) == 4, SG);
+  if constexpr (most <= 1024) {
+    if (a.cap <= most) return launch_few_ms<T, D, SG, most>(a, st);
+  } else {
+    if (a.cap <= 1024) return launch_few_ms<T, D, SG, 1024>(a, st);
+    if constexpr (sizeof(T) == 2) return launch_few_ms<T, D, SG, most>(a, st);
+  }
+  return hipErrorInvalidValue;  // the plan never gives this
+}
+
 template <typename T, int D, bool RC>
 hipError_t launch_mfma_form(AttendArgs a, hipStream_t st) {
+  if (a.few && RC == (sizeof(T) == 4)) {
+    if (a.G <= 4) return launch_few<T, D, 4>(a, st);
+    if (a.G <= 8) return launch_few<T, D, 8>(a, st);
+    return launch_few<T, D, 16>(a, st);
+  }
   const bool nt = stream_nt(a, D);
   if (a.form == kFormMerge)
     return nt ? launch_merge_nt<T, D, true, RC>(a, st) : launch_merge_nt<T, D, false, RC>(a, st);
@@ -1998,7 +2324,7 @@ static hipError_t launch_attend_d(AttendArgs a, lg_dtype dt, hipStream_t st) {
   if (a.form == kFormPortable)
     return dt == LG_BF16 ? launch_valu<uint16_t, D>(a, st) : launch_valu<float, D>(a, st);
   if (dt != LG_BF16) return launch_mfma_form<float, D, true>(a, st);
-  return a.cap % 32 == 0 ? launch_mfma_form<uint16_t, D, false>(a, st)
+  return a.cap % 32 == 0 || a.few ? launch_mfma_form<uint16_t, D, false>(a, st)
                          : launch_mfma_form<uint16_t, D, true>(a, st);
 }
 

@@ -159,6 +159,7 @@ static lg_status attend_launch(const lg_layer_cache& layer, const AttendPlan& pl
   a.split = plan.split;
   a.ns_grid = plan.ns_grid;
   a.dsplit = (flags & kFlagWholeDims) ? 1 : plan.dsplit;
+  a.few = plan.few;
   a.row_major = 0;
   a.flags = flags;
   a.spin_limit = kSpinLimit;

@@ -60,7 +60,38 @@ struct AttendPlan {
   int split;    // slots per split
   int ns_grid;  // splits per row in the grid (ceil(cap / split))
   int dsplit;   // workgroups per single-split row, each owning part of the output dims (1 or 2)
+  int few;      // 1: the automatic choice runs attend_few instead of the merge form's two launches
+                // (form, split and workspace stay the merge form's)
 };
+
+// Workgroups per row of attend_few, each forming D / this many output dims.
+constexpr int few_dsplit(bool f32, int D) { return (f32 ? 1 : 2) * (D / 64); }
+// Slots whose logits for SG heads fit its LDS (beside the K, V and numerator tiles of its waves).
+constexpr int few_max_slots(bool f32, int SG) {
+  return (f32 ? 8192 : 16384) / SG < 2048 ? (f32 ? 8192 : 16384) / SG : 2048;
+}
+
+// Launches of few rows that attend_few takes instead of the merge form. Its workgroups (at most one
+// per CU) each read their whole K row, so it wins where rows are short, or where the rows are many
+// enough that the merge form's splits are as long. Measured on MI355X, us a layer in a graph,
+// attend_few / merge form, rows 80% full, 4 heads a group:
+//   bf16, head_dim 128  cap 256: 1 row 5.5 / 8.8, 64 rows 6.9 / 10.4; cap 1024: 1 row 7.8 / 9.6,
+//                       64 rows 10.3 / 12.6, 120 rows 18.5 / 16.5; cap 2048: 1 row 12.4 / 9.7,
+//                       32 rows 13.5 / 13.1, 64 rows 15.7 / 17.6
+//   bf16, head_dim 64   cap 1024: 1 row 6.9 / 8.2, 120 rows 9.4 / 12.9; cap 2048: 1 row 10.7 / 8.7,
+//                       32 rows 11.8 / 10.6, 120 rows 14.0 / 16.3
+//   f32, head_dim 128   cap 256: 1 row 8.6 / 11.5; cap 512: 11.6 / 11.5; cap 1024: 1 row 18.9 / 11.8,
+//                       64 rows 20.8 / 18.8, 120 rows 22.9 / 26.4; cap 2048: 120 rows 47.1 / 41.7
+//   f32, head_dim 64    cap 256: 1 row 6.9 / 9.3; cap 512: 10.1 / 9.6; cap 1024: 120 rows 16.7 / 19.2
+inline bool few_rows(const lg_layer_cache& c) {
+  const bool f32 = c.dtype == LG_F32;
+  const long rows = (long)c.batch * c.n_kv_heads;
+  const int G = c.n_q_heads / c.n_kv_heads;
+  const int most = few_max_slots(f32, G <= 4 ? 4 : G <= 8 ? 8 : 16);
+  const bool many = rows > (!f32 && c.head_dim == 128 ? 32 : 64);
+  const int want = f32 ? (many ? 1024 : 256) : (many ? 2048 : 1024);
+  return rows * few_dsplit(f32, c.head_dim) <= kTargetWorkgroups && c.cap <= want && c.cap <= most;
+}
 
 // Largest split of this layer whose row needs no exchange (0 if none beyond kMaxSplitSlots).
 inline int single_split_max(const lg_layer_cache& c) {
@@ -102,6 +133,7 @@ inline AttendPlan attend_plan(const lg_layer_cache& c, int form, int split_req) 
   // both read the whole K row and compute the softmax, each forms half of the output dims and
   // reads half of V (head_dim 128).
   const long rows = (long)c.batch * c.n_kv_heads;
+  p.few = form == kFormAuto && split_req == 0 && p.form == kFormMerge && few_rows(c);
   p.dsplit = (p.form == kFormOneLaunch && p.split > kMaxSplitSlots && c.head_dim == 128 &&
               2 * rows <= kTargetWorkgroups) ? 2 : 1;
   return p;
@@ -205,6 +237,7 @@ struct AttendArgs {
   int row_major;       // one-launch grid order: splits of a row adjacent (1) or split slowest (0)
   int flags;           // test flags (kFlag*)
   int dsplit;          // AttendPlan::dsplit of this launch
+  int few;             // AttendPlan::few
   int spin_limit;      // polls before a wait gives up
   float scale_log2;    // log2(e) / sqrt(D)
 };

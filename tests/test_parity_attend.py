@@ -248,6 +248,12 @@ RAGGED_CAPS = [
     (70, 16, 1, 64, 2046, [2045, 1] + list(range(1000, 1068))),
     (35, 32, 2, 128, 2045, [2044, 2] + list(range(700, 733))),
     (36, 10, 2, 64, 2044, [2043, 0] + list(range(1900, 1934))),
+    # the same in caches too long for the few-rows kernel
+    (9, 32, 8, 128, 2051, [2050, 2015, 2016, 1, 0, 1024, 1023, 600, 31]),
+    (36, 14, 2, 128, 2051, [2050, 0] + list(range(1500, 1534))),
+    (70, 16, 1, 64, 2050, [2049, 1] + list(range(1000, 1068))),
+    (35, 32, 2, 128, 2049, [2048, 2] + list(range(700, 733))),
+    (36, 10, 2, 64, 2053, [2052, 0] + list(range(1900, 1934))),
     # one row, long cap: splits of 512 slots and more in a cache that is not streamed past the caches
     (1, 2, 1, 64, 16389, [16388]), (1, 7, 1, 64, 16387, [16000]), (1, 16, 1, 64, 16385, [9999]),
 ]
@@ -268,6 +274,29 @@ def test_attend_ragged_caps(shape, dtype):
         for x, y in zip(got, ref):
             x, y = np.nan_to_num(x, neginf=0.0), np.nan_to_num(y, neginf=0.0)
             assert np.all(np.abs(x - y) <= 2e-5 * np.maximum(1, np.abs(y).max()))
+
+
+# caps, rows and group sizes around the few-rows kernel's instances and its rule: one wave's block and
+# 16 waves' round (32, 512), 1024 and 2048 slots, 32 / 33, 64 / 65 and 128 rows
+FEW_ROWS = [
+    (1, 1, 1, 64, 32, [31]), (1, 16, 1, 128, 33, [32]), (2, 8, 1, 128, 512, [511, 480]),
+    (2, 8, 1, 64, 513, [512, 31]), (1, 6, 2, 128, 1024, [1023]), (2, 32, 2, 128, 1024, [1000, 0]),
+    (1, 4, 4, 64, 256, [255]), (1, 16, 1, 64, 256, [200]), (3, 7, 1, 128, 257, [256, 224, 1]),
+    (32, 4, 1, 128, 1024, [1023, 0] + list(range(400, 430))), (32, 7, 1, 128, 2048, [2047, 0] + list(range(600, 630))),
+    (33, 7, 1, 128, 2048, [2047, 0] + list(range(1600, 1631))), (64, 16, 1, 128, 1024, [1023, 0] + list(range(500, 562))),
+    (65, 8, 1, 64, 2048, [2047, 0] + list(range(1200, 1263))), (65, 4, 1, 128, 1024, [1023, 1] + list(range(300, 363))),
+    (127, 4, 1, 64, 1024, [1023, 1] + list(range(300, 425))), (43, 9, 3, 128, 300, [299, 1] + list(range(200, 241))),
+]
+
+
+@pytest.mark.parametrize("append", [True, False])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("shape", FEW_ROWS)
+def test_few_rows(shape, dtype, append):
+    """Launches of few rows: one launch in which each row is finished by its own workgroups, every
+    row against the oracle, with and without the step's append."""
+    B, Hq, Hkv, D, cap, lens = shape
+    run_case(B, Hq, Hkv, D, cap, lens, dtype, 0, append=append, seed=cap + Hq)
 
 
 @pytest.mark.parametrize("dtype,cap", [("f32", 32768), ("bf16", 32767), ("bf16", 32800), ("f32", 33000)])
