@@ -195,13 +195,14 @@ __device__ __forceinline__ SplitPlan split_plan(int n, int max_split) {
 // to A-row i is slot 8(i/4) + 4mt + i%4. These 8 slots are then, in order, the k index 8g..8g+7
 // of the alpha.V product, whose A operand (alpha of head c) is therefore the lane's own values.
 //
-// K loads. In the A layout every load instruction would read 64 bytes of each of 16 rows, so each
-// 128-byte line would be fetched by two instructions. Instead the two k-steps 2p and 2p + 1 of a
-// tile are loaded as two instructions that each read 8 whole lines: the first (kept in k[mt][2p])
-// reads A-rows 0..7, lanes c < 8 the k-step 2p part and lanes c >= 8 the k-step 2p + 1 part of
-// A-row c - 8; the second (k[mt][2p + 1]) reads A-rows 8..15 the same way (lanes c < 8: A-row
-// c + 8, step 2p; lanes c >= 8: A-row c, step 2p + 1). Rotating each 16-lane row by 8 lanes then
-// swaps the misplaced halves between the two registers (see fix_k).
+// K loads. A block's K rows are contiguous, and are loaded in lane order (KRaw): in the A layout
+// neighbouring lanes hold different rows, for which the CU's address unit takes about one cycle a
+// lane (55 cycles an instruction, measured on one CU) instead of 16. They reach the A layout through
+// the wave's LDS region, one tile of 16 slots at a time (turn_k), before the block's V rows are staged
+// there. Against loads in the A layout (whole lines a pair of instructions, set right by lane
+// rotations): batch 32, 28 / 4 heads, head_dim 128, cap 2048 26.6 -> 25.1 us a layer (113 MB), batch
+// 8, 32 / 8 heads, cap 4096 25.3 -> 25.0 us (108 MB), batch 64 with budgets of 512 to 8192 slots
+// 157.5 -> 154.0 us (719 MB), batch 8 in float32 30.0 -> 28.9 us (119 MB).
 // DV: the V dims (and output dims) the workgroup handles, D or a part of it (see attend_mfma_body).
 //
 // A float32 row is twice as long. Everything above counts bytes (a k-step is 64 bytes of each row),
@@ -210,9 +211,9 @@ __device__ __forceinline__ SplitPlan split_plan(int n, int max_split) {
 // The f32 MFMA (128 of them a block, 32 cycles each) take about a quarter of the time the block's
 // bytes take, so the sweep stays bound by memory. Measured against the vector-ALU sweep that these
 // caches had (one wave per 64 slots, a 64-lane reduction per slot and head): batch 8, 32 / 8 heads,
-// head_dim 128, cap 2048 float32 215 -> 30 us a layer (119 MB); batch 5, 32 / 8 heads, head_dim 64,
-// bfloat16 at cap 1500 (no multiple of 32) 134 -> 17 us; batch 1, 4 / 4 heads, head_dim 64, cap 256
-// float32 49 -> 18 us.
+// head_dim 128, cap 2048 float32 215 -> 29 us a layer (119 MB); batch 5, 32 / 8 heads, head_dim 64,
+// bfloat16 at cap 1500 (no multiple of 32) 134 -> 16 us; batch 1, 4 / 4 heads, head_dim 64, cap 256
+// float32 49 -> 14 us (all but the first now bound by their launches).
 template <typename T, int D, int DV = D>
 struct Geo {
   static constexpr bool F32 = sizeof(T) == 4;
@@ -228,18 +229,21 @@ struct Geo {
   }
 };
 
+// A block's K rows in memory order: lane l of load j holds the 16 bytes at 1024 j + 16 l.
+template <typename T, int D>
+struct KRaw {
+  static constexpr int RB = D * (int)sizeof(T), NK = Geo<T, D>::BS * RB / 1024;
+  uint4 x[NK];
+};
+// A block's V rows, 16 bytes per lane (see load_v).
 template <typename T, int D, int DV = D>
 struct Block {
-  using G = Geo<T, D, DV>;
-  uint4 k[G::MT][G::NS];
-  uint4 v[G::NV];  // V rows, 16 bytes per lane (see load_v)
+  uint4 v[Geo<T, D, DV>::NV];
 };
 
 struct RowCtx {
-  const char* kbase;  // lane's K address at slot 0: A-row (c mod 8) of tile 0, the 16 bytes at 16g
-                      // or 64 + 16g (c < 8 or not) of k-steps 0 and 1
   const char* vbase;  // lane's V address at slot 0 (see load_v)
-  int krow, vrow;     // the slots of a block that kbase and vbase stand for
+  int vrow;           // the slot of a block that vbase stands for
   const int32_t* posb;
   int L, app, cap, n_eff;
   int jsuf;  // first slot of the recent suffix within the split (see attend_mfma_body)
@@ -250,9 +254,7 @@ struct RowCtx {
   const uint4* snew;
 };
 
-// Block loads, in two halves so a pipelined wave can issue the next block's V rows as soon as the
-// current ones are in LDS, before its q.K^T. K: see "K loads" (base folded in kbase). V, 16 bytes
-// per lane (base folded in vbase):
+// V loads, 16 bytes per lane (base folded in vbase):
 //   bfloat16: DV / 8 lanes per row, so each load instruction reads 512 / DV consecutive rows of the
 //             workgroup's DV dims in lane order (1 KB): lane l of instruction i holds row
 //             blk + i (512 / DV) + l / (DV / 8) at dims 8 (l % (DV / 8)).
@@ -291,34 +293,15 @@ __device__ __forceinline__ void load_v(Block<T, D, DV>& B, const RowCtx& r, int 
   }
 }
 
-template <typename T, int D, bool NT, bool RC, int DV>
-__device__ __forceinline__ void load_k(Block<T, D, DV>& B, const RowCtx& r, int blk) {
-  using G = Geo<T, D, DV>;
-  constexpr int RB = D * (int)sizeof(T);
-  if (!RC || blk + G::BS <= r.cap) {
-    const char* kp = r.kbase + (size_t)blk * RB;
+// K loads of the block at slot blk of the row that starts at `row`; last: the byte offset of the row's
+// last 16 bytes (RC: dead slots past cap are clamped to it).
+template <typename T, int D, bool NT, bool RC>
+__device__ __forceinline__ void load_kraw(KRaw<T, D>& K, const char* row, int blk, int lane,
+                                          unsigned last) {
+  const unsigned off = (unsigned)blk * KRaw<T, D>::RB + 16 * lane;
 #pragma unroll
-    for (int mt = 0; mt < G::MT; ++mt) {
-#pragma unroll
-      for (int kk = 0; kk < G::NS; ++kk)  // k-step pair kk / 2; kk odd: A-rows 8..15
-        B.k[mt][kk] = ld_stream16<NT>(kp + G::slot(8 * (kk & 1), mt) * RB + 128 * (kk >> 1));
-    }
-  } else {
-#pragma unroll
-    for (int mt = 0; mt < G::MT; ++mt) {
-#pragma unroll
-      for (int kk = 0; kk < G::NS; ++kk) {
-        const int row = min(blk + r.krow + G::slot(8 * (kk & 1), mt), r.cap - 1) - r.krow;
-        B.k[mt][kk] = ld_stream16<NT>(r.kbase + (ptrdiff_t)row * RB + 128 * (kk >> 1));
-      }
-    }
-  }
-}
-
-template <typename T, int D, bool NT, bool RC, int DV>
-__device__ __forceinline__ void load_block(Block<T, D, DV>& B, const RowCtx& r, int blk) {
-  load_v<T, D, NT, RC, DV>(B, r, blk);
-  load_k<T, D, NT, RC, DV>(B, r, blk);
+  for (int j = 0; j < KRaw<T, D>::NK; ++j)
+    K.x[j] = ld_stream16<NT>(row + (RC ? min(off + 1024 * j, last) : off + 1024 * j));
 }
 
 struct Online {
@@ -395,21 +378,33 @@ __device__ __forceinline__ void patch_v(Block<float, D, DV>& B, const RowCtx& r,
   }
 }
 
-// Puts the K registers of one k-step pair into the A layout (see "K loads"): lanes 8..15 of every
-// 16-lane row take the first register from the second one's lanes 0..7, and lanes 0..7 take the
-// second register from the first one's lanes 8..15 (a rotation of the row by 8 lanes).
-__device__ __forceinline__ void fix_k(uint4& x, uint4& y) {
-  constexpr int kRowRor8 = 0x128;  // DPP row_ror:8
-  const uint4 x0 = x, y0 = y;
-  const unsigned* xs = (const unsigned*)&x0;
-  const unsigned* ys = (const unsigned*)&y0;
-  unsigned* xd = (unsigned*)&x;
-  unsigned* yd = (unsigned*)&y;
+// LDS tile of 16 K rows, row i = A-row i, padded so that 16 rows' pieces fall into different banks.
+template <typename T, int D> constexpr int ktile_stride() { return D * (int)sizeof(T) + 16; }
+// Tile mt of the block into LDS (row-major) and out again in the A layout. A load of four slots or
+// fewer lies in one tile: MT == 2 deals the slots to the tiles four at a time.
+template <typename T, int D>
+__device__ __forceinline__ void turn_k(const KRaw<T, D>& K, const RowCtx& r, int blk, int lane, int mt,
+                                       char* kt, uint4* kr) {
+  using Gm = Geo<T, D>;
+  constexpr int RB = KRaw<T, D>::RB, KS = ktile_stride<T, D>(), LPR = RB / 16;
+  const int g = lane >> 4, c = lane & 15;
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    xd[e] = (unsigned)__builtin_amdgcn_update_dpp((int)xs[e], (int)ys[e], kRowRor8, 0xf, 0xc, false);
-    yd[e] = (unsigned)__builtin_amdgcn_update_dpp((int)ys[e], (int)xs[e], kRowRor8, 0xf, 0x3, false);
+  for (int j = 0; j < KRaw<T, D>::NK; ++j) {
+    const int s = (64 * j + lane) / LPR;  // slot of the block
+    if (Gm::MT == 1 || RB >= 256) {
+      if (Gm::MT == 2 && ((64 * j / LPR) >> 2 & 1) != mt) continue;
+      const int i = Gm::MT == 2 ? 4 * (s >> 3) + (s & 3) : s;
+      *(uint4*)(kt + i * KS + 16 * (lane % LPR)) = K.x[j];
+    } else if (((s >> 2) & 1) == mt) {  // a load holds eight slots, four of each tile
+      *(uint4*)(kt + (4 * (s >> 3) + (s & 3)) * KS + 16 * (lane % LPR)) = K.x[j];
+    }
   }
+  // The appended row replaces the cache's slot (the wave's LDS writes land in order).
+  const int sub = r.lsub - blk;
+  if (sub >= 0 && sub < Gm::BS && (Gm::MT == 1 || ((sub >> 2) & 1) == mt) && lane < Gm::PPR)
+    *(uint4*)(kt + (Gm::MT == 2 ? 4 * (sub >> 3) + (sub & 3) : sub) * KS + 16 * lane) = r.snew[lane];
+#pragma unroll
+  for (int kk = 0; kk < Gm::NS; ++kk) kr[kk] = *(const uint4*)(kt + c * KS + 64 * kk + 16 * g);
 }
 
 // q as the B operand of q.K^T: lane (g, c) holds head c, the 16 bytes at 16 g of every k-step.
@@ -468,27 +463,14 @@ __device__ __forceinline__ f32x4_t qk_tile(const uint4* kr, const QFrag<T, D>& q
   return S;
 }
 
-template <typename T, int D, int DV>
-__device__ __forceinline__ void stage_qk(const Block<T, D, DV>& B, const RowCtx& r, int blk, int lane,
-                                         const QFrag<T, D>& qf, f32x4_t* S,
-                                         unsigned long long& suf) {
-  using Gm = Geo<T, D, DV>;
-  constexpr int NS = Gm::NS, BS = Gm::BS;
-  const int g = lane >> 4, c = lane & 15;
-  suf = suffix_bits<BS>(r, blk, lane);
-  // q.K^T on the matrix cores: lane holds slots blk + slot(4g + v, mt) of head c.
+// q.K^T of a block: lane holds slots blk + slot(4g + v, mt) of head c. kt: the wave's LDS region.
+template <typename T, int D>
+__device__ __forceinline__ void block_qk(const KRaw<T, D>& K, const RowCtx& r, int blk, int lane,
+                                         char* kt, const QFrag<T, D>& qf, f32x4_t* S) {
 #pragma unroll
-  for (int mt = 0; mt < Gm::MT; ++mt) {
-    uint4 kr[NS];
-#pragma unroll
-    for (int kk = 0; kk < NS; ++kk) kr[kk] = B.k[mt][kk];
-#pragma unroll
-    for (int p = 0; p < NS / 2; ++p) fix_k(kr[2 * p], kr[2 * p + 1]);
-    // The appended row's K in the lanes of its A-row.
-    if (r.lsub >= blk && r.lsub < blk + BS && r.lsub - blk == Gm::slot(c, mt)) {
-#pragma unroll
-      for (int kk = 0; kk < NS; ++kk) kr[kk] = r.snew[4 * kk + g];
-    }
+  for (int mt = 0; mt < Geo<T, D>::MT; ++mt) {
+    uint4 kr[Geo<T, D>::NS];
+    turn_k<T, D>(K, r, blk, lane, mt, kt, kr);
     S[mt] = qk_tile<T, D>(kr, qf);
   }
 }
@@ -618,12 +600,13 @@ __device__ __forceinline__ void finish_block(const f32x4_t* S, unsigned long lon
   }
 }
 
-// Bytes of a wave's LDS region: its V tile (bfloat16), and after the sweep its output numerators
-// ([16 heads][DV] float32).
-template <typename T, int DV>
+// Bytes of a wave's LDS region: its tile of K rows, then its V tile (bfloat16), and after the sweep
+// its output numerators ([16 heads][DV] float32).
+template <typename T, int D, int DV>
 constexpr int wave_lds_bytes() {
-  return sizeof(T) == 2 && 32 * vtile_stride<DV>() * 2 > 16 * DV * 4 ? 32 * vtile_stride<DV>() * 2
-                                                                     : 16 * DV * 4;
+  constexpr int v = sizeof(T) == 2 ? 32 * vtile_stride<DV>() * 2 : 0, k = 16 * ktile_stride<T, D>(),
+                o = 16 * DV * 4, vk = v > k ? v : k;
+  return vk > o ? vk : o;
 }
 // The wave's numerators into its LDS region (its last alpha.V has read the V tile).
 template <typename T, int DV>
@@ -833,7 +816,7 @@ __device__ __forceinline__ void single_split_epilogue(const AttendArgs& a, const
                                                       float (*sm_s)[16], const RowInfo& r,
                                                       int g, int c, bool hdr_ok,
                                                       const AccSlots<MS, NW>& old) {
-  constexpr int WB = wave_lds_bytes<T, DV>();
+  constexpr int WB = wave_lds_bytes<T, D, DV>();
   constexpr int NU = AccSlots<MS, NW>::NU;
   const int tid = threadIdx.x, G = a.G, GDV = G * DV;
   float* acc = a.acc + r.bk * a.cap;
@@ -914,7 +897,7 @@ __device__ __forceinline__ void exchange_epilogue(const AttendArgs& a, const f32
                                                   float (*sm_s)[16], const RowInfo& r, int g,
                                                   int c, bool hdr_ok, unsigned long long rw_old,
                                                   unsigned long long rw_chk) {
-  constexpr int NW = kWaves, WB = wave_lds_bytes<uint16_t, D>();
+  constexpr int NW = kWaves, WB = wave_lds_bytes<uint16_t, D, D>();
   constexpr int kStIter = (NSB * SG * 3 + 255) / 256;           // statistics words of a row
   constexpr int kPoIter = (SG * D + kMaxMfmaSplits + 255) / 256; // numerator words of a slice
   static_assert((size_t)kPoIter * 256 * 4 <= (size_t)NW * WB,
@@ -1281,7 +1264,7 @@ __device__ __forceinline__ void merge_form_epilogue(const AttendArgs& a, const f
                                                     float (*sm_m)[16], float (*sm_l)[16],
                                                     float (*sm_s)[16], const RowInfo& r, int wave,
                                                     int lane, int g, int c, int nb) {
-  constexpr int NW = kWaves, WB = wave_lds_bytes<T, D>(), BS = Geo<T, D>::BS;
+  constexpr int NW = kWaves, WB = wave_lds_bytes<T, D, D>(), BS = Geo<T, D>::BS;
   const int G = a.G;
   // Each wave, as soon as its own loop is done, puts its output numerators into its own LDS region
   // and copies its blocks' logits from the LDS copy to the stash, 16 B per lane (head
@@ -1374,7 +1357,11 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
   } else {
     hkv = blockIdx.x; b = blockIdx.y; split = blockIdx.z;
   }
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  // Uniform to the compiler in the long single splits only: in the others it then keeps epilogue
+  // addresses in registers through the sweep (254 instead of 214, spills in float32).
+  const int wave = MS > kMaxSplitSlots ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6)
+                                       : (int)(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
   const int g = lane >> 4, c = lane & 15;
   const int G = a.G;
   const size_t bk = (size_t)b * a.Hkv + hkv;
@@ -1382,8 +1369,7 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
   const char* Kb = (const char*)a.k + bk * cap * (D * ES);
   const char* Vb = (const char*)a.v + bk * cap * (D * ES);
   RowCtx rc;
-  rc.krow = Gm::slot(c & 7, 0);
-  rc.kbase = Kb + rc.krow * (D * ES) + 16 * (c < 8 ? g : 4 + g);
+  const unsigned klast = (unsigned)cap * (D * ES) - 16;
   rc.vrow = Gm::F32 ? Gm::slot(4 * g, 0) : lane / Gm::VPR;
   rc.vbase = Vb + rc.vrow * (D * ES) + dh * DV * ES + 16 * (Gm::F32 ? c : lane % Gm::VPR);
   rc.vp0 = dh * Gm::VPR;
@@ -1402,9 +1388,13 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
     for (int k = 0; k < kPosPer; ++k) pv[k] = rc.posb[min(lo + (int)threadIdx.x + 64 * NW * k, cap - 1)];
   };
   if (split == 0) load_pos(0);
+  KRaw<T, D> K;
   Block<T, D, DV> A;
   const bool spec = split == 0 && BS * wave < cap;
-  if (spec) load_block<T, D, NT, RC, DV>(A, rc, BS * wave);
+  if (spec) {
+    load_kraw<T, D, NT, RC>(K, Kb, BS * wave, lane, klast);
+    load_v<T, D, NT, RC, DV>(A, rc, BS * wave);
+  }
   int L, app;
   const int n_eff = live_slots(a, b, &L, &app);
   if (n_eff == 0) {  // the merge launch writes the empty result, or split 0 of the one-launch form
@@ -1505,7 +1495,7 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
 #pragma unroll
   for (int rr = 0; rr < VE; ++rr) O[rr] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   // LDS: per-wave V tiles during the sweep, then the wave partials or the polled words.
-  constexpr int WB = wave_lds_bytes<T, DV>();
+  constexpr int WB = wave_lds_bytes<T, D, DV>();
   __shared__ __attribute__((aligned(16))) char smem[NW * WB];
   char* mine = smem + wave * WB;
   uint16_t* vt = (uint16_t*)mine;
@@ -1527,7 +1517,10 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
   __shared__ int s_hdr_ok;
   unsigned long long rw_chk = 0;
   if (nb > 0) {
-    if (!spec) load_block<T, D, NT, RC, DV>(A, rc, s_lo + BS * wave);
+    if (!spec) {
+      load_kraw<T, D, NT, RC>(K, Kb, s_lo + BS * wave, lane, klast);
+      load_v<T, D, NT, RC, DV>(A, rc, s_lo + BS * wave);
+    }
     if (CO && threadIdx.x == 0) {
       s_hdr_ok = hd0.x == kWsMagic && hd0.y == kWsVersion && (int)hd0.z == a.B &&
                  (int)hd0.w == a.Hq && (int)hd1.x == a.Hkv && (int)hd1.y == D &&
@@ -1537,27 +1530,27 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
     }
     for (int i = 0; i + 1 < nb; ++i) {
       const int blk = s_lo + BS * (wave + NW * i);
+      block_qk<T, D>(K, rc, blk, lane, mine, qf, S);
+      load_kraw<T, D, NT, RC>(K, Kb, blk + BS * NW, lane, klast);
+      suf = suffix_bits<BS>(rc, blk, lane);
       if constexpr (Gm::F32) {
         // V is read from its registers, so the next block's V rows are requested last.
         patch_v<D, DV>(A, rc, blk, g, c);
-        stage_qk<T, D, DV>(A, rc, blk, lane, qf, S, suf);
-        load_k<T, D, NT, RC, DV>(A, rc, blk + BS * NW);
         finish_block<T, D, DV>(S, suf, A, rc, blk, g, c, G, a.scale_log2, stash_row, vt, st, O);
         load_v<T, D, NT, RC, DV>(A, rc, blk + BS * NW);
       } else {
         stage_v<D, DV>(A, rc, blk, g, c, vt);
         load_v<T, D, NT, RC, DV>(A, rc, blk + BS * NW);
-        stage_qk<T, D, DV>(A, rc, blk, lane, qf, S, suf);
-        load_k<T, D, NT, RC, DV>(A, rc, blk + BS * NW);
         finish_block<T, D, DV>(S, suf, A, rc, blk, g, c, G, a.scale_log2, stash_row, vt, st, O);
       }
     }
     if (multi && threadIdx.x == 0 && (int)(s_rw_old & 0xffffu) != p_ns - 1)
       rw_chk = row_peek(a.rows + bk);
     const int blk = s_lo + BS * (wave + NW * (nb - 1));
+    block_qk<T, D>(K, rc, blk, lane, mine, qf, S);
+    suf = suffix_bits<BS>(rc, blk, lane);
     if constexpr (Gm::F32) patch_v<D, DV>(A, rc, blk, g, c);
     else stage_v<D, DV>(A, rc, blk, g, c, vt);
-    stage_qk<T, D, DV>(A, rc, blk, lane, qf, S, suf);
     finish_block<T, D, DV>(S, suf, A, rc, blk, g, c, G, a.scale_log2, stash_row, vt, st, O);
   }
 
@@ -1623,55 +1616,14 @@ void attend_mfma(AttendArgs a) {
 // loaded in lane order and turned through a wave-private LDS tile, 16 slots at a time. Nothing a
 // wave needs waits for something else: scores, queries, new rows, the header and then its first
 // block with its positions are requested before the row's length is known, and no barrier
-// precedes the sweep.
+// precedes the sweep. Two rows of 733 slots, bfloat16, head_dim 128: the block loads are out after 1.5
+// to 3.5 us, the sweep ends at 6.5, the row is merged at 7.2 and written at 8.
 // -------------------------------------------------------------------------------------------
-// A block's K rows in memory order: lane l of load j holds the 16 bytes at 1024 j + 16 l.
-template <typename T, int D>
-struct KRaw {
-  static constexpr int RB = D * (int)sizeof(T), NK = Geo<T, D>::BS * RB / 1024;
-  uint4 x[NK];
-};
-// last: byte offset of the row's last 16 bytes (dead slots past cap are clamped to it).
-template <typename T, int D>
-__device__ __forceinline__ void load_kraw(KRaw<T, D>& K, const char* row, int blk, int lane, unsigned last) {
-  const unsigned off = (unsigned)blk * KRaw<T, D>::RB + 16 * lane;
-#pragma unroll
-  for (int j = 0; j < KRaw<T, D>::NK; ++j) K.x[j] = ld_stream16<false>(row + min(off + 1024 * j, last));
-}
-// LDS tile of 16 K rows, row i = A-row i, padded so that 16 rows' pieces fall into different banks.
-template <typename T, int D> constexpr int ktile_stride() { return D * (int)sizeof(T) + 16; }
-// Tile mt of the block into LDS (row-major) and out again in the A layout. A load of four slots or
-// fewer lies in one tile: MT == 2 deals the slots to the tiles four at a time.
-template <typename T, int D>
-__device__ __forceinline__ void turn_k(const KRaw<T, D>& K, const RowCtx& r, int blk, int lane, int mt,
-                                       char* kt, uint4* kr) {
-  using Gm = Geo<T, D>;
-  constexpr int RB = KRaw<T, D>::RB, KS = ktile_stride<T, D>(), LPR = RB / 16;
-  const int g = lane >> 4, c = lane & 15;
-#pragma unroll
-  for (int j = 0; j < KRaw<T, D>::NK; ++j) {
-    const int s = (64 * j + lane) / LPR;  // slot of the block
-    if (Gm::MT == 1 || RB >= 256) {
-      if (Gm::MT == 2 && ((64 * j / LPR) >> 2 & 1) != mt) continue;
-      const int i = Gm::MT == 2 ? 4 * (s >> 3) + (s & 3) : s;
-      *(uint4*)(kt + i * KS + 16 * (lane % LPR)) = K.x[j];
-    } else if (((s >> 2) & 1) == mt) {  // a load holds eight slots, four of each tile
-      *(uint4*)(kt + (4 * (s >> 3) + (s & 3)) * KS + 16 * (lane % LPR)) = K.x[j];
-    }
-  }
-  // The appended row replaces the cache's slot (the wave's LDS writes land in order).
-  const int sub = r.lsub - blk;
-  if (sub >= 0 && sub < Gm::BS && (Gm::MT == 1 || ((sub >> 2) & 1) == mt) && lane < Gm::PPR)
-    *(uint4*)(kt + (Gm::MT == 2 ? 4 * (sub >> 3) + (sub & 3) : sub) * KS + 16 * lane) = r.snew[lane];
-#pragma unroll
-  for (int kk = 0; kk < Gm::NS; ++kk) kr[kk] = *(const uint4*)(kt + c * KS + 64 * kk + 16 * g);
-}
-
 template <typename T, int D, int SG, int MS, int NW, int DS>
 __global__ __launch_bounds__(64 * NW) void attend_few(AttendArgs a) {
   constexpr int DV = D / DS, VE = DV / 16;
   using Gm = Geo<T, D, DV>;
-  constexpr int BS = Gm::BS, ES = (int)sizeof(T), WB = wave_lds_bytes<T, DV>();
+  constexpr int BS = Gm::BS, ES = (int)sizeof(T), WB = wave_lds_bytes<T, D, DV>();
   constexpr int NJ = MS / (64 * NW);  // slots per thread: tid + 64 NW k
   static_assert(NJ >= 1 && NW <= 16 && 64 % DS == 0, "slots in whole waves");
   // The DS parts of row r are workgroups 8 DS (r / 8) + r % 8 + 8 dh: on one XCD.
@@ -1724,9 +1676,9 @@ __global__ __launch_bounds__(64 * NW) void attend_few(AttendArgs a) {
   KRaw<T, D> K;
   Block<T, D, DV> A;  // V
   int ps = 0;         // positions of the block's slots
-  if (BS * wave < cap) {
+  {
     ps = rc.posb[min(BS * wave + (lane & (BS - 1)), cap - 1)];
-    load_kraw<T, D>(K, krow, BS * wave, lane, klast);
+    load_kraw<T, D, false, true>(K, krow, BS * wave, lane, klast);
     load_v<T, D, false, true, DV>(A, rc, BS * wave);
   }
   const int thr = sat_sub(a.t[b], a.suffix_w[b]);
@@ -1766,8 +1718,6 @@ __global__ __launch_bounds__(64 * NW) void attend_few(AttendArgs a) {
   __shared__ __attribute__((aligned(16))) char smem[NW * WB];
   char* mine = smem + wave * WB;
   uint16_t* vt = (uint16_t*)mine;
-  __shared__ __attribute__((aligned(16))) char ktile[NW * 16 * ktile_stride<T, D>()];
-  char* kt = ktile + wave * 16 * ktile_stride<T, D>();
   StashRow sr;
   sr.use_lds = true;
   sr.lds = (lds_float*)slog + (c < G ? c : 0) * MS;
@@ -1780,18 +1730,13 @@ __global__ __launch_bounds__(64 * NW) void attend_few(AttendArgs a) {
   for (int blk = BS * wave; blk < n; blk += BS * NW) {
     const int next = blk + BS * NW;
     f32x4_t S[Gm::MT];
-#pragma unroll
-    for (int mt = 0; mt < Gm::MT; ++mt) {
-      uint4 kr[Gm::NS];
-      turn_k<T, D>(K, rc, blk, lane, mt, kt, kr);
-      S[mt] = qk_tile<T, D>(kr, qf);
-    }
+    block_qk<T, D>(K, rc, blk, lane, mine, qf, S);
     const int slot = blk + (lane & (BS - 1));
     const unsigned long long suf =
         __ballot(lane < BS && slot < n && (slot == rc.lsub ? t_in : ps > thr));
     if (next < n) {
       ps = rc.posb[min(next + (lane & (BS - 1)), cap - 1)];
-      load_kraw<T, D>(K, krow, next, lane, klast);
+      load_kraw<T, D, false, true>(K, krow, next, lane, klast);
     }
     if constexpr (Gm::F32) patch_v<D, DV>(A, rc, blk, g, c);
     else {
