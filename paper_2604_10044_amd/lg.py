@@ -115,18 +115,30 @@ def _check(status: int, what: str):
                                        _lib.lg_status_string(status).decode()))
 
 
+# An attention call passes a dozen tensors, and on the small layers the marshalling is as long as the
+# kernel: the common cases come first, and the current stream is read as its handle (no Stream object).
 def _ptr(x) -> Optional[int]:
     if x is None:
         return None
-    if isinstance(x, int):
-        return x
-    return x.data_ptr()
+    try:
+        return x.data_ptr()
+    except AttributeError:
+        if isinstance(x, int):
+            return x
+        raise
 
 
 def _stream(stream) -> Optional[int]:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        return _current_raw_stream(torch.cuda.current_device())
     return stream if isinstance(stream, int) else stream.cuda_stream
+
+
+def _stream_handle(device: int) -> int:
+    return torch.cuda.current_stream(device).cuda_stream
+
+
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", _stream_handle)
 
 
 def lg_guard_params_default() -> GuardParams:
