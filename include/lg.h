@@ -248,6 +248,9 @@ lg_status lg_decode_attend_workspace_init(const lg_layer_cache* layer, void* wor
  *     groups of at most 8 query heads, else 1024), one launch in which every row is finished by
  *     its own workgroup (two workgroups per row at up to 128 rows of head_dim 128, each forming
  *     half of the output dims), without any exchange between workgroups;
+ *   - with few rows of a short cache (few_rows() in lg_internal.h: at batch 1, a cap of at most 1024
+ *     slots in bfloat16 and 256 in float32), one launch in which 1, 2 or 4 workgroups per row each
+ *     read the whole K row and form part of the output dims;
  *   - otherwise a sweep launch (the live slots of each row cut into splits of at most 1024 slots,
  *     one workgroup each, writing split partials and the logits to the workspace) and a merging
  *     launch.

@@ -15,11 +15,13 @@
 //               below).
 //   merge       (the automatic choice otherwise) each split writes its partial and its logits to
 //               memory and attend_combine_mfma merges them in a second launch.
+//   few rows    (the automatic choice instead of the merge form where few_rows() says so) one
+//               launch, attend_few: each row finished by 1, 2 or 4 workgroups without an exchange.
 //   portable    (caps beyond 32768; test hook) attend_valu + attend_combine.
-// The exchange between splits is for bfloat16 caches whose cap is a multiple of 32; the other two
+// The exchange between splits is for bfloat16 caches whose cap is a multiple of 32; the other
 // MFMA forms take both types and any cap up to 32768.
-// The sweep runs both products of the GQA group on the matrix cores; K rows load straight into the
-// A operand of q.K^T (16 B per lane).
+// The sweep runs both products of the GQA group on the matrix cores; K rows are loaded in memory
+// order and turned into the A operand of q.K^T through LDS.
 //   bfloat16: 16x16x32 bf16 MFMA. V rows are loaded coalesced, staged row-major in a wave-private
 //             LDS tile and read back with gfx950's transposing LDS load (ds_read_b64_tr_b16) as the
 //             B operand of alpha.V; alpha enters that product as a pair of bf16 terms (hi + lo,

@@ -29,8 +29,9 @@ __host__ __device__ inline size_t align_up(size_t x, size_t a) { return (x + a -
 // ------------------------------------------------------------------------------------------
 // Kernel forms of lg_decode_attend. The automatic choice for caps up to 32768 (both types):
 // kFormOneLaunch when every row is a single split (no exchange; see attend_plan), kFormMerge
-// otherwise (the sweep and a merging launch: at 1 to 64 rows and in the ragged batch it measured
-// faster than the one-launch form's exchange); kFormPortable for longer caches, whose rows would
+// otherwise (the sweep and a merging launch, in the ragged batch faster than the one-launch form's
+// exchange; or, for few rows of a short cache, attend_few, which the workspace header does not tell
+// apart: see few_rows); kFormPortable for longer caches, whose rows would
 // be more than kMaxMfmaSplits splits. The one-launch form with several splits per row (bfloat16,
 // cap a multiple of 32) is reachable through the test hook, which takes the MFMA forms for those
 // caches only.
