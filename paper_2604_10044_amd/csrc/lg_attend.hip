@@ -25,7 +25,7 @@
 //   bfloat16: 16x16x32 bf16 MFMA. V rows are loaded coalesced, staged row-major in a wave-private
 //             LDS tile and read back with gfx950's transposing LDS load (ds_read_b64_tr_b16) as the
 //             B operand of alpha.V; alpha enters that product as a pair of bf16 terms (hi + lo,
-//             within 2^-16).
+//             within 2^-16), where cap is no multiple of 32 as three (alpha exactly).
 //   float32:  16x16x4 f32 MFMA. V rows load straight into the B operand: lane (g, c) needs rows
 //             4 g + v of 4 consecutive dims, which are whole 256-byte stretches of a row, and alpha
 //             enters as the lane's own float32 values.
@@ -489,9 +489,18 @@ struct StashRow {
   bool use_lds;    // fixed per kernel instantiation
 };
 
+// The largest bfloat16 value below x, as a float's bits (x >= 0; 0 stays 0, NaN stays NaN).
+__device__ __forceinline__ uint32_t bf16_below(float x) {
+  return __builtin_elementwise_sub_sat(__float_as_uint(x), 1u) & 0xffff0000u;
+}
+
 // Second half: online softmax, logit stash, suffix mass, and alpha.V (DV dims), V from the LDS tile
 // (bfloat16) or from the block's registers (float32).
-template <typename T, int D, int DV>
+// X3 (bfloat16): alpha enters alpha.V as a whole float32, in three terms, and an infinite V value of a
+// slot with alpha > 0 gives an infinite output; without X3 in two terms, of which the second may be 0.
+// The third product costs nothing that shows: batch 5, 32 / 8 heads, head_dim 64, cap 1500 14.3 us a
+// layer with two and with three.
+template <typename T, int D, int DV, bool X3>
 __device__ __forceinline__ void finish_block(const f32x4_t* S, unsigned long long suf,
                                              const Block<T, D, DV>& B, const RowCtx& r, int blk,
                                              int g, int c, int G, float scale_log2,
@@ -566,20 +575,27 @@ __device__ __forceinline__ void finish_block(const f32x4_t* S, unsigned long lon
     }
   } else {
     constexpr int NB = DV / 16, RS = vtile_stride<DV>();
-    // alpha of head c for slots 8g..8g+7, in k order, as two bf16 A operands: hi = alpha truncated
-    // to bf16, lo = the remainder truncated to bf16, so hi + lo is within 2^-16 of alpha.
-    uint32_t hb[8], lb[8];
+    // alpha of head c for slots 8g..8g+7, in k order, as bf16 A operands. Two terms: hi = alpha
+    // truncated to bf16, lo = the remainder truncated to bf16, so hi + lo is within 2^-16 of alpha.
+    // Three: hi = the largest bf16 below alpha, mid = the largest below the remainder (at most 17
+    // bits), lo = what is left (at most 9 bits, a power of two if 9): alpha exactly, and no term of a
+    // positive alpha is 0.
+    uint32_t hb[8], mb[8], lb[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const float x = p[e >> 2][e & 3];
-      const uint32_t xb = __float_as_uint(x) & 0xffff0000u;
+      const uint32_t xb = X3 ? bf16_below(x) : __float_as_uint(x) & 0xffff0000u;
+      const float y = x - __uint_as_float(xb);
+      const uint32_t yb = X3 ? bf16_below(y) : __float_as_uint(y);
       hb[e] = xb >> 16;
-      lb[e] = __float_as_uint(x - __uint_as_float(xb)) >> 16;
+      mb[e] = yb >> 16;
+      lb[e] = X3 ? __float_as_uint(y - __uint_as_float(yb)) >> 16 : 0u;
     }
-    uint4 ph, pl;
-    ph.x = hb[0] | (hb[1] << 16); ph.y = hb[2] | (hb[3] << 16); ph.z = hb[4] | (hb[5] << 16); ph.w = hb[6] | (hb[7] << 16);
-    pl.x = lb[0] | (lb[1] << 16); pl.y = lb[2] | (lb[3] << 16); pl.z = lb[4] | (lb[5] << 16); pl.w = lb[6] | (lb[7] << 16);
-    const bf16x8_t Ahi = as_bf16x8(ph), Alo = as_bf16x8(pl);
+    auto pack = [](const uint32_t* x) {
+      return as_bf16x8(make_uint4(x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16),
+                                  x[6] | (x[7] << 16)));
+    };
+    const bf16x8_t Ahi = pack(hb), Amid = pack(mb), Alo = pack(lb);
 #pragma unroll
     for (int v = 0; v < 4; ++v) al[v] = __shfl(alpha, 4 * g + v, 64);
     // alpha.V: B[k][j] = V[slot 8g + k'][16nb + j] read from LDS with the transposing load: source
@@ -597,7 +613,8 @@ __device__ __forceinline__ void finish_block(const f32x4_t* S, unsigned long lon
 #pragma unroll
       for (int v = 0; v < 4; ++v) O[nb][v] *= al[v];
       O[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ahi, Bv, O[nb], 0, 0, 0);
-      O[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Alo, Bv, O[nb], 0, 0, 0);
+      O[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Amid, Bv, O[nb], 0, 0, 0);
+      if constexpr (X3) O[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Alo, Bv, O[nb], 0, 0, 0);
     }
   }
 }
@@ -1538,12 +1555,12 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
       if constexpr (Gm::F32) {
         // V is read from its registers, so the next block's V rows are requested last.
         patch_v<D, DV>(A, rc, blk, g, c);
-        finish_block<T, D, DV>(S, suf, A, rc, blk, g, c, G, a.scale_log2, stash_row, vt, st, O);
+        finish_block<T, D, DV, RC>(S, suf, A, rc, blk, g, c, G, a.scale_log2, stash_row, vt, st, O);
         load_v<T, D, NT, RC, DV>(A, rc, blk + BS * NW);
       } else {
         stage_v<D, DV>(A, rc, blk, g, c, vt);
         load_v<T, D, NT, RC, DV>(A, rc, blk + BS * NW);
-        finish_block<T, D, DV>(S, suf, A, rc, blk, g, c, G, a.scale_log2, stash_row, vt, st, O);
+        finish_block<T, D, DV, RC>(S, suf, A, rc, blk, g, c, G, a.scale_log2, stash_row, vt, st, O);
       }
     }
     if (multi && threadIdx.x == 0 && (int)(s_rw_old & 0xffffu) != p_ns - 1)
@@ -1553,7 +1570,7 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
     suf = suffix_bits<BS>(rc, blk, lane);
     if constexpr (Gm::F32) patch_v<D, DV>(A, rc, blk, g, c);
     else stage_v<D, DV>(A, rc, blk, g, c, vt);
-    finish_block<T, D, DV>(S, suf, A, rc, blk, g, c, G, a.scale_log2, stash_row, vt, st, O);
+    finish_block<T, D, DV, RC>(S, suf, A, rc, blk, g, c, G, a.scale_log2, stash_row, vt, st, O);
   }
 
   // The wave's partial: head c's max in every lane, sum and suffix sum reduced over the row groups.
@@ -1621,7 +1638,7 @@ void attend_mfma(AttendArgs a) {
 // precedes the sweep. Two rows of 733 slots, bfloat16, head_dim 128: the block loads are out after 1.5
 // to 3.5 us, the sweep ends at 6.5, the row is merged at 7.2 and written at 8.
 // -------------------------------------------------------------------------------------------
-template <typename T, int D, int SG, int MS, int NW, int DS>
+template <typename T, int D, bool RC, int SG, int MS, int NW, int DS>
 __global__ __launch_bounds__(64 * NW) void attend_few(AttendArgs a) {
   constexpr int DV = D / DS, VE = DV / 16;
   using Gm = Geo<T, D, DV>;
@@ -1745,7 +1762,7 @@ __global__ __launch_bounds__(64 * NW) void attend_few(AttendArgs a) {
       stage_v<D, DV>(A, rc, blk, g, c, vt);
       if (next < n) load_v<T, D, false, true, DV>(A, rc, next);
     }
-    finish_block<T, D, DV>(S, suf, A, rc, blk, g, c, G, a.scale_log2, sr, vt, st, O);
+    finish_block<T, D, DV, RC>(S, suf, A, rc, blk, g, c, G, a.scale_log2, sr, vt, st, O);
     if (Gm::F32 && next < n) load_v<T, D, false, true, DV>(A, rc, next);
   }
   // The wave's partial; then the waves are merged by wave 0 (lane: head c, waves g, g + 4, ...).
@@ -2210,32 +2227,32 @@ hipError_t launch_mfma_form(AttendArgs a, hipStream_t st);
 // Few rows (the plan has cap <= few_max_slots, and <= 1024 in float32). 16 waves where the logits leave the LDS for it (bfloat16: the step of a 1.5B-shaped batch
 // of one 261 us with 16 waves, 271 with 8); a second block in flight per wave is slower (its loads
 // only queue in the CU's address unit, and delay the first block's: 8 waves 295 -> 308 us).
-template <typename T, int D, int SG, int MS>
+template <typename T, int D, bool RC, int SG, int MS>
 static hipError_t launch_few_ms(const AttendArgs& a, hipStream_t st) {
   constexpr int DS = few_dsplit(sizeof(T) == 4, D);
   constexpr int NW = SG * MS <= 8192 && sizeof(T) == 2 ? 16 : 8;
   const unsigned grid = (unsigned)((a.B * a.Hkv + 7) / 8) * 8 * DS;
-  hipLaunchKernelGGL((attend_few<T, D, SG, MS, NW, DS>), dim3(grid), dim3(64 * NW), 0, st, a);
+  hipLaunchKernelGGL((attend_few<T, D, RC, SG, MS, NW, DS>), dim3(grid), dim3(64 * NW), 0, st, a);
   return hipGetLastError();
 }
-template <typename T, int D, int SG>
+template <typename T, int D, bool RC, int SG>
 static hipError_t launch_few(const AttendArgs& a, hipStream_t st) {
   constexpr int most = few_max_slots(sizeof(T) == 4, SG);
   if constexpr (most <= 1024) {
-    if (a.cap <= most) return launch_few_ms<T, D, SG, most>(a, st);
+    if (a.cap <= most) return launch_few_ms<T, D, RC, SG, most>(a, st);
   } else {
-    if (a.cap <= 1024) return launch_few_ms<T, D, SG, 1024>(a, st);
-    if constexpr (sizeof(T) == 2) return launch_few_ms<T, D, SG, most>(a, st);
+    if (a.cap <= 1024) return launch_few_ms<T, D, RC, SG, 1024>(a, st);
+    if constexpr (sizeof(T) == 2) return launch_few_ms<T, D, RC, SG, most>(a, st);
   }
   return hipErrorInvalidValue;  // the plan never gives this
 }
 
 template <typename T, int D, bool RC>
 hipError_t launch_mfma_form(AttendArgs a, hipStream_t st) {
-  if (a.few && RC == (sizeof(T) == 4)) {
-    if (a.G <= 4) return launch_few<T, D, 4>(a, st);
-    if (a.G <= 8) return launch_few<T, D, 8>(a, st);
-    return launch_few<T, D, 16>(a, st);
+  if (a.few) {
+    if (a.G <= 4) return launch_few<T, D, RC, 4>(a, st);
+    if (a.G <= 8) return launch_few<T, D, RC, 8>(a, st);
+    return launch_few<T, D, RC, 16>(a, st);
   }
   const bool nt = stream_nt(a, D);
   if (a.form == kFormMerge)
@@ -2271,7 +2288,7 @@ static hipError_t launch_attend_d(AttendArgs a, lg_dtype dt, hipStream_t st) {
   if (a.form == kFormPortable)
     return dt == LG_BF16 ? launch_valu<uint16_t, D>(a, st) : launch_valu<float, D>(a, st);
   if (dt != LG_BF16) return launch_mfma_form<float, D, true>(a, st);
-  return a.cap % 32 == 0 || a.few ? launch_mfma_form<uint16_t, D, false>(a, st)
+  return a.cap % 32 == 0 ? launch_mfma_form<uint16_t, D, false>(a, st)
                          : launch_mfma_form<uint16_t, D, true>(a, st);
 }
 

@@ -401,6 +401,99 @@ def test_attend_without_conf(form):
     for a, b in zip(res[0], res[1]):
         assert torch.equal(a, b)
 
+# Layers of every automatic form whose caps are no multiple of 32: few rows, merge with short and long
+# splits, one split per row (by two workgroups, by one, up to 1024 slots)
+RAGGED_FORMS = [(2, 8, 2, 128, 333), (3, 4, 1, 64, 999), (2, 14, 2, 128, 2047), (70, 16, 1, 64, 1301),
+                (32, 28, 4, 128, 1501), (40, 28, 4, 128, 1501), (32, 64, 4, 64, 777)]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,cap", RAGGED_FORMS)
+def test_ragged_caps_infinite_values(B, Hq, Hkv, D, cap):
+    """An infinite V value of a live slot makes its output dim infinite in every head that gives the slot
+    any probability (it is no smaller than 2^-40 here), also where that is exactly a bfloat16 value:
+    the largest of a row is 1 before the normalisation. The portable pair gives the same."""
+    from paper_2604_10044_amd import lg
+    dev = torch.device("cuda")
+    g, K, V = _rand_layer(B, Hq, Hkv, D, cap, cap)
+    q = torch.randn(B, Hq, D, generator=g).to(torch.bfloat16).to(dev)
+    n = cap - 1
+    top = (q[:, ::Hq // Hkv].float()[:, :, None] * K[:, :, :n].float()).sum(-1).argmax(-1)  # [B][Hkv]
+    for b in range(B):
+        for h in range(Hkv):
+            V[b, h, top[b, h], 3] = float("inf")
+            V[b, h, n // 2, D - 1] = -float("inf")
+    pos = torch.arange(cap, dtype=torch.int32).repeat(B, 1).contiguous().to(dev)
+    lens = torch.full((B,), n, dtype=torch.int32, device=dev)
+    sw = torch.full((B,), 64, dtype=torch.int32, device=dev)
+    f32 = lambda: torch.zeros(B, Hq, device=dev)  # noqa: E731
+    for form in ("auto", "portable"):
+        acc, lse, sm = torch.zeros(B, Hkv, cap, device=dev), f32(), f32()
+        layer = lg.layer_cache(K, V, acc, Hq)
+        ws = make_ws(lg, layer, FORMS[form])
+        out = torch.zeros(B, Hq, D, dtype=torch.bfloat16, device=dev)
+        attend(lg, layer, q, None, None, out, pos, lens, lens, sw, lse, sm, None, ws, FORMS[form])
+        torch.cuda.synchronize()
+        assert torch.all(torch.isposinf(out[:, :, 3])) and torch.all(torch.isneginf(out[:, :, D - 1])), form
+        assert torch.all(torch.isfinite(out[:, :, 4:D - 1])), form
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,cap", RAGGED_FORMS)
+def test_ragged_caps_float32_alpha(B, Hq, Hkv, D, cap):
+    """alpha enters alpha.V as a float32 where cap is no multiple of 32. Slots alternate between two key
+    rows, so a row has two probabilities, 1 and p before the normalisation, and the V values -va and vb
+    of a dim are bfloat16 numbers with 2^-13 vb <= |p vb - va| <= 2^-12 vb: every output is a sum of
+    such differences. Errors relative to 2^-12 vb: the logits (at most 0.6 in base 2, so within 2^-24)
+    and exp2 move p by 2^-22, 2^-10; the float32 sums cancel pairwise, 2^-22 a pair whatever its sign,
+    2^-10; the bfloat16 result is within 2^-9. Together below 2^-7. alpha cut to 16 bits (the two
+    bfloat16 terms of the other caps; p is chosen for it) is off by 2^-5 and more."""
+    from paper_2604_10044_amd import lg
+    dev = torch.device("cuda")
+    rng = np.random.default_rng(cap)
+    n = (cap - 1) // 2 * 2
+    # q = (x, 0, ...), keys (1, 0, ...) and (0, ...): logits x / sqrt(D) and 0, p = exp(-x / sqrt(D)).
+    man = np.arange(128, 256) / 128.0
+    best = None
+    for x in _round_bf16(rng.uniform(0.05, 0.4, 400).astype(np.float32)) * np.float32(np.sqrt(D)):
+        x = float(_round_bf16(np.float32([x]))[0])
+        p = np.exp(-x / np.sqrt(D))
+        bits = int(np.float32(p).view(np.uint32))
+        cut = float(np.float32(p)) - float(np.uint32(bits & 0xffff0000).view(np.float32))
+        cut -= float((np.float32(cut).view(np.uint32) & np.uint32(0xffff0000)).view(np.float32))
+        if best is None or cut / p > best[0]:
+            best = (cut / p, x, p)
+    _, x, p = best
+    e = np.floor(np.log2(p))
+    va, vb = np.meshgrid(np.concatenate([man * 2.0 ** e, man * 2.0 ** (e + 1)]), man, indexing="ij")
+    res = np.abs(va - p * vb)
+    ok = np.argwhere((res <= 2.0 ** -12 * vb) & (res >= 2.0 ** -13 * vb))
+    assert len(ok) >= 2
+    pick = ok[rng.integers(0, len(ok), D)]
+    va, vb = va[pick[:, 0], pick[:, 1]], vb[pick[:, 0], pick[:, 1]]
+    K = np.zeros((cap, D), np.float32)
+    V = np.zeros((cap, D), np.float32)
+    K[0:n:2, 0] = 1.0
+    V[0:n:2], V[1:n:2] = -va, vb
+    tb = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.float32)).to(torch.bfloat16).to(dev)  # noqa: E731
+    Kd = tb(K).expand(B, Hkv, cap, D).contiguous()
+    Vd = tb(V).expand(B, Hkv, cap, D).contiguous()
+    # the even slots have logit x / sqrt(D) and weight 1, the odd ones p: out = sum(-va + p vb) / Z
+    q = np.zeros((B, Hq, D), np.float32)
+    q[:, :, 0] = x
+    qd = tb(q)
+    pos = torch.arange(cap, dtype=torch.int32).repeat(B, 1).contiguous().to(dev)
+    lens = torch.full((B,), n, dtype=torch.int32, device=dev)
+    want = (p * vb - va) / (1 + p)
+    f32 = lambda: torch.zeros(B, Hq, device=dev)  # noqa: E731
+    for form in ("auto", "portable"):
+        acc, lse, sm = torch.zeros(B, Hkv, cap, device=dev), f32(), f32()
+        layer = lg.layer_cache(Kd, Vd, acc, Hq)
+        ws = make_ws(lg, layer, FORMS[form])
+        out = torch.zeros(B, Hq, D, dtype=torch.bfloat16, device=dev)
+        attend(lg, layer, qd, None, None, out, pos, lens, lens, lens, lse, sm, None, ws, FORMS[form])
+        got = out.float().cpu().numpy()
+        err = np.abs(got - want) / (2.0 ** -12 * vb / (1 + p))
+        assert err.max() <= 2.0 ** -7, (form, err.max())
+
 
 def test_forms_agree():
     a = run_case(2, 28, 4, 128, 704, [500, 699], "bf16", FORMS["portable"], seed=21)
