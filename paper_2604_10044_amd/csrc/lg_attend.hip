@@ -306,9 +306,29 @@ __device__ __forceinline__ void load_kraw(KRaw<T, D>& K, const char* row, int bl
     K.x[j] = ld_stream16<NT>(row + (RC ? min(off + 1024 * j, last) : off + 1024 * j));
 }
 
+// Sums that end in a float32 result, over lanes, waves and splits: the softmax and suffix sums (Sum<RC>;
+// RC: float32 caches and ragged caps; attend_few: over the waves, and in
+// float32 caches) and the outputs (Outs<T>, float32
+// caches). What the layers ran before (the portable pair; 128-slot splits for few rows) adds slots in
+// order, so the newest slots, which outweigh the others in a locked head, are rounded a few times
+// only; in float32 the order of lanes, many waves and splits rounds them more often. Relative error
+// against 64 bits (four seeds), portable pair / all in float32 / these sums (and qk_tile's): float32,
+// head_dim 128, cap 2048, batch 8, 32 / 8 heads out 1.25e-7 / 1.50e-7 / 1.16e-7; batch 32, 28 / 4 heads
+// out 1.28e-7 / 1.57e-7 / 1.15e-7, suffix mass 8.4e-8 / 12.4e-8 / 6.2e-8; bfloat16, batch 2, 16 / 1
+// heads, head_dim 128, cap 1024, suffix mass 7.4e-8 (128-slot splits) / 12.7e-8 / 8.2e-8. They cost
+// 0.2 us of 8.5 in a layer of few rows, 0.4 of 28.8 and 1.5 of 47.4 in the two float32 layers.
+template <bool RC> using Sum = std::conditional_t<RC, double, float>;
+template <typename T> using Outs = std::conditional_t<sizeof(T) == 4, double, float>;
+
+template <typename S>
 struct Online {
-  float m, l, s;
+  float m;
+  S l, s;
 };
+
+// 1 / z from r = 1 / z in float32 (one Newton step where z is a double).
+__device__ __forceinline__ float recip(float, float r) { return r; }
+__device__ __forceinline__ double recip(double z, float r) { return fma((double)r, fma(-z, (double)r, 1.0), (double)r); }
 
 // Maximum over the four 16-lane row groups, in every lane: two register swaps between lanes (gfx950's
 // permlane swaps) where a shuffle is an LDS round trip.
@@ -320,13 +340,43 @@ __device__ __forceinline__ float row_groups_max(float x) {
   const u32x2_t t = __builtin_amdgcn_permlane32_swap(w, w, false, false);
   return fmaxf(__uint_as_float(t.x), __uint_as_float(t.y));
 }
-// Maximum or sum over the four neighbouring lanes 4k .. 4k + 3, in each of them.
-template <bool MAX>
-__device__ __forceinline__ float quad_all(float x) {
-  const float y = __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(x), 0xB1, 0xf, 0xf, true));
-  x = MAX ? fmaxf(x, y) : x + y;
-  const float z = __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(x), 0x4E, 0xf, 0xf, true));
-  return MAX ? fmaxf(x, z) : x + z;
+// Sum over the four row groups, in every lane: in double by the same swaps, in float by shuffles.
+__device__ __forceinline__ float row_groups_sum(float x) {
+  x += __shfl_xor(x, 16, 64);
+  return x + __shfl_xor(x, 32, 64);
+}
+__device__ __forceinline__ double row_groups_sum(double x) {
+  typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
+  auto join = [](unsigned lo, unsigned hi) {
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+  };
+  unsigned long long u = (unsigned long long)__double_as_longlong(x);
+  u32x2_t lo = __builtin_amdgcn_permlane16_swap((unsigned)u, (unsigned)u, false, false);
+  u32x2_t hi = __builtin_amdgcn_permlane16_swap((unsigned)(u >> 32), (unsigned)(u >> 32), false, false);
+  x = join(lo.x, hi.x) + join(lo.y, hi.y);
+  u = (unsigned long long)__double_as_longlong(x);
+  lo = __builtin_amdgcn_permlane32_swap((unsigned)u, (unsigned)u, false, false);
+  hi = __builtin_amdgcn_permlane32_swap((unsigned)(u >> 32), (unsigned)(u >> 32), false, false);
+  return join(lo.x, hi.x) + join(lo.y, hi.y);
+}
+// Maximum or sum over the four neighbouring lanes 4k .. 4k + 3, in each of them (quad_perm 1 0 3 2,
+// then 2 3 0 1).
+template <int CTRL> __device__ __forceinline__ float quad_perm(float x) {
+  return __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(x), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL> __device__ __forceinline__ double quad_perm(double x) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(x);
+  const unsigned lo = __builtin_amdgcn_mov_dpp((unsigned)u, CTRL, 0xf, 0xf, true);
+  const unsigned hi = __builtin_amdgcn_mov_dpp((unsigned)(u >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+__device__ __forceinline__ float quad_max(float x) {
+  x = fmaxf(x, quad_perm<0xB1>(x));
+  return fmaxf(x, quad_perm<0x4E>(x));
+}
+template <typename S> __device__ __forceinline__ S quad_sum(S x) {
+  x += quad_perm<0xB1>(x);
+  return x + quad_perm<0x4E>(x);
 }
 
 // 2^x by the hardware instruction: exp2f without its scaling of results below 2^-126, which are 0
@@ -422,14 +472,21 @@ __device__ __forceinline__ unsigned long long suffix_bits(const RowCtx& r, int b
   return __ballot(lane < BS && ps >= r.jsuf && ps < r.n_eff);
 }
 
-// q.K^T of one tile of 16 slots, K rows in the A layout.
-template <typename T, int D>
-__device__ __forceinline__ f32x4_t qk_tile(const uint4* kr, const QFrag<T, D>& qf) {
+// log2(e) / sqrt(D).
+template <int D> constexpr double scale_log2_d() {
+  static_assert(D == 64 || D == 128, "supported head_dims");
+  return 1.4426950408889634074 * (D == 64 ? 0.125 : 0.088388347648318440550);
+}
+
+// Logits (base 2) of one tile of 16 slots, K rows in the A layout.
+template <typename T, int D, bool RC>
+__device__ __forceinline__ f32x4_t qk_tile(const uint4* kr, const QFrag<T, D>& qf, float scale_log2) {
   constexpr int NS = Geo<T, D>::NS;
-  f32x4_t S = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  f32x4_t s;
   if constexpr (sizeof(T) == 4) {
-    // Eight partial dot products for every four k-steps, added as a tree: as close to the exact
-    // sum as a lane-wise reduction (one chain of D terms is not), and eight independent chains.
+    // Eight partial dot products for every four k-steps, eight independent chains; their sums of four
+    // are added in double.
+    double S[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int k0 = 0; k0 < NS; k0 += 4) {
       f32x4_t P[8];
@@ -452,28 +509,45 @@ __device__ __forceinline__ f32x4_t qk_tile(const uint4* kr, const QFrag<T, D>& q
       }
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const float t = ((P[0][v] + P[1][v]) + (P[2][v] + P[3][v])) +
-                        ((P[4][v] + P[5][v]) + (P[6][v] + P[7][v]));
-        S[v] = k0 == 0 ? t : S[v] + t;
+#pragma unroll
+        for (int e = 0; e < 8; e += 4)
+          S[v] += (double)((P[e][v] + P[e + 1][v]) + (P[e + 2][v] + P[e + 3][v]));
       }
     }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) s[v] = (float)(S[v] * scale_log2_d<D>());
+  } else if constexpr (RC) {
+    f32x4_t P[NS];
+#pragma unroll
+    for (int kk = 0; kk < NS; ++kk)
+      P[kk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kr[kk]), as_bf16x8(qf.q[kk]),
+                                                      f32x4_t{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      double S = P[0][v] + P[1][v];
+      if constexpr (NS == 4) S += (double)(P[2][v] + P[3][v]);
+      s[v] = (float)(S * scale_log2_d<D>());
+    }
   } else {
+    f32x4_t S = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int kk = 0; kk < NS; ++kk)
       S = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kr[kk]), as_bf16x8(qf.q[kk]), S, 0, 0, 0);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) s[v] = S[v] * scale_log2;
   }
-  return S;
+  return s;
 }
 
-// q.K^T of a block: lane holds slots blk + slot(4g + v, mt) of head c. kt: the wave's LDS region.
-template <typename T, int D>
+// Logits of a block: lane holds slots blk + slot(4g + v, mt) of head c. kt: the wave's LDS region.
+template <typename T, int D, bool RC>
 __device__ __forceinline__ void block_qk(const KRaw<T, D>& K, const RowCtx& r, int blk, int lane,
-                                         char* kt, const QFrag<T, D>& qf, f32x4_t* S) {
+                                         char* kt, const QFrag<T, D>& qf, float scale_log2, f32x4_t* S) {
 #pragma unroll
   for (int mt = 0; mt < Geo<T, D>::MT; ++mt) {
     uint4 kr[Geo<T, D>::NS];
     turn_k<T, D>(K, r, blk, lane, mt, kt, kr);
-    S[mt] = qk_tile<T, D>(kr, qf);
+    S[mt] = qk_tile<T, D, RC>(kr, qf, scale_log2);
   }
 }
 
@@ -496,15 +570,15 @@ __device__ __forceinline__ uint32_t bf16_below(float x) {
 
 // Second half: online softmax, logit stash, suffix mass, and alpha.V (DV dims), V from the LDS tile
 // (bfloat16) or from the block's registers (float32).
-// X3 (bfloat16): alpha enters alpha.V as a whole float32, in three terms, and an infinite V value of a
-// slot with alpha > 0 gives an infinite output; without X3 in two terms, of which the second may be 0.
+// RC and bfloat16: alpha enters alpha.V as a whole float32, in three terms, and an infinite V value of a
+// slot with alpha > 0 gives an infinite output; without RC in two terms, of which the second may be 0.
 // The third product costs nothing that shows: batch 5, 32 / 8 heads, head_dim 64, cap 1500 14.3 us a
 // layer with two and with three.
-template <typename T, int D, int DV, bool X3>
+template <typename T, int D, int DV, bool RC, typename S_t>
 __device__ __forceinline__ void finish_block(const f32x4_t* S, unsigned long long suf,
                                              const Block<T, D, DV>& B, const RowCtx& r, int blk,
-                                             int g, int c, int G, float scale_log2,
-                                             const StashRow& sr, uint16_t* vt, Online& st,
+                                             int g, int c, int G, const StashRow& sr, uint16_t* vt,
+                                             Online<S_t>& st,
                                              f32x4_t* O) {
   using Gm = Geo<T, D, DV>;
   constexpr int MT = Gm::MT;
@@ -515,7 +589,7 @@ __device__ __forceinline__ void finish_block(const f32x4_t* S, unsigned long lon
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int slot = blk + Gm::slot(4 * g + v, mt);
-      s[mt][v] = slot < r.n_eff ? S[mt][v] * scale_log2 : -INFINITY;
+      s[mt][v] = slot < r.n_eff ? S[mt][v] : -INFINITY;
       mx = fmaxf(mx, s[mt][v]);
     }
   }
@@ -532,45 +606,44 @@ __device__ __forceinline__ void finish_block(const f32x4_t* S, unsigned long lon
   mx = row_groups_max(mx);
   const float m_new = fmaxf(st.m, mx);
   const float alpha = exp2_hw(st.m - m_new);
-  float p[MT][4];
-  float psum = 0.f, ssum = 0.f;
+  float p[MT][4], ps[MT][4];
 #pragma unroll
   for (int mt = 0; mt < MT; ++mt) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       p[mt][v] = exp2_hw(s[mt][v] - m_new);
-      psum += p[mt][v];
-      ssum += ((suf >> Gm::slot(4 * g + v, mt)) & 1ull) ? p[mt][v] : 0.f;
+      ps[mt][v] = ((suf >> Gm::slot(4 * g + v, mt)) & 1ull) ? p[mt][v] : 0.f;
     }
   }
-  st.l = st.l * alpha + psum;
-  st.s = st.s * alpha + ssum;
+  auto sum = [](const float(*x)[4]) {
+    S_t r = (x[0][0] + x[0][1]) + (x[0][2] + x[0][3]);
+    if constexpr (MT == 2) r += (S_t)((x[1][0] + x[1][1]) + (x[1][2] + x[1][3]));
+    return r;
+  };
+  st.l = st.l * alpha + sum(p);
+  st.s = st.s * alpha + sum(ps);
   st.m = m_new;
   float al[4];
   if constexpr (Gm::F32) {
     // k index g of step (mt, v) is slot(4g + v, mt): A is the lane's own alpha, B its V row.
-    // Accumulator 4h + e holds dims 64h + 4c + e. The block's terms are summed on their own and
-    // then added, so the running sum is rounded once a block and not once a slot.
+    // Accumulator 4h + e holds dims 64h + 4c + e.
 #pragma unroll
     for (int v = 0; v < 4; ++v) al[v] = __shfl(alpha, 4 * g + v, 64);
     constexpr int H = DV / 64;
 #pragma unroll
-    for (int h = 0; h < H; ++h) {
-      f32x4_t P[4];
+    for (int t = 0; t < 4 * H; ++t) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) P[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      for (int v = 0; v < 4; ++v) O[t][v] *= al[v];
+    }
 #pragma unroll
-      for (int i = 0; i < 4 * MT; ++i) {
+    for (int i = 0; i < 4 * MT; ++i) {
+#pragma unroll
+      for (int h = 0; h < H; ++h) {
         const unsigned* vx = (const unsigned*)&B.v[i * H + h];
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          P[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[i >> 2][i & 3], __uint_as_float(vx[e]), P[e],
-                                                      0, 0, 0);
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) O[4 * h + e][v] = fmaf(O[4 * h + e][v], al[v], P[e][v]);
+          O[4 * h + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[i >> 2][i & 3], __uint_as_float(vx[e]),
+                                                              O[4 * h + e], 0, 0, 0);
       }
     }
   } else {
@@ -584,12 +657,12 @@ __device__ __forceinline__ void finish_block(const f32x4_t* S, unsigned long lon
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const float x = p[e >> 2][e & 3];
-      const uint32_t xb = X3 ? bf16_below(x) : __float_as_uint(x) & 0xffff0000u;
+      const uint32_t xb = RC ? bf16_below(x) : __float_as_uint(x) & 0xffff0000u;
       const float y = x - __uint_as_float(xb);
-      const uint32_t yb = X3 ? bf16_below(y) : __float_as_uint(y);
+      const uint32_t yb = RC ? bf16_below(y) : __float_as_uint(y);
       hb[e] = xb >> 16;
       mb[e] = yb >> 16;
-      lb[e] = X3 ? __float_as_uint(y - __uint_as_float(yb)) >> 16 : 0u;
+      lb[e] = RC ? __float_as_uint(y - __uint_as_float(yb)) >> 16 : 0u;
     }
     auto pack = [](const uint32_t* x) {
       return as_bf16x8(make_uint4(x[0] | (x[1] << 16), x[2] | (x[3] << 16), x[4] | (x[5] << 16),
@@ -614,7 +687,7 @@ __device__ __forceinline__ void finish_block(const f32x4_t* S, unsigned long lon
       for (int v = 0; v < 4; ++v) O[nb][v] *= al[v];
       O[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Ahi, Bv, O[nb], 0, 0, 0);
       O[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Amid, Bv, O[nb], 0, 0, 0);
-      if constexpr (X3) O[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Alo, Bv, O[nb], 0, 0, 0);
+      if constexpr (RC) O[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Alo, Bv, O[nb], 0, 0, 0);
     }
   }
 }
@@ -831,8 +904,8 @@ __device__ __forceinline__ void load_acc_slots(AccSlots<MS, NW>& o, const float*
 template <typename T, int D, bool RC, int SG, int MS, int NW, int DV>
 __device__ __forceinline__ void single_split_epilogue(const AttendArgs& a, const f32x4_t* O,
                                                       char* mine, char* smem, const float* slog,
-                                                      float (*sm_m)[16], float (*sm_l)[16],
-                                                      float (*sm_s)[16], const RowInfo& r,
+                                                      float (*sm_m)[16], Sum<RC> (*sm_l)[16],
+                                                      Sum<RC> (*sm_s)[16], const RowInfo& r,
                                                       int g, int c, bool hdr_ok,
                                                       const AccSlots<MS, NW>& old) {
   constexpr int WB = wave_lds_bytes<T, D, DV>();
@@ -841,6 +914,7 @@ __device__ __forceinline__ void single_split_epilogue(const AttendArgs& a, const
   float* acc = a.acc + r.bk * a.cap;
   put_numerators<T, DV>(O, mine, g, c);
   __shared__ float sM1[kMaxGroup], srZ1[kMaxGroup], sf1[kMaxGroup][NW];
+  __shared__ Outs<T> srZo[kMaxGroup];  // 1 / sum for the outputs
   __shared__ int s_ok1;
   if (tid == 0) s_ok1 = hdr_ok ? 1 : 0;
   lds_barrier();  // every wave's statistics and numerators are in LDS
@@ -853,7 +927,7 @@ __device__ __forceinline__ void single_split_epilogue(const AttendArgs& a, const
     float M = -INFINITY;
 #pragma unroll
     for (int w = 0; w < NW; ++w) M = fmaxf(M, sm_m[w][h]);
-    float lsum = 0.f, ssum = 0.f;
+    Sum<RC> lsum = 0, ssum = 0;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
       const float mw = sm_m[w][h];
@@ -862,18 +936,20 @@ __device__ __forceinline__ void single_split_epilogue(const AttendArgs& a, const
       lsum += f * sm_l[w][h];
       ssum += f * sm_s[w][h];
     }
+    const float rZ = 1.f / (float)lsum;
     sM1[h] = M;
-    srZ1[h] = 1.f / lsum;
-    if (r.dh == 0) write_row_stats(a, r.b, r.hkv, h, M, 1.f / lsum, ssum);
+    srZ1[h] = rZ;
+    srZo[h] = recip((Outs<T>)lsum, rZ);
+    if (r.dh == 0) write_row_stats(a, r.b, r.hkv, h, M, rZ, (float)ssum);
   }
   lds_barrier();
   T* out = (T*)a.out + ((size_t)r.b * a.Hq + r.hkv * G) * D + r.dh * DV;
   for (int i = tid; i < GDV; i += 64 * NW) {
     const int h = i / DV;
-    float o = 0.f;
+    Outs<T> o = 0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) o += sf1[h][w] * ((const float*)(smem + w * WB))[i];
-    out[h * D + (i - h * DV)] = from_f32<T>(o * srZ1[h]);
+    for (int w = 0; w < NW; ++w) o += (Outs<T>)sf1[h][w] * ((const float*)(smem + w * WB))[i];
+    out[h * D + (i - h * DV)] = from_f32<T>((float)(o * srZo[h]));
   }
   if (r.dh != 0) return;
   // H2O increment of the split's slots: alpha = exp2(s - M) / Z; slots past the split keep their
@@ -1277,11 +1353,11 @@ __device__ __forceinline__ void exchange_epilogue(const AttendArgs& a, const f32
 
 // Merge form: the waves of the workgroup are merged in LDS into one partial for this split
 // (part_ml, part_s, part_o); attend_combine_mfma finishes the row in a second launch.
-template <typename T, int D, int SG>
+template <typename T, int D, bool RC, int SG>
 __device__ __forceinline__ void merge_form_epilogue(const AttendArgs& a, const f32x4_t* O,
                                                     char* mine, char* smem, const float* slog,
-                                                    float (*sm_m)[16], float (*sm_l)[16],
-                                                    float (*sm_s)[16], const RowInfo& r, int wave,
+                                                    float (*sm_m)[16], Sum<RC> (*sm_l)[16],
+                                                    Sum<RC> (*sm_s)[16], const RowInfo& r, int wave,
                                                     int lane, int g, int c, int nb) {
   constexpr int NW = kWaves, WB = wave_lds_bytes<T, D, D>(), BS = Geo<T, D>::BS;
   const int G = a.G;
@@ -1313,7 +1389,7 @@ __device__ __forceinline__ void merge_form_epilogue(const AttendArgs& a, const f
     float M = -INFINITY;
 #pragma unroll
     for (int w = 0; w < NW; ++w) M = fmaxf(M, sm_m[w][h]);
-    float lsum = 0.f, ssum = 0.f;
+    Sum<RC> lsum = 0, ssum = 0;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
       const float mw = sm_m[w][h];
@@ -1322,16 +1398,16 @@ __device__ __forceinline__ void merge_form_epilogue(const AttendArgs& a, const f
       lsum += f * sm_l[w][h];
       ssum += f * sm_s[w][h];
     }
-    a.part_ml[pbase + h] = make_float2(M, lsum);
-    a.part_s[pbase + h] = ssum;
+    a.part_ml[pbase + h] = make_float2(M, (float)lsum);
+    a.part_s[pbase + h] = (float)ssum;
   }
   lds_barrier();
   for (int i = threadIdx.x; i < G * D; i += 64 * NW) {
     const int h = i / D, d = i - h * D;
-    float o = 0.f;
+    Outs<T> o = 0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) o += sm_f[h][w] * ((const float*)(smem + w * WB))[h * D + d];
-    a.part_o[(pbase + h) * D + d] = o;
+    for (int w = 0; w < NW; ++w) o += (Outs<T>)sm_f[h][w] * ((const float*)(smem + w * WB))[h * D + d];
+    a.part_o[(pbase + h) * D + d] = (float)o;
   }
 }
 
@@ -1509,7 +1585,7 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
   stash_row.glob = CO ? nullptr : a.stash + (bk * G + (c < G ? c : 0)) * a.cap_s;
   stash_row.lo = s_lo;
 
-  Online st{-INFINITY, 0.f, 0.f};
+  Online<Sum<RC>> st{-INFINITY, 0, 0};
   f32x4_t O[VE];
 #pragma unroll
   for (int rr = 0; rr < VE; ++rr) O[rr] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -1549,37 +1625,34 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
     }
     for (int i = 0; i + 1 < nb; ++i) {
       const int blk = s_lo + BS * (wave + NW * i);
-      block_qk<T, D>(K, rc, blk, lane, mine, qf, S);
+      block_qk<T, D, RC>(K, rc, blk, lane, mine, qf, a.scale_log2, S);
       load_kraw<T, D, NT, RC>(K, Kb, blk + BS * NW, lane, klast);
       suf = suffix_bits<BS>(rc, blk, lane);
       if constexpr (Gm::F32) {
         // V is read from its registers, so the next block's V rows are requested last.
         patch_v<D, DV>(A, rc, blk, g, c);
-        finish_block<T, D, DV, RC>(S, suf, A, rc, blk, g, c, G, a.scale_log2, stash_row, vt, st, O);
+        finish_block<T, D, DV, RC>(S, suf, A, rc, blk, g, c, G, stash_row, vt, st, O);
         load_v<T, D, NT, RC, DV>(A, rc, blk + BS * NW);
       } else {
         stage_v<D, DV>(A, rc, blk, g, c, vt);
         load_v<T, D, NT, RC, DV>(A, rc, blk + BS * NW);
-        finish_block<T, D, DV, RC>(S, suf, A, rc, blk, g, c, G, a.scale_log2, stash_row, vt, st, O);
+        finish_block<T, D, DV, RC>(S, suf, A, rc, blk, g, c, G, stash_row, vt, st, O);
       }
     }
     if (multi && threadIdx.x == 0 && (int)(s_rw_old & 0xffffu) != p_ns - 1)
       rw_chk = row_peek(a.rows + bk);
     const int blk = s_lo + BS * (wave + NW * (nb - 1));
-    block_qk<T, D>(K, rc, blk, lane, mine, qf, S);
+    block_qk<T, D, RC>(K, rc, blk, lane, mine, qf, a.scale_log2, S);
     suf = suffix_bits<BS>(rc, blk, lane);
     if constexpr (Gm::F32) patch_v<D, DV>(A, rc, blk, g, c);
     else stage_v<D, DV>(A, rc, blk, g, c, vt);
-    finish_block<T, D, DV, RC>(S, suf, A, rc, blk, g, c, G, a.scale_log2, stash_row, vt, st, O);
+    finish_block<T, D, DV, RC>(S, suf, A, rc, blk, g, c, G, stash_row, vt, st, O);
   }
 
   // The wave's partial: head c's max in every lane, sum and suffix sum reduced over the row groups.
-  float l_run = st.l, s_run = st.s;
-  l_run += __shfl_xor(l_run, 16, 64);
-  l_run += __shfl_xor(l_run, 32, 64);
-  s_run += __shfl_xor(s_run, 16, 64);
-  s_run += __shfl_xor(s_run, 32, 64);
-  __shared__ float sm_m[NW][16], sm_l[NW][16], sm_s[NW][16];
+  const Sum<RC> l_run = row_groups_sum(st.l), s_run = row_groups_sum(st.s);
+  __shared__ float sm_m[NW][16];
+  __shared__ Sum<RC> sm_l[NW][16], sm_s[NW][16];
   if (g == 0) {
     sm_m[wave][c] = st.m;
     sm_l[wave][c] = l_run;
@@ -1610,7 +1683,7 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
       }
     }
   } else {
-    merge_form_epilogue<T, D, SG>(a, O, mine, smem, slog, sm_m, sm_l, sm_s, ri, wave, lane, g, c, nb);
+    merge_form_epilogue<T, D, RC, SG>(a, O, mine, smem, slog, sm_m, sm_l, sm_s, ri, wave, lane, g, c, nb);
   }
 }
 
@@ -1742,14 +1815,14 @@ __global__ __launch_bounds__(64 * NW) void attend_few(AttendArgs a) {
   sr.lds = (lds_float*)slog + (c < G ? c : 0) * MS;
   sr.glob = nullptr;
   sr.lo = 0;
-  Online st{-INFINITY, 0.f, 0.f};
+  Online<Outs<T>> st{-INFINITY, 0, 0};
   f32x4_t O[VE];
 #pragma unroll
   for (int i = 0; i < VE; ++i) O[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   for (int blk = BS * wave; blk < n; blk += BS * NW) {
     const int next = blk + BS * NW;
     f32x4_t S[Gm::MT];
-    block_qk<T, D>(K, rc, blk, lane, mine, qf, S);
+    block_qk<T, D, RC>(K, rc, blk, lane, mine, qf, a.scale_log2, S);
     const int slot = blk + (lane & (BS - 1));
     const unsigned long long suf =
         __ballot(lane < BS && slot < n && (slot == rc.lsub ? t_in : ps > thr));
@@ -1762,16 +1835,14 @@ __global__ __launch_bounds__(64 * NW) void attend_few(AttendArgs a) {
       stage_v<D, DV>(A, rc, blk, g, c, vt);
       if (next < n) load_v<T, D, false, true, DV>(A, rc, next);
     }
-    finish_block<T, D, DV, RC>(S, suf, A, rc, blk, g, c, G, a.scale_log2, sr, vt, st, O);
+    finish_block<T, D, DV, RC>(S, suf, A, rc, blk, g, c, G, sr, vt, st, O);
     if (Gm::F32 && next < n) load_v<T, D, false, true, DV>(A, rc, next);
   }
   // The wave's partial; then the waves are merged by wave 0 (lane: head c, waves g, g + 4, ...).
-  float l_run = st.l, s_run = st.s;
-  l_run += __shfl_xor(l_run, 16, 64);
-  l_run += __shfl_xor(l_run, 32, 64);
-  s_run += __shfl_xor(s_run, 16, 64);
-  s_run += __shfl_xor(s_run, 32, 64);
-  __shared__ float sm_m[NW][16], sm_l[NW][16], sm_s[NW][16], sf[16][NW], sM[16], srZ[16], sS[16];
+  const double l_run = row_groups_sum((double)st.l), s_run = row_groups_sum((double)st.s);
+  __shared__ float sm_m[NW][16], sf[16][NW], sM[16], srZ[16], sS[16];
+  __shared__ double sm_l[NW][16], sm_s[NW][16];
+  __shared__ Outs<T> srZo[16];
   if (g == 0) {
     sm_m[wave][c] = st.m;
     sm_l[wave][c] = l_run;
@@ -1796,8 +1867,8 @@ __global__ __launch_bounds__(64 * NW) void attend_few(AttendArgs a) {
       mw[q] = sm_m[4 * q + q4][h];
       M = fmaxf(M, mw[q]);
     }
-    M = quad_all<true>(M);
-    float lsum = 0.f, ssum = 0.f;
+    M = quad_max(M);
+    double lsum = 0, ssum = 0;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       const float f = mw[q] == -INFINITY ? 0.f : exp2_hw(mw[q] - M);
@@ -1805,12 +1876,13 @@ __global__ __launch_bounds__(64 * NW) void attend_few(AttendArgs a) {
       lsum += f * sm_l[4 * q + q4][h];
       ssum += f * sm_s[4 * q + q4][h];
     }
-    lsum = quad_all<false>(lsum);
-    ssum = quad_all<false>(ssum);
+    lsum = quad_sum(lsum);
+    ssum = quad_sum(ssum);
     if (q4 == 0) {
       sM[h] = M;
-      srZ[h] = 1.f / lsum;
-      sS[h] = ssum;
+      srZ[h] = 1.f / (float)lsum;
+      srZo[h] = recip((Outs<T>)lsum, srZ[h]);
+      sS[h] = (float)ssum;
     }
   }
   lds_barrier();
@@ -1819,10 +1891,10 @@ __global__ __launch_bounds__(64 * NW) void attend_few(AttendArgs a) {
   T* out = (T*)a.out + ((size_t)b * a.Hq + hkv * G) * D + dh * DV;
   for (int i = tid; i < G * DV; i += 64 * NW) {
     const int h = i / DV;
-    float o = 0.f;
+    Outs<T> o = 0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) o += sf[h][w] * ((const float*)(smem + w * WB))[i];
-    out[h * D + (i - h * DV)] = from_f32<T>(o * srZ[h]);
+    for (int w = 0; w < NW; ++w) o += (Outs<T>)sf[h][w] * ((const float*)(smem + w * WB))[i];
+    out[h * D + (i - h * DV)] = from_f32<T>((float)(o * srZo[h]));
   }
   // H2O increment, one slot per thread: the parts of the row take the groups of 64 in turn.
 #pragma unroll
@@ -2032,6 +2104,7 @@ __global__ __launch_bounds__(256) void attend_combine_mfma(AttendArgs a) {
   __shared__ float2 sml[kMaxMfmaSplits * kMaxGroup];
   __shared__ float sps[kMaxMfmaSplits * kMaxGroup];
   __shared__ float sM[kMaxGroup], srZ[kMaxGroup], sF[kMaxGroup * kMaxMfmaSplits];
+  __shared__ Outs<T> srZo[kMaxGroup];
   if constexpr (FX) {
 #pragma unroll
     for (int u = 0; u < CombineLoads<D, GM>::kStIter; ++u) {
@@ -2055,16 +2128,17 @@ __global__ __launch_bounds__(256) void attend_combine_mfma(AttendArgs a) {
   if (tid < G) {
     float M = -INFINITY;
     for (int k = 0; k < ns; ++k) M = fmaxf(M, sml[k * G + tid].x);
-    float Z = 0.f, S = 0.f;
+    Sum<RC> Zs = 0, Ss = 0;
     for (int k = 0; k < ns; ++k) {
       const float f = exp2_hw(sml[k * G + tid].x - M);
       sF[tid * kMaxMfmaSplits + k] = f;
-      Z += sml[k * G + tid].y * f;
-      S += sps[k * G + tid] * f;
+      Zs += (Sum<RC>)sml[k * G + tid].y * f;
+      Ss += (Sum<RC>)sps[k * G + tid] * f;
     }
-    const float rZ = 1.f / Z;
+    const float S = (float)Ss, rZ = 1.f / (float)Zs;
     sM[tid] = M;
     srZ[tid] = rZ;
+    srZo[tid] = recip((Outs<T>)Zs, rZ);
     if (split == 0) {
       // Row statistics and the confidence proxy, issued before the bulk stores. Lanes 0..G-1 of
       // wave 0 hold the G heads; their max goes to conf with one atomic.
@@ -2109,9 +2183,9 @@ __global__ __launch_bounds__(256) void attend_combine_mfma(AttendArgs a) {
   }
   for (int i = tid; i < cnt; i += 256) {
     const int h = (o_lo + i) / D;
-    float o = 0.f;
-    for (int k = 0; k < ns; ++k) o += sF[h * kMaxMfmaSplits + k] * spo[k * per + i];
-    out[o_lo + i] = from_f32<T>(o * srZ[h]);
+    Outs<T> o = 0;
+    for (int k = 0; k < ns; ++k) o += (Outs<T>)sF[h * kMaxMfmaSplits + k] * spo[k * per + i];
+    out[o_lo + i] = from_f32<T>((float)(o * srZo[h]));
   }
 }
 
@@ -2224,13 +2298,15 @@ hipError_t launch_mfma_form(AttendArgs a, hipStream_t st);
 // The build compiles this file once per part, in parallel, each with the kernels of one cache type
 // and head_dim; part 0 holds the portable kernels and the dispatch.
 #if LG_ATTEND_PART > 0
-// Few rows (the plan has cap <= few_max_slots, and <= 1024 in float32). 16 waves where the logits leave the LDS for it (bfloat16: the step of a 1.5B-shaped batch
-// of one 261 us with 16 waves, 271 with 8); a second block in flight per wave is slower (its loads
-// only queue in the CU's address unit, and delay the first block's: 8 waves 295 -> 308 us).
+// Few rows (the plan has cap <= few_max_slots, and <= 1024 in float32). 16 waves where the logits leave
+// the LDS for it (bfloat16: the step of a 1.5B-shaped batch of one 261 us with 16 waves, 271 with 8);
+// 8 for a ragged cap at head_dim 128, whose third alpha term does not fit the 128 registers of 16 waves
+// (36 of them spilled). A second block in flight per wave is slower (its loads only queue in the CU's
+// address unit, and delay the first block's: 8 waves 295 -> 308 us).
 template <typename T, int D, bool RC, int SG, int MS>
 static hipError_t launch_few_ms(const AttendArgs& a, hipStream_t st) {
   constexpr int DS = few_dsplit(sizeof(T) == 4, D);
-  constexpr int NW = SG * MS <= 8192 && sizeof(T) == 2 ? 16 : 8;
+  constexpr int NW = SG * MS <= 8192 && sizeof(T) == 2 && !(RC && D == 128) ? 16 : 8;
   const unsigned grid = (unsigned)((a.B * a.Hkv + 7) / 8) * 8 * DS;
   hipLaunchKernelGGL((attend_few<T, D, RC, SG, MS, NW, DS>), dim3(grid), dim3(64 * NW), 0, st, a);
   return hipGetLastError();
