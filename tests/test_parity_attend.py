@@ -541,6 +541,38 @@ def test_float32_error_against_64_bits(dtype, B, Hq, Hkv, D, cap):
     first = 0 if dtype == "f32" else 1  # a bfloat16 out holds its own rounding
     assert np.all(rel["auto"][first:] <= 1.05 * rel["portable"][first:]), rel
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,Hq,Hkv,D,cap", [(1, 8, 2, 128, 256), (2, 16, 1, 64, 251), (2, 14, 2, 128, 3072),
+                                            (40, 8, 2, 64, 2049), (32, 28, 4, 128, 1500), (70, 8, 2, 128, 1024)])
+def test_small_score_increments(dtype, B, Hq, Hkv, D, cap):
+    """A probability below 2^-126 is added to its slot's score as it is (few rows, merge with short and long
+    splits, one split per row). One slot has logit 0, one -88.5 and the others -177, so the second has
+    probability exp(-88.5) = 3.7e-39. The logit is within 2^-17 of it in float32 and the increment a
+    multiple of 2^-149, so 1e-4 of it bounds the error."""
+    from paper_2604_10044_amd import lg
+    dev = torch.device("cuda")
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    n, top, low = cap - 1, cap // 3, cap // 2
+    K = torch.zeros(B, Hkv, cap, D, dtype=dt, device=dev)
+    K[:, :, :, 0] = -2
+    K[:, :, top, 0], K[:, :, low, 0] = 0, -1
+    q = torch.zeros(B, Hq, D, dtype=dt, device=dev)
+    q[:, :, 0] = 88.5 * np.sqrt(D)
+    pos = torch.arange(cap, dtype=torch.int32, device=dev).repeat(B, 1).contiguous()
+    lens = torch.full((B,), n, dtype=torch.int32, device=dev)
+    p = np.exp(-float(q[0, 0, 0]) / np.sqrt(D)) * (Hq // Hkv)
+    for form in ("auto", "portable"):
+        acc = torch.zeros(B, Hkv, cap, device=dev)
+        layer = lg.layer_cache(K, K, acc, Hq)
+        ws = make_ws(lg, layer, FORMS[form])
+        out = torch.zeros(B, Hq, D, dtype=dt, device=dev)
+        lse, sm = torch.zeros(B, Hq, device=dev), torch.zeros(B, Hq, device=dev)
+        attend(lg, layer, q, None, None, out, pos, lens, lens, lens, lse, sm, None, ws, FORMS[form])
+        torch.cuda.synchronize()
+        a = acc.cpu().numpy().astype(np.float64)
+        assert np.all(a[:, :, top] == Hq // Hkv), form
+        assert np.all(np.abs(a[:, :, low] - p) <= 1e-4 * p), (form, a[0, 0, low], p)
+
 
 def test_forms_agree():
     a = run_case(2, 28, 4, 128, 704, [500, 699], "bf16", FORMS["portable"], seed=21)
