@@ -19,6 +19,8 @@
 // sequences): moves K, V and acc rows r <- keep_idx[r] in place. keep_idx is ascending with keep_idx[r] >= r, so walking the rows in
 // chunks, reading a whole chunk before writing it, never overwrites a row a later chunk reads;
 // the next chunk's loads are issued before the current chunk's stores.
+#include <algorithm>
+
 #include "lg_keepset.h"
 
 namespace lg {
@@ -87,7 +89,7 @@ struct CompactArgs {
   const int32_t* keep_idx;
   const int32_t* new_len;
   int32_t B, Hkv, cap, row_bytes;
-  int32_t n_col;  // 128-byte columns of a K row and a V row together
+  int32_t n_layers;  // layers of this launch
 };
 
 __global__ __launch_bounds__(kKeepThreads) void keepset_kernel(KeepArgs a) {
@@ -187,12 +189,13 @@ __device__ __forceinline__ void compact_column(const CompactArgs& a, int l, int 
   }
 }
 
-// Grid (layer, kv head x column, group of sequences), the layer fastest: the dispatcher deals
+// Grid (layer + layers x column, kv head, group of sequences), the layer fastest (y and z are at most
+// 65535, which is what the host admits for heads and sequences): the dispatcher deals
 // consecutive workgroups round-robin to the 8 XCDs, so the rows of one flagged sequence spread over
 // all of them. Group z takes the flagged sequences of rank z, z + groups, ..., whichever they are,
 // so a launch with nothing to move stays small and a few flagged sequences do not share a group.
 __global__ __launch_bounds__(kCompactThreads) void compact_kernel(CompactArgs a) {
-  const int l = blockIdx.x, hkv = blockIdx.y / a.n_col, col = blockIdx.y % a.n_col;
+  const int l = blockIdx.x % a.n_layers, col = blockIdx.x / a.n_layers, hkv = blockIdx.y;
   const int lane = threadIdx.x & 63, groups = gridDim.z;
   int rank = 0;  // flagged sequences before this chunk
   for (int b0 = 0; b0 < a.B; b0 += 64) {
@@ -248,12 +251,13 @@ hipError_t launch_compact(const KeepArgs& ka, int n_layers, const lg_layer_cache
     ca.Hkv = Hkv;
     ca.cap = ka.cap;
     ca.row_bytes = row_bytes;
-    ca.n_col = 2 * row_bytes / kColBytes;
+    ca.n_layers = nl;
+    const int n_col = 2 * row_bytes / kColBytes;  // columns of a K row and a V row together
     // About kCompactWorkgroups workgroups: enough to fill the chip when every sequence is flagged,
     // few enough that the launch of a step with nothing to move costs no more than its start.
-    const int per_group = nl * Hkv * ca.n_col;
-    const int groups = min(ka.B, max(1, kCompactWorkgroups / per_group));
-    dim3 grid(nl, Hkv * ca.n_col, groups);
+    const long per_group = (long)nl * Hkv * n_col;
+    const int groups = (int)std::min((long)ka.B, std::max(1L, kCompactWorkgroups / per_group));
+    dim3 grid(nl * n_col, Hkv, groups);
     hipLaunchKernelGGL(compact_kernel, grid, dim3(kCompactThreads), 0, st, ca);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

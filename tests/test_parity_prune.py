@@ -175,6 +175,27 @@ def test_prune_parity_edges(B, cap, D, dtype, policy):
           budgets=[max(1, cap - i % 3) for i in range(B)])
 
 
+def test_prune_many_kv_heads():
+    """More KV heads times columns of a row than a grid's y extent (65535) has room for: the last two
+    of eight slots move to the front in every head (positions past the anchors, a recent window of two)."""
+    from paper_2604_10044_amd import lg
+    dev = torch.device("cuda")
+    B, Hkv, cap, D = 1, 16384, 8, 128
+    g = torch.Generator(device="cuda").manual_seed(3)
+    K, V = (torch.randn(B, Hkv, cap, D, generator=g, device=dev) for _ in range(2))
+    acc = torch.rand(B, Hkv, cap, generator=g, device=dev)
+    want = [torch.cat([x[:, :, 6:], x[:, :, 2:]], 2).clone() for x in (K, V, acc)]
+    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device=dev)  # noqa: E731
+    pos, length, budget = i32([list(range(100, 108))]), i32([8]), i32([8])
+    keep, new_len = torch.zeros(B, cap, dtype=torch.int32, device=dev), i32([0])
+    lg.lg_prune_compact(lg.lg_guard_params_default(), B, cap, [lg.layer_cache(K, V, acc, Hkv)], pos, length,
+                        budget, None, None, keep, new_len)
+    torch.cuda.synchronize()
+    assert new_len.tolist() == [2] and length.tolist() == [2] and pos[0, :2].tolist() == [106, 107]
+    for x, w in zip((K, V, acc), want):
+        assert torch.equal(x, w)
+
+
 def test_budget_upkeep_without_decisions():
     assert _case(16, 512, 128, "bf16", 2, seed=11, with_decision=False) > 0
 
