@@ -15,10 +15,10 @@
 // key by an 8-bit radix select over (score, slot) keys and stream-compacts the slots at or above it
 // with block-wide prefix sums.
 //
-// compact_kernel (one workgroup per 128-byte column of a (layer, kv head)'s K or V rows and group of
-// sequences): moves K, V and acc rows r <- keep_idx[r] in place. keep_idx is ascending with keep_idx[r] >= r, so walking the rows in
-// chunks, reading a whole chunk before writing it, never overwrites a row a later chunk reads;
-// the next chunk's loads are issued before the current chunk's stores.
+// compact_kernel (a workgroup at a time per 128-byte column of a (sequence, layer, kv head)'s K or V
+// rows): moves K, V and acc rows r <- keep_idx[r] in place. keep_idx is ascending with keep_idx[r] >= r,
+// so walking the rows in chunks, reading a whole chunk before writing it, never overwrites a row a later
+// chunk reads; the next chunk's loads are issued before the current chunk's stores.
 #include <algorithm>
 
 #include "lg_keepset.h"
@@ -89,7 +89,10 @@ struct CompactArgs {
   const int32_t* keep_idx;
   const int32_t* new_len;
   int32_t B, Hkv, cap, row_bytes;
-  int32_t n_layers;  // layers of this launch
+  int32_t n_layers;               // layers of this launch
+  int32_t n_col;                  // 128-byte columns of a K row and a V row together
+  int32_t per_seq;                // items of a sequence: n_layers x Hkv x n_col
+  int32_t step_rank, step_rest;   // the grid as whole sequences and items
 };
 
 __global__ __launch_bounds__(kKeepThreads) void keepset_kernel(KeepArgs a) {
@@ -121,7 +124,7 @@ constexpr int kColBytes = 128;
 constexpr int kColLanes = kColBytes / 16;                // lanes of a row
 constexpr int kPassRows = kCompactThreads / kColLanes;   // rows of one load instruction
 constexpr int kRowsPerPass = kPassRows * kCompactUnroll;
-constexpr int kCompactWorkgroups = 4096;
+constexpr int kCompactWorkgroups = 1024;
 static_assert(kRowsPerPass <= kCompactThreads, "at most one score per thread and pass");
 
 // Rows of a compaction pass, held in registers between its loads and its stores.
@@ -189,23 +192,42 @@ __device__ __forceinline__ void compact_column(const CompactArgs& a, int l, int 
   }
 }
 
-// Grid (layer + layers x column, kv head, group of sequences), the layer fastest (y and z are at most
-// 65535, which is what the host admits for heads and sequences): the dispatcher deals
-// consecutive workgroups round-robin to the 8 XCDs, so the rows of one flagged sequence spread over
-// all of them. Group z takes the flagged sequences of rank z, z + groups, ..., whichever they are,
-// so a launch with nothing to move stays small and a few flagged sequences do not share a group.
+// A fixed grid walks the (flagged sequence, kv head, column, layer) items, the layer fastest: the
+// dispatcher deals consecutive workgroups round-robin to the 8 XCDs, so the rows of one flagged sequence
+// spread over all of them. Most steps move nothing, and then the launch costs what its workgroups cost
+// to start: 1024 (four a CU, as many as are resident) 1.9 us at 28 layers of the 7B shape, where a grid
+// with the sequences in z, 4032 workgroups, took 6.0; one of 32 sequences flagged 34.7 us and 34.5, all
+// 32 1.07 ms with both.
 __global__ __launch_bounds__(kCompactThreads) void compact_kernel(CompactArgs a) {
-  const int l = blockIdx.x % a.n_layers, col = blockIdx.x / a.n_layers, hkv = blockIdx.y;
-  const int lane = threadIdx.x & 63, groups = gridDim.z;
-  int rank = 0;  // flagged sequences before this chunk
-  for (int b0 = 0; b0 < a.B; b0 += 64) {
-    const int mine = b0 + lane < a.B ? a.new_len[b0 + lane] : 0;
-    unsigned long long m = __ballot(mine > 0);
-    for (; m != 0; m &= m - 1, ++rank) {
-      if (rank % groups != (int)blockIdx.z) continue;
-      const int k = __builtin_ctzll(m);
-      compact_column(a, l, hkv, col, b0 + k, __builtin_amdgcn_readlane(mine, k));
-      __syncthreads();
+  const int lane = threadIdx.x & 63;
+  int b0 = 0, seen = 0;  // the chunk of 64 sequences at hand, flagged sequences before the bits of m
+  int mine = lane < a.B ? a.new_len[lane] : 0;
+  unsigned long long m = __ballot(mine > 0);
+  if (m == 0 && a.B <= 64) return;  // before the division
+  int rank = blockIdx.x / a.per_seq, rest = blockIdx.x % a.per_seq;  // the item: flagged sequence, and within
+  for (;;) {
+    while (m == 0 || seen < rank) {
+      const int c = __popcll(m);
+      if (m != 0 && seen + c > rank) {
+        m &= m - 1;
+        ++seen;
+        continue;
+      }
+      seen += c;
+      b0 += 64;
+      if (b0 >= a.B) return;
+      mine = b0 + lane < a.B ? a.new_len[b0 + lane] : 0;
+      m = __ballot(mine > 0);
+    }
+    const int k = __builtin_ctzll(m);
+    const int t = rest / a.n_layers;
+    compact_column(a, rest % a.n_layers, t / a.n_col, t % a.n_col, b0 + k, __builtin_amdgcn_readlane(mine, k));
+    __syncthreads();
+    rank += a.step_rank;
+    rest += a.step_rest;
+    if (rest >= a.per_seq) {
+      rest -= a.per_seq;
+      ++rank;
     }
   }
 }
@@ -252,13 +274,12 @@ hipError_t launch_compact(const KeepArgs& ka, int n_layers, const lg_layer_cache
     ca.cap = ka.cap;
     ca.row_bytes = row_bytes;
     ca.n_layers = nl;
-    const int n_col = 2 * row_bytes / kColBytes;  // columns of a K row and a V row together
-    // About kCompactWorkgroups workgroups: enough to fill the chip when every sequence is flagged,
-    // few enough that the launch of a step with nothing to move costs no more than its start.
-    const long per_group = (long)nl * Hkv * n_col;
-    const int groups = (int)std::min((long)ka.B, std::max(1L, kCompactWorkgroups / per_group));
-    dim3 grid(nl * n_col, Hkv, groups);
-    hipLaunchKernelGGL(compact_kernel, grid, dim3(kCompactThreads), 0, st, ca);
+    ca.n_col = 2 * row_bytes / kColBytes;
+    ca.per_seq = nl * Hkv * ca.n_col;  // at most 64 x 65535 x 8
+    const int grid = (int)std::min((long)ca.per_seq * ka.B, (long)kCompactWorkgroups);
+    ca.step_rank = grid / ca.per_seq;
+    ca.step_rest = grid % ca.per_seq;
+    hipLaunchKernelGGL(compact_kernel, dim3(grid), dim3(kCompactThreads), 0, st, ca);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
