@@ -416,6 +416,12 @@ typedef __attribute__((address_space(3))) short4_t lds_short4;
 // rows 8 apart over different banks.
 template <int D> constexpr int vtile_stride() { return D + 8; }
 
+// Between LDS accesses of one wave in which lanes read what other lanes wrote, or write what others read:
+// the hardware keeps a wave's LDS accesses in order, and this keeps the compiler to it (it emits nothing).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+}
+
 // First half of a block, in two steps: stage_v writes the V rows to the wave's LDS tile
 // (row-major; afterwards the V registers are free), stage_qk takes the suffix mask and runs q.K^T
 // (afterwards the K registers are free).
@@ -425,6 +431,7 @@ __device__ __forceinline__ void stage_v(const Block<uint16_t, D, DV>& B, const R
   constexpr int RS = vtile_stride<DV>(), LPR = DV / 8, RPL = vrows_per_load<DV>();
   const int lane = 16 * g + c;
   const int rl = lane / LPR, cl = 8 * (lane % LPR);  // the lane's row within a load, and dims
+  wave_lds_fence();  // the block's K tiles have been read
   if (blk + 32 > r.n_eff) {  // partial last block: rows past the live ones may hold anything
 #pragma unroll
     for (int i = 0; i < DV / 16; ++i) {
@@ -436,9 +443,11 @@ __device__ __forceinline__ void stage_v(const Block<uint16_t, D, DV>& B, const R
     for (int i = 0; i < DV / 16; ++i) *(uint4*)(vt + (i * RPL + rl) * RS + cl) = B.v[i];
   }
   // The appended row replaces the cache's slot (the wave's LDS writes land in order).
+  wave_lds_fence();
   if (r.lsub >= blk && r.lsub < blk + 32) {
     if (lane < DV / 8) *(uint4*)(vt + (r.lsub - blk) * RS + 8 * lane) = r.snew[D / 8 + r.vp0 + lane];
   }
+  wave_lds_fence();
 }
 
 // float32 V rows stay in their registers: dead rows are zeroed and the appended row put in place.
@@ -466,6 +475,7 @@ __device__ __forceinline__ void turn_k(const KRaw<T, D>& K, const RowCtx& r, int
   using Gm = Geo<T, D>;
   constexpr int RB = KRaw<T, D>::RB, KS = ktile_stride<T, D>(), LPR = RB / 16;
   const int g = lane >> 4, c = lane & 15;
+  wave_lds_fence();  // what the region held (a tile of K or V) has been read
 #pragma unroll
   for (int j = 0; j < KRaw<T, D>::NK; ++j) {
     const int s = (64 * j + lane) / LPR;  // slot of the block
@@ -479,8 +489,10 @@ __device__ __forceinline__ void turn_k(const KRaw<T, D>& K, const RowCtx& r, int
   }
   // The appended row replaces the cache's slot (the wave's LDS writes land in order).
   const int sub = r.lsub - blk;
+  wave_lds_fence();
   if (sub >= 0 && sub < Gm::BS && (Gm::MT == 1 || ((sub >> 2) & 1) == mt) && lane < Gm::PPR)
     *(uint4*)(kt + (Gm::MT == 2 ? 4 * (sub >> 3) + (sub & 3) : sub) * KS + 16 * lane) = r.snew[lane];
+  wave_lds_fence();
 #pragma unroll
   for (int kk = 0; kk < Gm::NS; ++kk) kr[kk] = *(const uint4*)(kt + c * KS + 64 * kk + 16 * g);
 }
@@ -730,6 +742,7 @@ constexpr int wave_lds_bytes() {
 template <typename T, int DV>
 __device__ __forceinline__ void put_numerators(const f32x4_t* O, char* mine, int g, int c) {
   float* my_o = (float*)mine;
+  wave_lds_fence();
 #pragma unroll
   for (int t = 0; t < DV / 16; ++t) {
     const int d = sizeof(T) == 4 ? 64 * (t >> 2) + 4 * c + (t & 3) : 16 * t + c;
@@ -1831,6 +1844,7 @@ __global__ __launch_bounds__(64 * NW) void attend_few(AttendArgs a) {
           ((uint4*)((T*)(i < Gm::PPR ? a.k_w : a.v_w) + (bk * cap + L) * D))[i % Gm::PPR] = xnew[k];
       }
     }
+    wave_lds_fence();
   }
   const bool t_in = a.t[b] > thr;  // the appended slot is in the recent suffix
   rc.L = L;
