@@ -516,6 +516,15 @@ template <int D> constexpr double scale_log2_d() {
   return 1.4426950408889634074 * (D == 64 ? 0.125 : 0.088388347648318440550);
 }
 
+// An element of a 16-byte load as an MFMA operand, in a register of its own: while it was part of the
+// load, clang 22 (ROCm 7.2) put the accumulator of q.K^T over elements that were still to be multiplied, in
+// the non-temporal merge-form instances (seen in the listing; wrong logits).
+__device__ __forceinline__ float own_register(unsigned u) {
+  float x = __uint_as_float(u);
+  asm("" : "+v"(x));
+  return x;
+}
+
 // Logits (base 2) of one tile of 16 slots, K rows in the A layout.
 template <typename T, int D, bool RC>
 __device__ __forceinline__ f32x4_t qk_tile(const uint4* kr, const QFrag<T, D>& qf, float scale_log2) {
@@ -536,11 +545,7 @@ __device__ __forceinline__ f32x4_t qk_tile(const uint4* kr, const QFrag<T, D>& q
         const unsigned* qx = (const unsigned*)&qf.q[kk];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          // A register of its own: while the element is part of a 16-byte load, clang 22
-          // (ROCm 7.2) put the accumulator over elements that were still to be multiplied, in
-          // the non-temporal merge-form instances (seen in the listing; wrong logits).
-          float x = __uint_as_float(kx[e]);
-          asm("" : "+v"(x));
+          const float x = own_register(kx[e]);
           f32x4_t& acc = P[4 * (kk & 1) + e];
           acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x, __uint_as_float(qx[e]), acc, 0, 0, 0);
         }
@@ -679,9 +684,10 @@ __device__ __forceinline__ void finish_block(const f32x4_t* S, unsigned long lon
       for (int h = 0; h < H; ++h) {
         const unsigned* vx = (const unsigned*)&B.v[i * H + h];
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          O[4 * h + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[i >> 2][i & 3], __uint_as_float(vx[e]),
-                                                              O[4 * h + e], 0, 0, 0);
+        for (int e = 0; e < 4; ++e) {
+          const float x = own_register(vx[e]);
+          O[4 * h + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[i >> 2][i & 3], x, O[4 * h + e], 0, 0, 0);
+        }
       }
     }
   } else {
