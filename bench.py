@@ -164,7 +164,9 @@ FORM_NAMES = {1: "attend_valu + attend_combine (portable pair)",
 
 
 def attend_kernel_name(header: dict) -> str:
-    """The attention launch that ran, from the form the workspace was initialised for."""
+    """The attention launch that ran, from what the workspace was initialised for."""
+    if header["few_rows"]:
+        return "lg_decode_attend: attend_few (one launch for few rows)"
     return "lg_decode_attend: %s, splits of <= %d slots" % (
         FORM_NAMES.get(header["form"], "form %d" % header["form"]), header["split"])
 

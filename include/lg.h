@@ -199,7 +199,8 @@ typedef struct {
   uint32_t magic, version;
   int32_t batch, n_q_heads, n_kv_heads, head_dim, cap, dtype, form, split;
   uint32_t status;      /* 0, or LG_ATTEND_STATUS_* bits */
-  uint32_t reserved[5];
+  int32_t few_rows;     /* 1: lg_decode_attend runs its launch for few rows on this shape */
+  uint32_t reserved[4];
 } lg_attend_workspace_header;
 
 /* Workspace bytes lg_decode_attend needs for this layer shape (0 for an invalid shape). The

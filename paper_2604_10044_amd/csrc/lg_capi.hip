@@ -99,6 +99,7 @@ static WsHeader ws_header(const lg_layer_cache& c, const AttendPlan& p) {
   h.form = p.form;
   h.split = p.split;
   h.status = 0;
+  h.few = p.few;
   return h;
 }
 

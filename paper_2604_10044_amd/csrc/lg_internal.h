@@ -30,8 +30,8 @@ __host__ __device__ inline size_t align_up(size_t x, size_t a) { return (x + a -
 // Kernel forms of lg_decode_attend. The automatic choice for caps up to 32768 (both types):
 // kFormOneLaunch when every row is a single split (no exchange; see attend_plan), kFormMerge
 // otherwise (the sweep and a merging launch, in the ragged batch faster than the one-launch form's
-// exchange; or, for few rows of a short cache, attend_few, which the workspace header does not tell
-// apart: see few_rows); kFormPortable for longer caches, whose rows would
+// exchange; or, for few rows of a short cache, attend_few on the same workspace, told apart by the
+// header's `few`: see few_rows); kFormPortable for longer caches, whose rows would
 // be more than kMaxMfmaSplits splits. The one-launch form with several splits per row (bfloat16,
 // cap a multiple of 32) is reachable through the test hook, which takes the MFMA forms for those
 // caches only.
@@ -148,7 +148,8 @@ struct WsHeader {
   uint32_t magic, version;
   int32_t batch, n_q_heads, n_kv_heads, head_dim, cap, dtype, form, split;
   uint32_t status;
-  uint32_t reserved[5];
+  int32_t few;         // AttendPlan::few of the initialising call (for readers; no launch checks it)
+  uint32_t reserved[4];
 };
 static_assert(sizeof(WsHeader) == 64, "header size");
 

@@ -43,7 +43,7 @@ DECISION_FIELDS = ["trigger", "warn", "votes", "stall_gate", "tailrep_gate", "n"
                    "lz_cost", "novel", "nov_r", "period", "span_lo", "level", "n_int"]
 ATTEND_ERROR_COL = 14  # lg_decision.attend_error (not a decision of the paper's rule)
 HEADER_FIELDS = ["magic", "version", "batch", "n_q_heads", "n_kv_heads", "head_dim", "cap",
-                 "dtype", "form", "split", "status"]
+                 "dtype", "form", "split", "status", "few_rows"]
 STATE_INTS = 528     # lg_guard_state is 528 int32 (16 fields + 512 tail runs)
 DECISION_INTS = 16   # lg_decision is 16 int32
 

@@ -67,11 +67,11 @@ def test_two_runs_are_bitwise_identical():
     assert any(d[0][0] for d, _ in ta), "no trigger in the run"
 
 
-@pytest.mark.parametrize("form", ["one", "portable"])
+@pytest.mark.parametrize("form", ["one", "portable", "merge"])
 def test_split_plan_changes_no_decision(form):
-    # automatic plan: the merge form, two 128-slot splits per row at cap 256; the one-launch form
-    # exchanges the same splits' partials within its launch; the portable kernels use 64-slot
-    # splits
+    # automatic plan: the launch for few rows; the merge form has two 128-slot splits per row at cap
+    # 256, the one-launch form exchanges the same splits' partials within its launch; the portable
+    # kernels use 64-slot splits
     wl, p = _tiny(80)
     a, ta, ca = _run(wl, "auto", 80, p)
     b, tb, cb = _run(wl, form, 80, p)
@@ -97,11 +97,11 @@ def test_split_plan_changes_no_decision(form):
     assert np.all(np.abs(a["lse"] - b["lse"]) <= 2e-4 * np.maximum(1, np.abs(a["lse"])))
 
 
-@pytest.mark.parametrize("form", ["one", "portable"])
+@pytest.mark.parametrize("form", ["one", "portable", "merge"])
 def test_split_plan_many_layers(form):
-    """1.5B-shaped batch 1 (28 layers, 1024-slot budget; seven 128-slot splits per row merged by a
-    second launch in the automatic plan, the same splits exchanged within one launch, or 64-slot
-    splits of the portable kernels): outputs and scores within tolerance over 12 steps, lengths
+    """1.5B-shaped batch 1 (28 layers, 1024-slot budget; the launch for few rows in the automatic plan
+    against seven 128-slot splits per row merged by a second launch, the same splits exchanged within
+    one launch, and 64-slot splits of the portable kernels): outputs and scores within tolerance over 12 steps, lengths
     and positions identical."""
     from paper_2604_10044_amd.synth import qwen15b
     wl = qwen15b(steps=12)

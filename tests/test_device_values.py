@@ -41,7 +41,7 @@ def test_attend_clamps_lengths_and_saturates_the_suffix_threshold():
     sm = torch.zeros(B, Hq, device=dev)
     conf = torch.zeros(B, device=dev)
     to = lambda a, dt=torch.bfloat16: torch.from_numpy(a).to(dev).to(dt)
-    for form in (0, 1, 2):   # the automatic (one-launch) form, the portable and the merge form
+    for form in (0, 1, 2):   # the automatic choice (few rows), the portable and the merge form
         accd.copy_(torch.from_numpy(acc0))
         Kd.copy_(torch.from_numpy(K).to(torch.bfloat16))
         Vd.copy_(torch.from_numpy(V).to(torch.bfloat16))

@@ -28,8 +28,8 @@ def _assert_same(a, b, what):
             np.testing.assert_array_equal(a[k], b[k], err_msg="%s %s" % (what, k))
 
 
-# portable kernels (automatic for float32), the one-launch form (automatic for bf16), the merge form
-@pytest.mark.parametrize("dtype,form", [("f32", 0), ("bf16", 0), ("bf16", 2)])
+# the launch for few rows (automatic for both types), the portable kernels, the merge form
+@pytest.mark.parametrize("dtype,form", [("f32", 0), ("f32", 1), ("bf16", 0), ("bf16", 2)])
 @pytest.mark.parametrize("policy", [oracle.POLICY_LOOPGUARD, oracle.POLICY_H2O])
 def test_step_graph_replay_matches_eager(policy, dtype, form):
     import dataclasses

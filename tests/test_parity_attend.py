@@ -30,6 +30,19 @@ def auto_is_single_split(cap, rows, G):
     return rows >= 128 and cap <= (2048 if G <= 8 else 1024)
 
 
+def few_rows(rows, G, D, cap, dtype):
+    """The automatic choice runs the launch for few rows (1) or not (0): at most 256 workgroups, whose
+    logits fit the LDS, of short rows, or of more and longer ones where that measures faster."""
+    f32 = dtype == "f32"
+    most = min(2048, (8192 if f32 else 16384) // (4 if G <= 4 else 8 if G <= 8 else 16))
+    if f32:
+        want = 1024 if rows > 64 else 256
+    else:
+        want = 2048 if rows > (32 if D == 128 else 64) else 1024
+    return int(rows * (D // 64) * (1 if f32 else 2) <= 256 and cap <= min(want, most)
+               and not auto_is_single_split(cap, rows, G))
+
+
 def split_plan(cap, rows, max_split, n_eff, G=7, one_launch=True):
     """Splits of a row of n_eff live slots in an MFMA launch (the library's plan: the given split
     length; by default, in the one-launch form, one split per row for launches of >= 128 rows
@@ -189,29 +202,45 @@ def test_attend_every_form_and_split(form, max_split):
     (12, 2, 128, 1024, [300, 769]), (12, 2, 128, 1024, [1000, 1023]),
     (16, 1, 64, 512, [130, 511]), (32, 2, 128, 1024, [97, 700]), (4, 4, 128, 256, [255, 129])])
 def test_fixed_chunk_rows(Hq, Hkv, D, cap, lens):
-    """Launches of a few rows (batch 2 or less): the automatic choice cuts rows into 128-slot
-    splits, which start at fixed slots, and the merging launch's grid has more workgroups than
-    most rows have splits; those past a row's last split still merge their slice of the output.
-    Lengths around the 288-slot point below which a balanced plan would have used shorter
-    splits; group sizes 6, 16 (head_dim 64 and 128) and 1 cover the three compiled group
-    bounds of the merging kernel."""
+    """The merge form with 128-slot splits, which start at fixed slots: the merging launch's grid has
+    more workgroups than most rows have splits; those past a row's last split still merge their
+    slice of the output. Lengths around the 288-slot point below which a balanced plan would have
+    used shorter splits; group sizes 6, 16 (head_dim 64 and 128) and 1 cover the three compiled
+    group bounds of the merging kernel. (The automatic choice runs these shapes in one launch.)"""
+    run_case(len(lens), Hq, Hkv, D, cap, lens, "bf16", FORMS["merge"], append=True, seed=sum(lens) + Hq,
+             max_split=128)
+
+
+def runs(Hq, Hkv, D, cap, B, dtype="bf16", form=0):
+    """What lg_decode_attend runs for a layer: (form, split, few rows)."""
     from paper_2604_10044_amd import lg
-    kv = torch.zeros(1, Hkv, cap, D, dtype=torch.bfloat16, device="cuda")
-    hdr = lg.workspace_header(make_ws(lg, lg.layer_cache(kv, kv, torch.zeros(1, Hkv, cap,
-                                                                              device="cuda"), Hq)))
-    assert (hdr["form"], hdr["split"]) == (FORMS["merge"], 128)
-    run_case(len(lens), Hq, Hkv, D, cap, lens, "bf16", 0, append=True, seed=sum(lens) + Hq)
+    kv = torch.zeros(B, Hkv, cap, D, dtype=torch.bfloat16 if dtype == "bf16" else torch.float32, device="cuda")
+    acc = torch.zeros(B, Hkv, cap, device="cuda")
+    h = lg.workspace_header(make_ws(lg, lg.layer_cache(kv, kv, acc, Hq), form))
+    return h["form"], h["split"], h["few_rows"]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,Hq,Hkv,D,cap", [(2, 14, 2, 128, 2047), (1, 4, 1, 64, 1025), (4, 32, 2, 128, 2045),
+                                            (4, 16, 1, 64, 2047), (2, 1, 1, 128, 1025)])
+def test_fixed_chunk_ragged_caps(B, Hq, Hkv, D, cap, dtype):
+    """The same in caches whose cap is no multiple of 32, of both types, by the automatic choice: the three
+    group bounds and both head_dims, rows that end in and at the last, shorter split."""
+    assert runs(Hq, Hkv, D, cap, B, dtype) == (FORMS["merge"], 128, 0)
+    lens = [cap - 1, 1024, 289, 0][:B]
+    run_case(B, Hq, Hkv, D, cap, lens, dtype, 0, append=True, seed=cap + Hq)
 
 
 @pytest.mark.parametrize("Hq,Hkv,D", [(16, 1, 128), (8, 1, 64), (4, 1, 128)])
 def test_attend_long_splits(Hq, Hkv, D):
-    """64 rows over a 2048-slot cache: the automatic choice cuts each row into 512-slot splits,
-    long enough that the split form stages its logits in LDS (group bounds 16, 8 and 4); ragged
-    lengths include a single live slot, a full cache and a split boundary."""
+    """64 rows over a 2048-slot cache, the merge form with 512-slot splits, long enough that it stages its
+    logits in LDS (group bounds 16, 8 and 4); ragged lengths include a single live slot, a full cache
+    and a split boundary."""
     rng = np.random.default_rng(Hq + D)
     lens = rng.integers(600, 2047, 64).tolist()
     lens[0], lens[1], lens[2], lens[3] = 0, 2047, 511, 1024
-    run_case(64, Hq, Hkv, D, 2048, lens, "bf16", 0, append=True, seed=Hq * 7 + D)
+    assert runs(Hq, Hkv, D, 2048, 64, form=FORMS["merge"]) == (FORMS["merge"], 512, 0)
+    run_case(64, Hq, Hkv, D, 2048, lens, "bf16", FORMS["merge"], append=True, seed=Hq * 7 + D)
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,D,cap", [(32, 28, 4, 128, 2048), (32, 32, 4, 64, 2048),
@@ -296,6 +325,7 @@ def test_few_rows(shape, dtype, append):
     """Launches of few rows: one launch in which each row is finished by its own workgroups, every
     row against the oracle, with and without the step's append."""
     B, Hq, Hkv, D, cap, lens = shape
+    assert runs(Hq, Hkv, D, cap, B, dtype)[2] == few_rows(B * Hkv, Hq // Hkv, D, cap, dtype)
     run_case(B, Hq, Hkv, D, cap, lens, dtype, 0, append=append, seed=cap + Hq)
 
 
@@ -363,6 +393,63 @@ def test_attend_suffix_extremes(form):
     np.testing.assert_allclose(sm, 1.0, atol=2e-6)
     _, _, sm, _ = run_case(2, 4, 1, 128, 128, [100, 126], "bf16", FORMS[form], seed=9, suffix_w=0)
     assert np.all(sm == 0)
+
+
+# Layers that the hook cannot give a form: few rows of both types (one wave's rounds and several), and
+# merge and single-split instances of float32 and ragged caps. (rows x (B, Hq, Hkv, D, cap))
+AUTO_EDGES = [("bf16", 1, 8, 2, 128, 512), ("bf16", 3, 16, 1, 64, 1023), ("bf16", 70, 4, 1, 64, 2048),
+              ("f32", 2, 8, 2, 128, 256), ("f32", 70, 16, 1, 64, 512), ("bf16", 3, 8, 2, 128, 2049),
+              ("f32", 3, 8, 2, 64, 1500), ("bf16", 64, 8, 2, 128, 1501), ("f32", 64, 16, 2, 64, 700)]
+
+
+@pytest.mark.parametrize("dtype,B,Hq,Hkv,D,cap", AUTO_EDGES)
+def test_auto_extremes(dtype, B, Hq, Hkv, D, cap):
+    """Logits spanning hundreds and logits near zero, no append, rows with one slot and none, and suffixes
+    wider than every position and of width 0, by the automatic choice."""
+    rng = np.random.default_rng(cap)
+    lens = ([cap - 1, 0, 1] + rng.integers(1, cap, B).tolist())[:B]
+    for kw in ({"q_scale": 40.0}, {"q_scale": 1e-3}, {"append": False}):
+        run_case(B, Hq, Hkv, D, cap, lens, dtype, 0, seed=cap, **kw)
+    _, _, sm, _ = run_case(B, Hq, Hkv, D, cap, lens, dtype, 0, seed=9, suffix_w=10 ** 6)
+    np.testing.assert_allclose(sm, 1.0, atol=2e-6)
+    _, _, sm, _ = run_case(B, Hq, Hkv, D, cap, lens, dtype, 0, seed=9, suffix_w=0)
+    assert np.all(sm == 0)
+
+
+@pytest.mark.parametrize("dtype,B,Hq,Hkv,D,cap", AUTO_EDGES)
+def test_auto_conf_and_workspace(dtype, B, Hq, Hkv, D, cap):
+    """By the automatic choice: conf may be NULL (every other output is unchanged), and a workspace that has
+    served other row lengths gives what a new one gives."""
+    from paper_2604_10044_amd import lg
+    dev = torch.device("cuda")
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(cap)
+    K, V, q = (torch.randn(*s, generator=g, device=dev, dtype=dt)
+               for s in ((B, Hkv, cap, D), (B, Hkv, cap, D), (B, Hq, D)))
+    pos = torch.arange(cap, dtype=torch.int32, device=dev).repeat(B, 1).contiguous()
+    sw = torch.full((B,), 64, dtype=torch.int32, device=dev)
+    acc0 = torch.rand(B, Hkv, cap, generator=g, device=dev)
+
+    def one(ws, lens, conf):
+        acc = acc0.clone()
+        layer = lg.layer_cache(K, V, acc, Hq)
+        ws = make_ws(lg, layer) if ws is None else ws
+        out = torch.zeros(B, Hq, D, dtype=dt, device=dev)
+        lse, sm = torch.zeros(B, Hq, device=dev), torch.zeros(B, Hq, device=dev)
+        n = torch.tensor(lens, dtype=torch.int32, device=dev)
+        lg.lg_decode_attend(layer, q, None, None, out, pos, n, n, sw, lse, sm, conf, ws)
+        torch.cuda.synchronize()
+        assert lg.workspace_header(ws)["status"] == 0
+        return (out, lse, sm, acc), ws
+
+    rng = np.random.default_rng(B)
+    ws = None
+    for step in range(4):
+        lens = rng.integers(0, cap + 1, B).tolist()
+        got, ws = one(ws, lens, torch.zeros(B, device=dev))
+        for ref in (one(None, lens, torch.zeros(B, device=dev))[0], one(None, lens, None)[0]):
+            for x, y in zip(got, ref):
+                assert torch.equal(x, y), (step, lens)
 
 
 def _rand_layer(B, Hq, Hkv, D, cap, seed):
@@ -709,7 +796,9 @@ def _full_size_layer_case(wl, layer_id, pairs, form=0, max_split=0, flags=0):
     assert hd["status"] == 0
     if form == 0:
         # bfloat16 layers run the one-launch form when every row is one split, else the merge
-        # form, with the library's split plan
+        # form with the library's split plan, or the launch for few rows
+        assert hd["few_rows"] == few_rows(wl.batch * wl.n_kv_heads, wl.n_q_heads // wl.n_kv_heads, wl.head_dim,
+                                          wl.cap, "bf16")
         G = wl.n_q_heads // wl.n_kv_heads
         rows = wl.batch * wl.n_kv_heads
         one = auto_is_single_split(wl.cap, rows, G)
