@@ -74,23 +74,26 @@ constexpr int few_max_slots(bool f32, int SG) {
 
 // Launches of few rows that attend_few takes instead of the merge form. Its workgroups (at most one
 // per CU) each read their whole K row, so it wins where rows are short, or where the rows are many
-// enough that the merge form's splits are as long. Measured on MI355X, us a layer in a graph,
-// attend_few / merge form, rows 80% full, 4 heads a group:
-//   bf16, head_dim 128  cap 256: 1 row 5.5 / 8.8, 64 rows 6.9 / 10.4; cap 1024: 1 row 7.8 / 9.6,
-//                       64 rows 10.3 / 12.6, 120 rows 18.5 / 16.5; cap 2048: 1 row 12.4 / 9.7,
-//                       32 rows 13.5 / 13.1, 64 rows 15.7 / 17.6
-//   bf16, head_dim 64   cap 1024: 1 row 6.9 / 8.2, 120 rows 9.4 / 12.9; cap 2048: 1 row 10.7 / 8.7,
-//                       32 rows 11.8 / 10.6, 120 rows 14.0 / 16.3
-//   f32, head_dim 128   cap 256: 1 row 8.6 / 11.5; cap 512: 11.6 / 11.5; cap 1024: 1 row 18.9 / 11.8,
-//                       64 rows 20.8 / 18.8, 120 rows 22.9 / 26.4; cap 2048: 120 rows 47.1 / 41.7
-//   f32, head_dim 64    cap 256: 1 row 6.9 / 9.3; cap 512: 10.1 / 9.6; cap 1024: 120 rows 16.7 / 19.2
+// enough that the merge form's splits are as long. Measured on MI355X, us a layer in a graph of 8
+// layers (rows 80% full, caches not resident in the last-level cache), attend_few / merge form, at 4
+// heads a group; groups of 1, 8 and 16 heads change sides at the same points:
+//   bf16, head_dim 128  cap 256: 1 row 5.2 / 8.8, 64 rows 6.8 / 10.0; cap 1024: 1 row 7.7 / 9.7,
+//                       64 rows 10.7 / 12.8; cap 1536: 40 rows 14.0 / 13.0, 64 rows 18.4 / 14.9;
+//                       cap 2048: 40 rows 19.2 / 14.7, 64 rows 23.2 / 17.6
+//   bf16, head_dim 64   cap 1024: 1 row 6.9 / 8.2; cap 2048: 1 row 10.7 / 8.7, 32 rows 11.8 / 10.6,
+//                       96 rows 16.2 / 16.1, 127 rows 17.3 / 17.7
+//   f32, head_dim 128   cap 256: 1 row 9.2 / 12.1, 64 rows 10.2 / 14.0; cap 512: 1 row 11.6 / 11.5,
+//                       65 rows 13.9 / 16.6, 120 rows 18.8 / 20.0; cap 768: 65 rows 20.5 / 19.8
+//   f32, head_dim 64    cap 256: 1 row 7.3 / 9.7, 64 rows 8.4 / 10.8; cap 512: 1 row 10.1 / 9.6; cap 768:
+//                       65 rows 13.0 / 14.2, 127 rows 16.2 / 17.6; cap 1024: 65 rows 16.3 / 16.5, at 8
+//                       heads 17.0 / 16.7
 inline bool few_rows(const lg_layer_cache& c) {
   const bool f32 = c.dtype == LG_F32;
   const long rows = (long)c.batch * c.n_kv_heads;
   const int G = c.n_q_heads / c.n_kv_heads;
   const int most = few_max_slots(f32, G <= 4 ? 4 : G <= 8 ? 8 : 16);
-  const bool many = rows > (!f32 && c.head_dim == 128 ? 32 : 64);
-  const int want = f32 ? (many ? 1024 : 256) : (many ? 2048 : 1024);
+  const int want = rows <= 64 ? (f32 ? 256 : 1024)
+                   : c.head_dim == 128 ? 512 : (f32 ? 768 : 2048);  // head_dim 128: float32 only
   return rows * few_dsplit(f32, c.head_dim) <= kTargetWorkgroups && c.cap <= want && c.cap <= most;
 }
 
