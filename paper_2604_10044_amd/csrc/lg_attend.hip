@@ -7,12 +7,11 @@
 //   H2O increment acc[j] += sum over the group's query heads of alpha_j (Sec. 2.2, Sec. 6.1)
 //   confidence    conf[b] = max(conf[b], max_h suffix mass)
 //
-// The slots of each row (sequence, kv head) are cut into splits, one workgroup each. Three forms:
-//   one-launch  (bfloat16) the row is finished in the same launch: by its own workgroup(s) when
-//               it is a single split (the automatic choice for launches of at least 128 rows
-//               whose cap fits one split), else by its splits exchanging their partials through
-//               memory; no workgroup waits for one that may not have started (see the exchange
-//               below).
+// The slots of each row (sequence, kv head) are cut into splits, one workgroup each. The forms:
+//   one-launch  the row is finished in the same launch: by its own workgroup(s) when it is a single
+//               split (the automatic choice for launches of at least 128 rows whose cap fits one
+//               split), else (test hook) by its splits exchanging their partials through memory; no
+//               workgroup waits for one that may not have started (see the exchange below).
 //   merge       (the automatic choice otherwise) each split writes its partial and its logits to
 //               memory and attend_combine_mfma merges them in a second launch.
 //   few rows    (the automatic choice instead of the merge form where few_rows() says so) one
@@ -152,7 +151,7 @@ __global__ __launch_bounds__(64) void attend_valu(AttendArgs a) {
 }
 
 // -------------------------------------------------------------------------------------------
-// MFMA sweep (bfloat16 cache).
+// MFMA sweep.
 //
 // Each workgroup (kWaves waves) owns one split of a (sequence, kv head): a contiguous, 32-aligned
 // slot range, balanced so every split of the row has about the same length. Its waves take the
@@ -210,12 +209,12 @@ __device__ __forceinline__ SplitPlan split_plan(int n, int max_split) {
 // A float32 row is twice as long. Everything above counts bytes (a k-step is 64 bytes of each row),
 // so head_dim 64 is cut exactly like a bfloat16 head_dim 128; at head_dim 128 a block is one tile of
 // 16 slots (A-row i = slot i), which keeps a block at 16 KB and its registers as they are.
-// The f32 MFMA (128 of them a block, 32 cycles each) take about a quarter of the time the block's
-// bytes take, so the sweep stays bound by memory. Measured against the vector-ALU sweep that these
+// The f32 MFMA (64 of them a block, 32 cycles each) take about an eighth of the time the block's bytes
+// take, so the sweep stays bound by memory. Measured against the vector-ALU sweep that these
 // caches had (one wave per 64 slots, a 64-lane reduction per slot and head): batch 8, 32 / 8 heads,
-// head_dim 128, cap 2048 float32 215 -> 29 us a layer (119 MB); batch 5, 32 / 8 heads, head_dim 64,
-// bfloat16 at cap 1500 (no multiple of 32) 134 -> 16 us; batch 1, 4 / 4 heads, head_dim 64, cap 256
-// float32 49 -> 14 us (all but the first now bound by their launches).
+// head_dim 128, cap 2048 float32 215 -> 29.5 us a layer (119 MB); batch 5, 32 / 8 heads, head_dim 64,
+// bfloat16 at cap 1500 (no multiple of 32) 134 -> 14.5 us; batch 1, 4 / 4 heads, head_dim 64, cap 256
+// float32 49 -> 12 us in attend_few (the last two bound by their launches and the call).
 template <typename T, int D, int DV = D>
 struct Geo {
   static constexpr bool F32 = sizeof(T) == 4;
@@ -247,7 +246,7 @@ struct RowCtx {
   const char* vbase;  // lane's V address at slot 0 (see load_v)
   int vrow;           // the slot of a block that vbase stands for
   const int32_t* posb;
-  int L, app, cap, n_eff;
+  int cap, n_eff;
   int jsuf;  // first slot of the recent suffix within the split (see attend_mfma_body)
   // The appended row: slot lsub (-1 when this split does not hold it) takes the new K and V rows
   // staged in LDS (snew: D / 8 16-byte pieces of K, then of V) in place of what the cache held;
@@ -1611,8 +1610,6 @@ __device__ __forceinline__ void attend_mfma_body(const AttendArgs& a) {
     const uint4* h = (const uint4*)a.hdr;
     hd0 = h[0]; hd1 = h[1]; hd2 = h[2];
   }
-  rc.L = L;
-  rc.app = app;
   rc.n_eff = n_eff;
 
   QFrag<T, D> qf;
@@ -1759,7 +1756,8 @@ void attend_mfma(AttendArgs a) {
 // wave needs waits for something else: scores, queries, new rows, the header and then its first
 // block with its positions are requested before the row's length is known, and no barrier
 // precedes the sweep. Two rows of 733 slots, bfloat16, head_dim 128: the block loads are out after 1.5
-// to 3.5 us, the sweep ends at 6.5, the row is merged at 7.2 and written at 8.
+// to 3.5 us, the sweep ends at 6.5, the row is merged at 7.2 and written at 8 (stamps taken before the
+// merge's sums were in double, which adds 0.2).
 // -------------------------------------------------------------------------------------------
 template <typename T, int D, bool RC, int SG, int MS, int NW, int DS>
 __global__ __launch_bounds__(64 * NW) void attend_few(AttendArgs a) {
@@ -1853,8 +1851,6 @@ __global__ __launch_bounds__(64 * NW) void attend_few(AttendArgs a) {
     wave_lds_fence();
   }
   const bool t_in = a.t[b] > thr;  // the appended slot is in the recent suffix
-  rc.L = L;
-  rc.app = app;
   rc.n_eff = n;
   rc.lsub = app ? L : -1;
   __shared__ __attribute__((aligned(16))) float slog[SG * MS];
