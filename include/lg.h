@@ -263,6 +263,10 @@ lg_status lg_decode_attend_workspace_init(const lg_layer_cache* layer, void* wor
  * and exits. Its waits are still bounded (about 0.1 s); see the status word above. Longer
  * caches run a portable kernel pair. Sequences with no live slot and no appended row produce out = 0,
  * lse = -inf, suffix_mass = 0.
+ * Infinite V values: alpha multiplies V as a float32 in float32 caches, in caches whose cap is no
+ * multiple of 32 and in the portable pair, so +-inf in a slot with alpha > 0 gives +-inf. In the other
+ * bfloat16 caches alpha is a sum of two bfloat16 terms, the second 0 where alpha is one itself, and
+ * the product may be NaN.
  */
 lg_status lg_decode_attend(const lg_layer_cache* layer, const void* q, const void* k_new,
                            const void* v_new, void* out, const int32_t* pos, const int32_t* len,

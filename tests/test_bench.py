@@ -82,3 +82,10 @@ def test_bench_json_line():
     # nothing triggers and nothing overflows
     assert d["interventions"] == 0 and d["overflow_compactions"] == 0
     assert d["step_frac_of_copy"] > 0 and d["copy_gbps"] > 0
+
+
+def test_attend_kernel_name():
+    """The launch for few rows runs on the merge form's workspace and is named by the header's own word."""
+    name = lambda form, few: bench.attend_kernel_name({"form": form, "split": 128, "few_rows": few})  # noqa: E731
+    assert "attend_few" in name(2, 1) and "merge" not in name(2, 1)
+    assert "merge form" in name(2, 0) and "one-launch" in name(3, 0)
