@@ -2346,7 +2346,7 @@ hipError_t launch_mfma_form(AttendArgs a, hipStream_t st);
 // The build compiles this file once per part, in parallel, each with the kernels of one cache type
 // and head_dim; part 0 holds the portable kernels and the dispatch.
 #if LG_ATTEND_PART > 0
-// Few rows (the plan has cap <= few_max_slots, and <= 1024 but for bfloat16 at head_dim 64). 16 waves where the logits leave
+// Few rows (the plan has cap <= few_max_slots, and <= 1024 in float32). 16 waves where the logits leave
 // the LDS for it (bfloat16: the step of a 1.5B-shaped batch of one 261 us with 16 waves, 271 with 8);
 // 8 for a ragged cap at head_dim 128, whose third alpha term does not fit the 128 registers of 16 waves
 // (36 of them spilled). A second block in flight per wave is slower (its loads only queue in the CU's
@@ -2366,7 +2366,7 @@ static hipError_t launch_few(const AttendArgs& a, hipStream_t st) {
     if (a.cap <= most) return launch_few_ms<T, D, RC, SG, most>(a, st);
   } else {
     if (a.cap <= 1024) return launch_few_ms<T, D, RC, SG, 1024>(a, st);
-    if constexpr (sizeof(T) == 2 && D == 64) return launch_few_ms<T, D, RC, SG, most>(a, st);
+    if constexpr (sizeof(T) == 2) return launch_few_ms<T, D, RC, SG, most>(a, st);
   }
   return hipErrorInvalidValue;  // the plan never gives this
 }

@@ -76,14 +76,19 @@ constexpr int few_max_slots(bool f32, int SG) {
 // per CU) each read their whole K row, so it wins where rows are short, or where the rows are many
 // enough that the merge form's splits are as long. Measured on MI355X, us a layer in a graph of 8
 // layers (rows 80% full, caches not resident in the last-level cache), attend_few / merge form, at 4
-// heads a group; groups of 1, 8 and 16 heads change sides at the same points:
+// heads a group; groups of 1 to 16 heads change sides at the same points but for the line given.
+// Launched call by call the merge form's second launch costs 3 us more (54 rows, bf16, head_dim 128, cap
+// 1270 12.7 / 16.1), so ties, and 33 to 64 rows up to cap 1280, go to attend_few:
 //   bf16, head_dim 128  cap 256: 1 row 5.2 / 8.8, 64 rows 6.8 / 10.0; cap 1024: 1 row 7.7 / 9.7,
-//                       64 rows 10.7 / 12.8; cap 1536: 40 rows 14.0 / 13.0, 64 rows 18.4 / 14.9;
-//                       cap 2048: 40 rows 19.2 / 14.7, 64 rows 23.2 / 17.6
+//                       64 rows 10.7 / 12.8; cap 1280, attend_few over merge form: 33 rows 0.98, 48
+//                       rows 1.00, 64 rows 1.09, at 8 heads 0.85 to 0.87 and at cap 1408 0.84 to
+//                       0.92; cap 1536: 40 rows 14.0 / 13.0, 64 rows 18.4 / 14.9; cap 2048: 40 rows
+//                       19.2 / 14.7, 64 rows 23.2 / 17.6
 //   bf16, head_dim 64   cap 1024: 1 row 6.9 / 8.2; cap 2048: 1 row 10.7 / 8.7, 32 rows 11.8 / 10.6,
 //                       96 rows 16.2 / 16.1, 127 rows 17.3 / 17.7
 //   f32, head_dim 128   cap 256: 1 row 9.2 / 12.1, 64 rows 10.2 / 14.0; cap 512: 1 row 11.6 / 11.5,
-//                       65 rows 13.9 / 16.6, 120 rows 18.8 / 20.0; cap 768: 65 rows 20.5 / 19.8
+//                       65 rows 13.9 / 16.6, 120 rows 18.8 / 20.0; cap 768: 65 rows 20.5 / 19.8,
+//                       96 rows 22.9 / 23.1; cap 1024: 65 rows 24.8 / 22.1, 120 rows 28.8 / 28.2
 //   f32, head_dim 64    cap 256: 1 row 7.3 / 9.7, 64 rows 8.4 / 10.8; cap 512: 1 row 10.1 / 9.6; cap 768:
 //                       65 rows 13.0 / 14.2, 127 rows 16.2 / 17.6; cap 1024: 65 rows 16.3 / 16.5, at 8
 //                       heads 17.0 / 16.7
@@ -92,8 +97,9 @@ inline bool few_rows(const lg_layer_cache& c) {
   const long rows = (long)c.batch * c.n_kv_heads;
   const int G = c.n_q_heads / c.n_kv_heads;
   const int most = few_max_slots(f32, G <= 4 ? 4 : G <= 8 ? 8 : 16);
-  const int want = rows <= 64 ? (f32 ? 256 : 1024)
-                   : c.head_dim == 128 ? 512 : (f32 ? 768 : 2048);  // head_dim 128: float32 only
+  const bool wide = c.head_dim == 128;
+  const int want = rows <= 64 ? (f32 ? 256 : wide && rows > 32 ? (G > 4 ? 1408 : 1280) : 1024)
+                   : wide ? 768 : (f32 ? 1024 : 2048);  // more rows of head_dim 128: float32 only
   return rows * few_dsplit(f32, c.head_dim) <= kTargetWorkgroups && c.cap <= want && c.cap <= most;
 }
 

@@ -36,9 +36,9 @@ def few_rows(rows, G, D, cap, dtype):
     f32 = dtype == "f32"
     most = min(2048, (8192 if f32 else 16384) // (4 if G <= 4 else 8 if G <= 8 else 16))
     if rows <= 64:
-        want = 256 if f32 else 1024
+        want = 256 if f32 else 1024 if D == 64 or rows <= 32 else 1408 if G > 4 else 1280
     else:
-        want = 512 if D == 128 else 768 if f32 else 2048
+        want = 768 if D == 128 else 1024 if f32 else 2048
     return int(rows * (D // 64) * (1 if f32 else 2) <= 256 and cap <= min(want, most)
                and not auto_is_single_split(cap, rows, G))
 
@@ -306,7 +306,7 @@ def test_attend_ragged_caps(shape, dtype):
 
 
 # caps, rows and group sizes around the few-rows kernel's instances and its rule: one wave's block and
-# 16 waves' round (32, 512), 256, 512, 768, 1024 and 2048 slots, 64 / 65 and 128 rows
+# 16 waves' round (32, 512), 256, 768, 1024, 1280, 1408 and 2048 slots, 32 / 33, 64 / 65 and 128 rows
 FEW_ROWS = [
     (1, 1, 1, 64, 32, [31]), (1, 16, 1, 128, 33, [32]), (2, 8, 1, 128, 512, [511, 480]),
     (2, 8, 1, 64, 513, [512, 31]), (1, 6, 2, 128, 1024, [1023]), (2, 32, 2, 128, 1024, [1000, 0]),
@@ -314,8 +314,10 @@ FEW_ROWS = [
     (32, 4, 1, 128, 1024, [1023, 0] + list(range(400, 430))), (32, 7, 1, 128, 2048, [2047, 0] + list(range(600, 630))),
     (33, 7, 1, 128, 2048, [2047, 0] + list(range(1600, 1631))), (64, 16, 1, 128, 1024, [1023, 0] + list(range(500, 562))),
     (65, 8, 1, 64, 2048, [2047, 0] + list(range(1200, 1263))), (65, 4, 1, 128, 1024, [1023, 1] + list(range(300, 363))),
-    (65, 4, 1, 128, 512, [511, 1] + list(range(300, 363))), (65, 16, 1, 128, 513, [512, 1] + list(range(300, 363))),
-    (65, 8, 1, 64, 768, [767, 1] + list(range(500, 563))), (65, 4, 1, 64, 769, [768, 1] + list(range(500, 563))),
+    (65, 4, 1, 128, 768, [767, 1] + list(range(300, 363))), (65, 8, 1, 128, 769, [768, 1] + list(range(300, 363))),
+    (65, 8, 1, 64, 1024, [1023, 1] + list(range(500, 563))), (65, 4, 1, 64, 1025, [1024, 1] + list(range(500, 563))),
+    (33, 4, 1, 128, 1280, [1279, 1] + list(range(900, 931))), (33, 4, 1, 128, 1281, [1280, 1] + list(range(900, 931))),
+    (16, 28, 4, 128, 1408, [1407, 1] + list(range(900, 914))), (32, 14, 2, 128, 1409, [1408, 1] + list(range(900, 930))),
     (127, 4, 1, 64, 1024, [1023, 1] + list(range(300, 425))), (43, 9, 3, 128, 300, [299, 1] + list(range(200, 241))),
 ]
 
